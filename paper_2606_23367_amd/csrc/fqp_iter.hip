@@ -818,34 +818,6 @@ constexpr int kCapH = 2 * kCapT;        // held rows kept in registers (two per 
 // push the kernel past the 64 registers a lane may use with two accounts per
 // compute unit
 
-// one safeguarded Newton step on turnover(lam) = tau from the summed
-// turnover gt and free count nft at lam; updates the bracket [lo, hi_b], the
-// best multiplier known to be feasible and returns the next multiplier
-__device__ __forceinline__ float cap_step(float gt, float nft, float tau, float rho, float lam,
-                                          float& lo, float& hi_b, float& best_feas,
-                                          bool& done) {
-  const float tol = 1e-6f * fmaxf(tau, 1e-6f);
-  if (gt <= tau) { hi_b = lam; best_feas = lam; } else { lo = lam; }
-  done = fabsf(gt - tau) <= tol || (lam == 0.f && gt <= tau);
-  float nl = lam;
-  if (!done) {
-    nl = (nft > 0.f) ? lam + rho * (gt - tau) / nft : NAN;
-    if (gt <= tau && !(nl > 0.f) && lo == 0.f && lam > 0.f) {
-      nl = 0.f;                        // try the unconstrained multiplier
-    } else if (!(nl > lo && nl < hi_b)) {
-      nl = isfinite(hi_b) ? 0.5f * (lo + hi_b) : fmaxf(2.f * lam, lam + 1e-4f);
-    }
-    if (isfinite(hi_b) && hi_b - lo <= 1e-6f * hi_b && lo > 0.f) { done = true; nl = hi_b; }
-  }
-  return fmaxf(nl, 0.f);
-}
-
-// the multiplier the search hands on: never one whose turnover is known to
-// exceed tau
-__device__ __forceinline__ float cap_result(float lam, bool done, float best_feas) {
-  return (!done && isfinite(best_feas)) ? best_feas : lam;
-}
-
 // the account's rows as seen by the output phase: base pointers the whole
 // workgroup shares, so that a row is addressed by its 32-bit index
 struct ProxRows {

@@ -115,6 +115,57 @@ hipError_t launch_kfactor(int k, int G, int kp, int nparts, const double* part, 
                           double gamma, double rho_b, double* Kw, float* Kinv, float* c,
                           float* q, float* sig, float* mbg, hipStream_t st);
 
+// ---- account-resident iterations -------------------------------------------
+// the trade lines and lot indices of every row, [m][npr] (npr: rows padded
+// to whole 64-row tiles)
+struct ResRowArgs {
+  int n, npr, W, m;
+  const float* mu;
+  const float* lb;
+  const float* ub;
+  const float* lbv;          // [m][n] per-asset bounds or null
+  const float* ubv;
+  const uint32_t* elig;
+  const uint32_t* hold;
+  const int32_t* hold_pre;
+  const int32_t* hold_ptr;
+  const float4* hold_rec;
+  float4* rows;              // [m][npr] out: {mu, w0, lb, ub}
+  int32_t* lot;              // [m][npr] out: lot record or -1; null without tax
+};
+
+struct ResArgs {
+  int n, npr, ntile, k, G, kp, ncls;
+  const int* m_act;
+  const int* act;
+  const float4* Bq;          // B~ in tile order (fqp_resident.hip)
+  const float4* rows;
+  const int32_t* lot;
+  const float4* hold_rec;
+  const float* d;
+  float* v;                  // [m][n] ADMM state
+  float* zs;                 // [m][n] z of the state a block ends with
+  float* par;
+  const float* Kinv;
+  const float* cvec;
+  const float* qvec;
+  const float* sig1;
+  const float* mbg;
+  float* zb;
+  float* vb;
+  const float* blo;
+  const float* bhi;
+  int* iters;
+};
+// quarter of the padded factor width the resident kernel is compiled for
+int resident_kq(int kw);
+// whether a book of m accounts runs its blocks account-resident: kw = used
+// columns of B~, ncap = accounts with a turnover cap
+bool resident_fits(int n, int kw, int G, bool lots, int m, int ncap, int n_cu);
+hipError_t launch_resident_setup(const ResRowArgs& A, int kp, int KQ, const float* Bt, float4* Bq,
+                                 hipStream_t st);
+hipError_t launch_resident(const ResArgs& A, int KQ, int m_total, int count, hipStream_t st);
+
 // ---- packing / validation -------------------------------------------------
 struct PackArgs {
   int n, W, m, G;            // G: constraint rows (bands, then halfspaces)
@@ -145,8 +196,9 @@ struct PackArgs {
   int32_t* hold_tax;
   int32_t* status;          // [m]
   float* par;               // [m][kNPar]
-  // pinned host memory (device address) or null: the total of held names
-  // and the most held names of one account, stored by the scan
+  // pinned host memory (device address) or null: [0] the total of held names,
+  // [1] the most held names of one account, [4] the accounts with a finite
+  // turnover cap, stored by the scan
   int32_t* host_counts;
 };
 hipError_t launch_pack_count(const PackArgs& A, hipStream_t st);

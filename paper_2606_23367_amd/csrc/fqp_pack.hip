@@ -123,18 +123,20 @@ __global__ __launch_bounds__(256) void pack_count_kernel(PackArgs A) {
 __global__ void pack_scan_kernel(PackArgs A) {
   // exclusive scan of hold_cnt into hold_ptr (single workgroup); the total
   // goes to hold_ptr[m], the largest count of one account to hold_ptr[m + 1]
-  __shared__ int carry, most;
+  __shared__ int carry, most, caps;
   __shared__ int sh[256];
   if (threadIdx.x == 0) {
     carry = 0;
     most = 0;
+    caps = 0;
   }
   __syncthreads();
-  int mx = 0;
+  int mx = 0, nc = 0;
   for (int base = 0; base < A.m; base += 256) {
     const int i = base + threadIdx.x;
     const int v = (i < A.m) ? A.hold_cnt[i] : 0;
     mx = max(mx, v);
+    nc += (i < A.m && isfinite(A.tau[i])) ? 1 : 0;
     sh[threadIdx.x] = v;
     __syncthreads();
     for (int o = 1; o < 256; o <<= 1) {
@@ -149,6 +151,7 @@ __global__ void pack_scan_kernel(PackArgs A) {
     __syncthreads();
   }
   atomicMax(&most, mx);
+  atomicAdd(&caps, nc);
   __syncthreads();
   if (threadIdx.x == 0) {
     A.hold_ptr[A.m] = carry;
@@ -156,6 +159,7 @@ __global__ void pack_scan_kernel(PackArgs A) {
     if (A.host_counts) {
       A.host_counts[0] = carry;
       A.host_counts[1] = most;
+      A.host_counts[4] = caps;
     }
   }
 }

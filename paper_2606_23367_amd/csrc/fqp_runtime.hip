@@ -229,8 +229,9 @@ struct DevBuf {
 struct GraphKey {
   IterArgs ia;
   KArgs ka;
+  ResArgs ra;
   unsigned gx, gy, gpx, gpy;
-  int m, kp, precision, count, cap_resident;
+  int m, kp, precision, count, cap_resident, kq;
 };
 
 struct fqp_handle {
@@ -242,8 +243,9 @@ struct fqp_handle {
   hipEvent_t ev_t[4] = {nullptr, nullptr, nullptr, nullptr};   // phase timing
   // polish rounds: refining-account counts read back behind the launches
   hipEvent_t ev_r[4] = {nullptr, nullptr, nullptr, nullptr};
-  // [8] pinned host memory: [0, 4) round counts, [4, 6) held names, [6]
-  // valid accounts at set-up, [7] accounts left after a certification pass;
+  // [16] pinned host memory: [0, 4) round counts, [4, 6) held names, [6]
+  // valid accounts at set-up, [7] accounts left after a certification pass,
+  // [8] accounts with a turnover cap;
   // kernels store the counts there themselves (no copy launch)
   int32_t* hcount = nullptr;
   int32_t* hcount_dev = nullptr;  // the same memory, as the device addresses it
@@ -403,7 +405,7 @@ fqp_error fqp_create(fqp_handle** h, int device) {
   for (int q = 0; q < 4 && ok; ++q) ok = hipEventCreate(&hh->ev_t[q]) == hipSuccess;
   for (int q = 0; q < 4 && ok; ++q)
     ok = hipEventCreateWithFlags(&hh->ev_r[q], hipEventDisableTiming) == hipSuccess;
-  ok = ok && hipHostMalloc((void**)&hh->hcount, 8 * sizeof(int32_t), hipHostMallocDefault) ==
+  ok = ok && hipHostMalloc((void**)&hh->hcount, 16 * sizeof(int32_t), hipHostMallocDefault) ==
                  hipSuccess;
   ok = ok && hipHostGetDevicePointer((void**)&hh->hcount_dev, hh->hcount, 0) == hipSuccess;
   ok = ok && hipHostMalloc((void**)&hh->hstat, 4 * sizeof(long long), hipHostMallocDefault) ==
@@ -768,8 +770,7 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   // memory while the factor-space set-up below runs
   HIP_CHECK(hipEventRecord(h->ev_pack, st));
 
-  // ---- universe: bf16 copies of B~ and the factor-space blocks per class
-  if (split) HIP_CHECK(launch_split_bt(n, npad, kp, Bt, bt_hi, bt_lo, btt_hi, btt_lo, st));
+  // ---- universe: the factor-space blocks per class
   for (int c = 0; c < ncls; ++c) {
     HIP_CHECK(launch_gram(n, kp, kg, nparts, gram_rows, Bt, U->d, cls_gamma[c], rho_cls[c], gpart, st));
     HIP_CHECK(launch_kfactor(k, G, kp, nparts, gpart, U->f, cls_gamma[c], rho_b,
@@ -781,7 +782,34 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   const int n_held = h->hcount[4], max_held = h->hcount[5];
   const bool cap_resident = cap_resident_fits(n, max_held) && P->lb_asset == nullptr;
   WS(hold_rec, float4, "hold_rec", 2 * (size_t)std::max(n_held, 1));
+  // blocks of iterations account-resident, or by the four passes (the passes
+  // when their launches are to be timed)
+  const bool lots = P->tax_ptr != nullptr;
+  const bool resident =
+      !S.profile && resident_fits(n, kg + 1, G, lots, m, h->hcount[8], h->n_cu);
+  const int KQ = resident ? resident_kq(kg + 1) : 0;
+  const int ntile = (n + 63) / 64, npr = 64 * ntile;
+  WS(Bq, float4, "Bq", resident ? (size_t)ntile * KQ * 64 : 1);
+  WS(rows, float4, "res_rows", resident ? (size_t)m * npr : 1);
+  WS(lot, int32_t, "res_lot", resident && lots ? (size_t)m * npr : 1);
   HIP_CHECK(launch_pack_rec(pk, hold_rec, n_held, st));
+  ResArgs ra;
+  std::memset(&ra, 0, sizeof(ra));
+  if (resident) {
+    ResRowArgs rr{};
+    rr.n = n; rr.npr = npr; rr.W = W; rr.m = m; rr.mu = mu_use; rr.lb = P->lb; rr.ub = P->ub;
+    rr.lbv = P->lb_asset; rr.ubv = P->ub_asset; rr.elig = P->eligible; rr.hold = hold;
+    rr.hold_pre = hold_pre; rr.hold_ptr = hold_ptr; rr.hold_rec = hold_rec; rr.rows = rows;
+    rr.lot = lots ? lot : nullptr;
+    HIP_CHECK(launch_resident_setup(rr, kp, KQ, Bt, Bq, st));
+    ra.n = n; ra.npr = npr; ra.ntile = ntile; ra.k = k; ra.G = G; ra.kp = kp; ra.ncls = ncls;
+    ra.m_act = m_act; ra.act = act; ra.Bq = Bq; ra.rows = rows; ra.lot = rr.lot;
+    ra.hold_rec = hold_rec; ra.d = U->d; ra.v = v; ra.zs = z; ra.par = par; ra.Kinv = Kinv;
+    ra.cvec = cvec; ra.qvec = qvec; ra.sig1 = sig1; ra.mbg = mbg; ra.zb = zb; ra.vb = vb;
+    ra.blo = rlo; ra.bhi = rhi; ra.iters = iters;
+  } else if (split) {
+    HIP_CHECK(launch_split_bt(n, npad, kp, Bt, bt_hi, bt_lo, btt_hi, btt_lo, st));
+  }
   h->stats.workspace_bytes = h->total_bytes;
   h->stats.workspace_requests = h->requests;
 
@@ -890,6 +918,8 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   key.gx = igrid.x; key.gy = igrid.y; key.gpx = igrid_p.x; key.gpy = igrid_p.y;
   key.m = m; key.kp = kp; key.precision = S.precision; key.count = S.check_every;
   key.cap_resident = cap_resident ? 1 : 0;
+  key.ra = ra;
+  key.kq = KQ;
 
   // graph_reused reports a call that captured nothing: every block replayed
   // the graph kept from an earlier call
@@ -903,7 +933,8 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
         h->drop_graph();
         HIP_CHECK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
         for (int c = 0; c < count; ++c) {
-          hipError_t e1 = launch_iteration(c);
+          const hipError_t e1 = resident ? launch_resident(ra, KQ, m, count, st) : launch_iteration(c);
+          if (resident) c = count;
           if (e1 != hipSuccess) {
             hipGraph_t tmp = nullptr;
             (void)hipStreamEndCapture(st, &tmp);
@@ -919,7 +950,8 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
       }
       HIP_CHECK(hipGraphLaunch(h->gexec, st));
     } else {
-      for (int c = 0; c < count; ++c) HIP_CHECK(launch_iteration(c));
+      if (resident) HIP_CHECK(launch_resident(ra, KQ, m, count, st));
+      else for (int c = 0; c < count; ++c) HIP_CHECK(launch_iteration(c));
       if (S.profile) {
         HIP_CHECK(hipStreamSynchronize(st));
         const int cb = 2 * S.check_every;
@@ -980,7 +1012,8 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
     if (done_iters < S.first_check && done_iters < S.max_iter) continue;
     HIP_CHECK(hipEventRecord(h->ev_t[2], st));
     // polish + certification rounds on z = prox(v; lam*)
-    HIP_CHECK(launch_prox(ia, m, cap_resident, 1, st));   // z = prox(v; lam*)
+    // (account-resident blocks leave it behind)
+    if (!resident) HIP_CHECK(launch_prox(ia, m, cap_resident, 1, st));
     pa.nf_gate = std::max(4 * k + 64, n / 8 + 4 * k);
     pa.nf_small = 2 * k + 32;
     pa.max_prop = 16;
@@ -1026,7 +1059,7 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   if (!count_known && (e = first_count()) != FQP_OK) return e;   // no block ran
   if (active > 0) {
     // last pattern from the current iterate, diagnostics, final statuses
-    HIP_CHECK(launch_prox(ia, m, cap_resident, 1, st));   // z = prox(v; lam*)
+    if (!resident) HIP_CHECK(launch_prox(ia, m, cap_resident, 1, st));   // z = prox(v; lam*)
     pa.first_round = 1;
     pa.nf_gate = 0;
     pa.nf_small = 0;
