@@ -37,6 +37,7 @@ enum PState {
   PS_CAP = 0, PS_NF, PS_NX, PS_NC, PS_DONE, PS_ROUNDS,
   PS_BACT0, PS_BACT1, PS_BUP0, PS_BUP1, PS_STALL, PS_ND, PS_SIG,
   PS_BLOCK,            // the fixed row a null-direction step releases (row * 16 + code), or -1
+  PS_TICK,             // row blocks of a null-direction pass that have finished (0 between passes)
   kNPState
 };
 static_assert(kNPState <= kPStateStride, "polish bookkeeping does not fit");
@@ -548,6 +549,8 @@ constexpr int kRR = 2;                    // rows per thread
 constexpr int kRB = kRT * kRR;            // rows per block
 constexpr int kRW = kRT / 64;             // waves
 constexpr int kPU = 2;                    // rows per thread and step of the one-workgroup sweeps
+constexpr int kSplitDir = 32;             // row blocks from which several null directions are
+                                          // swept by row blocks, a launch each
 
 // polish_rows partials per (account, block): the column sums of B~ over the
 // block's nonzero fixed rows (k + G), then budget sum, turnover sum, free
@@ -1427,10 +1430,21 @@ __device__ __forceinline__ SweepDir sweep_dir(const int* ps, const double* nv,
   return D;
 }
 
+// the direction's entry of every constraint row (0: inactive), into LDS: the
+// column of an active row is 1 + the active rows before it
+__device__ __forceinline__ void dir_rows(const int* ps, int G, const double* nv, double* s_nv) {
+  const unsigned a0 = (unsigned)ps[PS_BACT0], a1 = (unsigned)ps[PS_BACT1];
+  for (int g = threadIdx.x; g < G; g += blockDim.x) {
+    const unsigned below = g < 32 ? a0 & ((1u << g) - 1u) : a1 & ((1u << (g - 32)) - 1u);
+    const int col = 1 + __popc(below) + (g < 32 ? 0 : __popc(a0));
+    s_nv[g] = band_active(ps, g) ? nv[col] : 0.0;
+  }
+}
+
 // one row's bounds on the step: Lo <= s <= Up keeps it stationary; the keys
 // name the row and the piece it would move into (row * 16 + code)
-__device__ __forceinline__ void sweep_row(const PolishArgs& A, const int* ps, const SweepDir& D,
-                                          const double* mult, int i, int c, double gbi,
+__device__ __forceinline__ void sweep_row(const PolishArgs& A, const SweepDir& D,
+                                          const double* s_nv, const double* mult, int i, int c, double gbi,
                                           double wi, int grp, const RowData& r, float kap,
                                           bool phi, double& Lo, double& Up, int& loKey,
                                           int& upKey) {
@@ -1442,12 +1456,7 @@ __device__ __forceinline__ void sweep_row(const PolishArgs& A, const int* ps, co
   double nb = 0.0, lg = 0.0;
   if (G) {
     lg = rows_dot_g(A, i, grp, mult + 2);
-    int col = 1;
-    for (int g2 = 0; g2 < G; ++g2) {
-      if (!band_active(ps, g2)) continue;
-      nb += row_coef_g(A, i, grp, g2) * D.nv[col];
-      ++col;
-    }
+    nb = rows_dot_g(A, i, grp, s_nv);      // (one-hot rows: the row's own label only)
   }
   const double T = -(gbi - mult[0] + lg);
   const double al = D.n0 + nb;
@@ -1478,13 +1487,32 @@ __device__ __forceinline__ void sweep_row(const PolishArgs& A, const int* ps, co
   }
 }
 
+// what a step reads per constraint row, staged in LDS (one thread walks it:
+// from global memory each row was a chain of round trips)
+struct StepRows {
+  double nv[kMaxG];            // the direction's entry (0: inactive)
+  double gs[kMaxG];            // the row's value at the polished w
+  float lo[kMaxG], hi[kMaxG];  // its bounds
+};
+__device__ __forceinline__ void step_bounds(const PolishArgs& A, int a, const double* gsum,
+                                            StepRows& R) {
+  for (int g = threadIdx.x; g < A.G; g += blockDim.x) {
+    R.gs[g] = gsum[g];
+    R.lo[g] = A.blo[(size_t)a * A.G + g];
+    R.hi[g] = A.bhi[(size_t)a * A.G + g];
+  }
+}
+
 // the step along D given the rows' bounds [Lo, Up] (keys kLo, kUp): updates
 // mult; *block takes the row to release when one blocks the target
-__device__ void sweep_step(const PolishArgs& A, int a, const int* ps, const SweepDir& D,
+__device__ void sweep_step(const PolishArgs& A, const int* ps, const SweepDir& D, const StepRows& R,
                            double Lo, double Up, int kLo, int kUp, double thr, double turn0,
-                           float tauf, const double* s_gs, double* mult, int* block) {
+                           float tauf, double* mult, int* block) {
   const int G = A.G;
   const double ncap = D.ncap, lamc = D.lamc;
+  const unsigned act0 = (unsigned)ps[PS_BACT0], act1 = (unsigned)ps[PS_BACT1];
+  const unsigned up0 = (unsigned)ps[PS_BUP0], up1 = (unsigned)ps[PS_BUP1];
+  const bool cap_on = ps[PS_CAP];
   // targets along this direction, by priority: (1) an active constraint the
   // solve could not enforce (dependent row) and that is violated: push its
   // multiplier outward until a fixed row blocks, and release that row; (2)
@@ -1493,7 +1521,7 @@ __device__ void sweep_step(const PolishArgs& A, int a, const int* ps, const Swee
   double tgt = 0.0, best = 0.0, worst = 0.0;
   bool has_tgt = false;
   const double vtol = 0.1 * A.eps_prim;
-  if (ps[PS_CAP]) {              // lam_cap + s ncap >= 0
+  if (cap_on) {                  // lam_cap + s ncap >= 0
     if (ncap > 1e-12) { const double u = -lamc / ncap; if (u > Lo) { Lo = u; kLo = INT_MAX; } }
     else if (ncap < -1e-12) { const double u = -lamc / ncap; if (u < Up) { Up = u; kUp = INT_MAX; } }
     const double sl = (double)tauf - turn0;
@@ -1506,20 +1534,18 @@ __device__ void sweep_step(const PolishArgs& A, int a, const int* ps, const Swee
       }
     }
   }
-  int col = 1;
   for (int gg = 0; gg < G; ++gg) {
-    if (!band_active(ps, gg)) continue;
-    const double nbv = D.nv[col++];
+    if (!(((gg < 32 ? act0 : act1) >> (gg & 31)) & 1u)) continue;
+    const double nbv = R.nv[gg];
     const double cur = mult[2 + gg];
-    const bool up = band_upper(ps, gg);
+    const bool up = ((gg < 32 ? up0 : up1) >> (gg & 31)) & 1u;
     // upper band: lam >= 0 ; lower band: lam <= 0
     const double sgn_req = up ? 1.0 : -1.0;
     const double aa = sgn_req * nbv, bb = sgn_req * cur;   // bb + s aa >= 0
     if (aa > 1e-12) { const double u = -bb / aa; if (u > Lo) { Lo = u; kLo = INT_MAX; } }
     else if (aa < -1e-12) { const double u = -bb / aa; if (u < Up) { Up = u; kUp = INT_MAX; } }
     if (fabs(nbv) <= 1e-12) continue;
-    const double sl = up ? (double)A.bhi[(size_t)a * G + gg] - s_gs[gg]
-                         : s_gs[gg] - (double)A.blo[(size_t)a * G + gg];
+    const double sl = up ? (double)R.hi[gg] - R.gs[gg] : R.gs[gg] - (double)R.lo[gg];
     if (sl < -vtol && -sl > worst) {
       worst = -sl; tgt = (aa > 0.0) ? INFINITY : -INFINITY; has_tgt = true;
     } else if (worst == 0.0) {
@@ -1542,10 +1568,9 @@ __device__ void sweep_step(const PolishArgs& A, int a, const int* ps, const Swee
   if (!isfinite(st)) st = 0.0;
   // eta += st * v  ->  nu -= st v0, bands += st v_b, lam_cap += st v_cap
   mult[0] -= st * D.n0;
-  col = 1;
   for (int gg = 0; gg < G; ++gg)
-    if (band_active(ps, gg)) mult[2 + gg] += st * D.nv[col++];
-  if (ps[PS_CAP]) mult[1] += st * ncap;
+    if (((gg < 32 ? act0 : act1) >> (gg & 31)) & 1u) mult[2 + gg] += st * R.nv[gg];
+  if (cap_on) mult[1] += st * ncap;
 }
 
 // the check passes' per-row inputs of U rows (all loads issued together)
@@ -1573,10 +1598,36 @@ __device__ __forceinline__ void check_in(const PolishArgs& A, int a, int base, i
   row_data_n<U>(A, a, I.ii, lbf, ubf, I.rd);
 }
 
+// the row blocks' bounds of one direction: the extremes over the blocks and
+// the smallest keys of the blocks attaining them (every thread gets them;
+// s_sh: 3 doubles a wave, s_key: two ints)
+__device__ __forceinline__ void gather_bounds(const PolishArgs& A, int a, double* s_sh, int* s_key,
+                                              double& Lo, double& Up, int& kLo, int& kUp) {
+  const double* sp = A.spart + (size_t)a * A.n_sb * 4;
+  double l = -INFINITY, u = INFINITY;
+  for (int bb = threadIdx.x; bb < A.n_sb; bb += blockDim.x) {
+    l = fmax(l, sp[4 * bb]);
+    u = fmin(u, sp[4 * bb + 1]);
+  }
+  double sv[1] = {0.0}, mv[2] = {l, -u};
+  bred<1, 2>(sv, mv, s_sh);
+  Lo = mv[0];
+  Up = -mv[1];
+  if (threadIdx.x == 0) { s_key[0] = INT_MAX; s_key[1] = INT_MAX; }
+  __syncthreads();
+  for (int bb = threadIdx.x; bb < A.n_sb; bb += blockDim.x) {
+    if (isfinite(Lo) && sp[4 * bb] == Lo) atomicMin(&s_key[0], (int)sp[4 * bb + 2]);
+    if (isfinite(Up) && sp[4 * bb + 1] == Up) atomicMin(&s_key[1], (int)sp[4 * bb + 3]);
+  }
+  __syncthreads();
+  kLo = s_key[0];
+  kUp = s_key[1];
+}
+
 // per-block bounds of the one-direction sweep: [m][n_sb][4] = Lo, Up and
 // the smallest keys of the rows attaining them
 __global__ __launch_bounds__(kRT) void polish_sweep_kernel(PolishArgs A, int final_pass) {
-  __shared__ double mult[2 + kMaxG];
+  __shared__ double mult[2 + kMaxG], s_nv[kMaxG];
   __shared__ double s_sh[3 * kRW];
   __shared__ int s_key[2];
   const int G = A.G, tid = threadIdx.x;
@@ -1590,17 +1641,19 @@ __global__ __launch_bounds__(kRT) void polish_sweep_kernel(PolishArgs A, int fin
   const bool phi = (kap > 0.f) || isfinite(tauf) || (par[P_HASTAX] != 0.f);
   const double* gmult = A.mult + (size_t)a * (2 + G);
   for (int q = tid; q < 2 + G; q += kRT) mult[q] = gmult[q];
+  const double* nul = wk_of(A, a).nul;
+  dir_rows(ps, G, nul, s_nv);
   if (tid == 0) { s_key[0] = INT_MAX; s_key[1] = INT_MAX; }
   CheckIn<kRR> I;
   check_in(A, a, b * kRB, kRT, false, lbf, ubf, I);
   __syncthreads();
-  const SweepDir D = sweep_dir(ps, wk_of(A, a).nul, mult);
+  const SweepDir D = sweep_dir(ps, nul, mult);
   double Lo = -INFINITY, Up = INFINITY;
   int loKey = INT_MAX, upKey = INT_MAX;
 #pragma unroll
   for (int u = 0; u < kRR; ++u)
     if (I.ii[u] < A.n)
-      sweep_row(A, ps, D, mult, I.ii[u], I.cc[u], I.gb[u], I.w[u], I.grp[u], I.rd[u], kap, phi,
+      sweep_row(A, D, s_nv, mult, I.ii[u], I.cc[u], I.gb[u], I.w[u], I.grp[u], I.rd[u], kap, phi,
                 Lo, Up, loKey, upKey);
   double sv[1] = {0.0}, mv[2] = {Lo, -Up};
   bred<1, 2>(sv, mv, s_sh);
@@ -1624,9 +1677,10 @@ __global__ __launch_bounds__(kRT) void polish_sweep_kernel(PolishArgs A, int fin
 __global__ __launch_bounds__(kPTC) void polish_pre_kernel(PolishArgs A, int final_pass) {
   __shared__ double shd[kPW];
   __shared__ double s_red6[6 * kPW];
-  __shared__ double s_gs[kMaxG];
+  __shared__ StepRows R;
   __shared__ double mult[2 + kMaxG];
   __shared__ int s_block, s_key[2], s_bad;
+  double* const s_nv = R.nv;
   const int G = A.G, n = A.n;
   const int slot = blockIdx.x;
   if (slot >= *A.m_act) return;
@@ -1642,7 +1696,7 @@ __global__ __launch_bounds__(kPTC) void polish_pre_kernel(PolishArgs A, int fina
   if (tid == 0) { s_bad = 0; s_block = -1; }
   __syncthreads();                        // flags above are initialised
   const Wk wkc = wk_of(A, a);
-  for (int g = tid; g < G; g += kPTC) s_gs[g] = wkc.gsum[g];
+  step_bounds(A, a, wkc.gsum, R);
   double gmax = 0.0, mumax = 0.0;
   int bad = 0;
   for (int rb = tid; rb < A.n_rb; rb += kPTC) {
@@ -1654,7 +1708,7 @@ __global__ __launch_bounds__(kPTC) void polish_pre_kernel(PolishArgs A, int fina
   if (bad) atomicOr(&s_bad, 1);
   {
     double sv[1] = {0.0}, mv[2] = {gmax, mumax};
-    bred<1, 2>(sv, mv, s_red6);           // (also publishes s_gs)
+    bred<1, 2>(sv, mv, s_red6);           // (also publishes R)
     gmax = mv[0]; mumax = mv[1];
   }
   const double turn0 = wkc.misc[3];       // turnover of w (polish_solve)
@@ -1663,31 +1717,24 @@ __global__ __launch_bounds__(kPTC) void polish_pre_kernel(PolishArgs A, int fina
   const int ncol = G + 3;
   const double thr = 0.01 * A.eps_comp * scale;
   if (nd == 1) {
+    double Lo, Up;
+    int kLo, kUp;
+    dir_rows(ps, G, wkc.nul, s_nv);
+    gather_bounds(A, a, s_red6, s_key, Lo, Up, kLo, kUp);
     if (tid == 0) {
-      // the blocks' bounds in block order: the extreme and the smallest key
-      // among the blocks attaining it
-      double Lo = -INFINITY, Up = INFINITY;
-      int kLo = INT_MAX, kUp = INT_MAX;
-      for (int bb = 0; bb < A.n_sb; ++bb) {
-        const double* sp = A.spart + ((size_t)a * A.n_sb + bb) * 4;
-        const double l = sp[0], u = sp[1];
-        const int kl = (int)sp[2], ku = (int)sp[3];
-        if (l > Lo) { Lo = l; kLo = kl; } else if (l == Lo) kLo = min(kLo, kl);
-        if (u < Up) { Up = u; kUp = ku; } else if (u == Up) kUp = min(kUp, ku);
-      }
-      if (!isfinite(Lo)) kLo = INT_MAX;
-      if (!isfinite(Up)) kUp = INT_MAX;
       const SweepDir D = sweep_dir(ps, wkc.nul, mult);
-      sweep_step(A, a, ps, D, Lo, Up, kLo, kUp, thr, turn0, tauf, s_gs, mult, &s_block);
+      sweep_step(A, ps, D, R, Lo, Up, kLo, kUp, thr, turn0, tauf, mult, &s_block);
     }
     __syncthreads();
-  } else if (nd > 1) {
+  } else if (nd > 1 && A.n_sb < kSplitDir) {
     // one sweep over the directions (a second one, for directions that
     // interact, cost a full pass per direction and certified no more
     // accounts: the next refinement round revisits them anyway)
     for (int sweep = 0; sweep < 1; ++sweep) {
       for (int q = 0; q < nd; ++q) {
         const SweepDir D = sweep_dir(ps, wkc.nul + q * ncol, mult);
+        dir_rows(ps, G, wkc.nul + q * ncol, s_nv);
+        __syncthreads();
         double Lo = -INFINITY, Up = INFINITY;
         int loKey = INT_MAX, upKey = INT_MAX;
         for (int base = 0; base < n; base += kPU * kPTC) {
@@ -1696,7 +1743,7 @@ __global__ __launch_bounds__(kPTC) void polish_pre_kernel(PolishArgs A, int fina
 #pragma unroll
           for (int u = 0; u < kPU; ++u)
             if (I.ii[u] < n)
-              sweep_row(A, ps, D, mult, I.ii[u], I.cc[u], I.gb[u], I.w[u], I.grp[u], I.rd[u],
+              sweep_row(A, D, s_nv, mult, I.ii[u], I.cc[u], I.gb[u], I.w[u], I.grp[u], I.rd[u],
                         kap, phi, Lo, Up, loKey, upKey);
         }
         double sv[1] = {0.0}, mv[2] = {Lo, -Up};
@@ -1708,8 +1755,7 @@ __global__ __launch_bounds__(kPTC) void polish_pre_kernel(PolishArgs A, int fina
         if (Up == Ub && isfinite(Ub)) atomicMin(&s_key[1], upKey);
         __syncthreads();
         if (tid == 0)
-          sweep_step(A, a, ps, D, Lb, Ub, s_key[0], s_key[1], thr, turn0, tauf, s_gs, mult,
-                     &s_block);
+          sweep_step(A, ps, D, R, Lb, Ub, s_key[0], s_key[1], thr, turn0, tauf, mult, &s_block);
         __syncthreads();
       }
     }
@@ -1722,6 +1768,78 @@ __global__ __launch_bounds__(kPTC) void polish_pre_kernel(PolishArgs A, int fina
     misc[1] = turn0;
     misc[2] = s_bad ? 1.0 : 0.0;
   }
+}
+
+// One of several null directions, for accounts of many row blocks: the
+// blocks' bounds as in polish_sweep, and the block that finishes last takes
+// the step (the directions interact: the next one, the next launch, starts
+// from the stepped multipliers).  One workgroup sweeping all rows was 7.2 ms
+// a round at n = 384,800 (8 rows a thread and direction at n = 16,384 break
+// even with the eight launches); spread over 752 blocks it is bound by the
+// launches.
+__global__ __launch_bounds__(kRT) void polish_dir_kernel(PolishArgs A, int final_pass, int q) {
+  __shared__ double mult[2 + kMaxG];
+  __shared__ StepRows R;
+  __shared__ double s_sh[3 * kRW];
+  __shared__ int s_key[2], s_last, s_block;
+  double* const s_nv = R.nv;
+  const int G = A.G, tid = threadIdx.x;
+  const int b = blockIdx.x, slot = blockIdx.y;
+  if (slot >= *A.m_act) return;
+  const int a = A.act[slot];
+  int* ps = A.pstate + (size_t)a * kPStateStride;
+  const int nd = ps[PS_ND];
+  if (ps[PS_DONE] || (ps[PS_STALL] && !final_pass) || nd <= 1 || q >= nd) return;
+  const float* par = A.par + (size_t)a * kNPar;
+  const float lbf = par[P_LB], ubf = par[P_UB], kap = par[P_KAPPA], tauf = par[P_TAU];
+  const bool phi = (kap > 0.f) || isfinite(tauf) || (par[P_HASTAX] != 0.f);
+  double* gmult = A.mult + (size_t)a * (2 + G);
+  const Wk wk = wk_of(A, a);
+  for (int e = tid; e < 2 + G; e += kRT) mult[e] = gmult[e];
+  dir_rows(ps, G, wk.nul + q * (G + 3), s_nv);
+  if (tid == 0) { s_key[0] = INT_MAX; s_key[1] = INT_MAX; }
+  CheckIn<kRR> I;
+  check_in(A, a, b * kRB, kRT, false, lbf, ubf, I);
+  __syncthreads();
+  const SweepDir D = sweep_dir(ps, wk.nul + q * (G + 3), mult);
+  double Lo = -INFINITY, Up = INFINITY;
+  int loKey = INT_MAX, upKey = INT_MAX;
+#pragma unroll
+  for (int u = 0; u < kRR; ++u)
+    if (I.ii[u] < A.n)
+      sweep_row(A, D, s_nv, mult, I.ii[u], I.cc[u], I.gb[u], I.w[u], I.grp[u], I.rd[u], kap, phi,
+                Lo, Up, loKey, upKey);
+  double sv[1] = {0.0}, mv[2] = {Lo, -Up};
+  bred<1, 2>(sv, mv, s_sh);
+  const double Lb = mv[0], Ub = -mv[1];
+  if (Lo == Lb && isfinite(Lb)) atomicMin(&s_key[0], loKey);
+  if (Up == Ub && isfinite(Ub)) atomicMin(&s_key[1], upKey);
+  __syncthreads();
+  if (tid == 0) {
+    double* sp = A.spart + ((size_t)a * A.n_sb + b) * 4;
+    sp[0] = Lb;
+    sp[1] = Ub;
+    sp[2] = s_key[0];
+    sp[3] = s_key[1];
+    __threadfence();                       // the bounds before the count, device-wide
+    s_last = atomicAdd(&ps[PS_TICK], 1) == A.n_sb - 1;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();                         // every block's bounds are visible
+  step_bounds(A, a, wk.gsum, R);
+  double Lg, Ug;
+  int kLo, kUp;
+  gather_bounds(A, a, s_sh, s_key, Lg, Ug, kLo, kUp);
+  if (tid == 0) {
+    const double thr = 0.01 * A.eps_comp * wk.misc[0];
+    s_block = ps[PS_BLOCK];
+    sweep_step(A, ps, D, R, Lg, Ug, kLo, kUp, thr, wk.misc[1], tauf, mult, &s_block);
+    ps[PS_BLOCK] = s_block;
+    ps[PS_TICK] = 0;
+  }
+  __syncthreads();
+  for (int e = tid; e < 2 + G; e += kRT) gmult[e] = mult[e];
 }
 
 // per-block diagnostics of the pattern's w and the refinement proposals
@@ -1819,6 +1937,9 @@ __global__ __launch_bounds__(kRT) void polish_check_rows_kernel(PolishArgs A, in
 __global__ __launch_bounds__(64) void polish_decide_kernel(PolishArgs A, fqp_result R,
                                                            int final_pass) {
   __shared__ int s_done;
+  // the constraint rows' values, bounds and multipliers (one thread walks them)
+  __shared__ double s_gs[kMaxG], s_ml[2 + kMaxG];
+  __shared__ float s_lo[kMaxG], s_hi[kMaxG];
   const int G = A.G, tid = threadIdx.x;
   const int slot = blockIdx.x;
   if (slot >= *A.m_act) return;
@@ -1843,10 +1964,17 @@ __global__ __launch_bounds__(64) void polish_decide_kernel(PolishArgs A, fqp_res
   }
   const float* par = A.par + (size_t)a * kNPar;
   const float tauf = par[P_TAU];
-  const double* mult = A.mult + (size_t)a * (2 + G);
+  const double* gmult = A.mult + (size_t)a * (2 + G);
   const Wk wkc = wk_of(A, a);
-  const double* s_gs = wkc.gsum;
+  for (int g = tid; g < G; g += 64) {
+    s_gs[g] = wkc.gsum[g];
+    s_lo[g] = A.blo[(size_t)a * G + g];
+    s_hi[g] = A.bhi[(size_t)a * G + g];
+  }
+  for (int g = tid; g < 2 + G; g += 64) s_ml[g] = gmult[g];
+  const double* mult = s_ml;
   int8_t* code = A.code_next + (size_t)a * A.n;
+  __syncthreads();
   if (tid == 0) {
     const double scale = wkc.misc[0];
     const bool s_bad = wkc.misc[2] != 0.0 || bad != 0.0;
@@ -1856,7 +1984,7 @@ __global__ __launch_bounds__(64) void polish_decide_kernel(PolishArgs A, fqp_res
     // f(w) - f* <= gap)
     double rexp = 0.0, comp = 0.0, gap = 0.0;
     for (int g = 0; g < G; ++g) {
-      const double lo = A.blo[(size_t)a * G + g], hi = A.bhi[(size_t)a * G + g];
+      const double lo = s_lo[g], hi = s_hi[g];
       rexp = fmax(rexp, fmax(lo - s_gs[g], s_gs[g] - hi));
       const double lg = mult[2 + g];
       if (lg != 0.0) {              // (a one-sided row's other slack is infinite)
@@ -1915,7 +2043,7 @@ __global__ __launch_bounds__(64) void polish_decide_kernel(PolishArgs A, fqp_res
         ++nchg;
       }
       for (int g = 0; g < G; ++g) {
-        const double lo = A.blo[(size_t)a * G + g], hi = A.bhi[(size_t)a * G + g];
+        const double lo = s_lo[g], hi = s_hi[g];
         const bool act = band_active(ps, g), up = band_upper(ps, g);
         const double lg = mult[2 + g];
         if (act && ((up && lg < 0.0) || (!up && lg > 0.0))) { set_band(ps, g, false, false); ++nchg; }
@@ -1980,6 +2108,12 @@ hipError_t launch_polish_check_r(const PolishArgs& A, const fqp_result& R, int f
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(polish_pre_kernel, dim3(A.m_total), dim3(kPTC), 0, st, A, final_pass);
   if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (A.n_sb >= kSplitDir)
+    for (int q = 0; q < kMaxNull; ++q) {
+      hipLaunchKernelGGL(polish_dir_kernel, dim3(A.n_sb, A.m_total), dim3(kRT), 0, st, A,
+                         final_pass, q);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
   hipLaunchKernelGGL(polish_check_rows_kernel, dim3(A.n_sb, A.m_total), dim3(kRT), 0, st, A,
                      final_pass);
   if ((e = hipGetLastError()) != hipSuccess) return e;
