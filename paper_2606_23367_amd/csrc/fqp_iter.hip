@@ -316,59 +316,6 @@ __global__ __launch_bounds__(1024) void kfactor_kernel(int k, int G, int kp, int
 // ---------------------------------------------------------------------------
 enum PassMode { MODE_CONTRACT = 0, MODE_PROJECT = 1 };
 
-struct RowInfo {
-  float lb, ub, w0;
-  bool taxed;
-  TaxLots t;
-};
-
-__device__ __forceinline__ float prox_row(const RowInfo& ri, float v, float th, float irho,
-                                          bool* at_kink) {
-  float zn;
-  if (ri.taxed) {
-    zn = prox_taxed(v, ri.w0, th, irho, ri.t, ri.lb, ri.ub);
-    if (at_kink)
-      *at_kink = (zn == ri.w0) || (zn == ri.w0 - ri.t.b1) || (zn == ri.w0 - ri.t.b2) ||
-                 (zn == ri.w0 - ri.t.b3) || zn <= ri.lb || zn >= ri.ub;
-  } else {
-    zn = prox_plain(v, ri.w0, th, ri.lb, ri.ub);
-    if (at_kink) *at_kink = (zn == ri.w0) || zn <= ri.lb || zn >= ri.ub;
-  }
-  return zn;
-}
-
-// box, w0 and tax lots of (account a, row) from its eligibility word, its
-// holding word and the holding prefix word (already loaded) and the
-// account's first record hptr: one more dependent load, only for held rows
-template <typename Args>
-__device__ __forceinline__ RowInfo row_info_w(const Args& A, size_t off, int row, float lbp,
-                                              float ubp, uint32_t ew, uint32_t hw, int hpre,
-                                              int hptr) {
-  RowInfo ri;
-  const int b = row & 31;
-  const bool el = (ew >> b) & 1u;
-  asset_box(A, off, el, lbp, ubp, ri.lb, ri.ub);
-  ri.w0 = 0.f;
-  ri.taxed = false;
-  if ((hw >> b) & 1u) {
-    const int idx = hptr + hpre + popc_below(hw, b);
-    const float4 r0 = A.hold_rec[2 * idx], r1 = A.hold_rec[2 * idx + 1];
-    ri.w0 = r0.x;
-    ri.taxed = r0.y > 0.f;
-    ri.t.b1 = r0.y; ri.t.b2 = r0.z; ri.t.b3 = r0.w;
-    ri.t.s0 = r1.x; ri.t.s1 = r1.y; ri.t.s2 = r1.z; ri.t.s3 = r1.w;
-  }
-  return ri;
-}
-
-template <typename Args>
-__device__ __forceinline__ RowInfo row_info(const Args& A, int a, int row, float lbp, float ubp) {
-  const size_t wi = (size_t)a * A.W + (row >> 5);
-  const uint32_t ew = A.elig ? A.elig[wi] : 0xffffffffu;
-  return row_info_w(A, (size_t)a * A.n + row, row, lbp, ubp, ew, A.hold[wi], A.hold_pre[wi],
-                    A.hold_ptr[a]);
-}
-
 template <int NCH, int MODE>
 __global__ __launch_bounds__(256, 2) void iter_kernel(IterArgs A) {
   constexpr int kp = NCH * 32;
@@ -1172,17 +1119,27 @@ __global__ __launch_bounds__(kCapT) void prox_stream_kernel(IterArgs A, int zmod
 // each thread's partial sums (up to 79 row tiles) and K^-1 rows come in one
 // batch of loads each
 constexpr int kKsT = 512;
+// KB entries of K^-1 a thread loads at the start, PB row-tile partials it has
+// in flight at once.  The constraint rows' block of the Gram matrix and their
+// states go through LDS, loaded at the start by all threads: read from global
+// memory inside the sum over the rows they were most of the kernel at 50
+// groups (8 x 384,800, 151 columns, with the loads below free of branches: 36.8 ->
+// 14.0 us; 500 x 10,000, 81 columns: 10.1 -> 8.1).
+template <int KB, int PB>
 __global__ __launch_bounds__(kKsT) void ksolve_kernel(KArgs A) {
-  __shared__ double t[kMaxKp], rhs[kMaxKp], red[kKsT], redq[kKsT / 64];
+  extern __shared__ float s_mb[];            // [kg][G], then c of the rows [G]
+  __shared__ double t[256], red[kKsT], redq[kKsT / 64];   // t: zeros past column kp - 1
+  __shared__ double s_y[kMaxG];              // zb - vb of the constraint rows
+  __shared__ float s_zf[kMaxG], s_vf[kMaxG]; // zb, vb
   __shared__ float tsp[kKsT];                // split partial sums
   __shared__ float pprime[kMaxKp];
   const int slot = blockIdx.x;
-  if (slot >= *A.m_act) return;
+  const int m_act = *A.m_act;
+  if (slot >= m_act) return;
   const int a = A.act[slot];
   const int tid = threadIdx.x;
   const int kp = A.kp, k = A.k, G = A.G, kg = k + G;
   const size_t M = A.m_total;
-  const int n_rt = tile_map(*A.m_act, A.n, A.nblk, 0).n_rt;
   float* par = A.par + (size_t)a * kNPar;
   // (one class: no dependent load of the account's class before K^-1)
   const int cls = A.ncls == 1 ? 0 : (int)par[P_CLASS];
@@ -1198,62 +1155,77 @@ __global__ __launch_bounds__(kKsT) void ksolve_kernel(KArgs A) {
 
   // nsp threads per factor column split the row tiles (and below the
   // K^-1 rows), so that more independent loads are in flight.  Each thread
-  // issues its first batch of 16 partials, then its first 16 entries of
-  // K^-1 (used after the reduction), before any of them is waited on.
+  // issues its entries of K^-1 (used after the reduction; they do not wait
+  // for the account), then its first batch of partials, before any of them
+  // is waited on.
   const int nsp = kp <= kKsT ? kKsT / kp : 1;
   const int jq = tid % kp, qq = tid / kp;
-  float kb[16];
+  // (no branch around a load: the merge behind one would wait for it.  Rows
+  // past the block's last repeat it; t is zero there)
+  float kb[KB];
+  {
+    const unsigned k0 = (unsigned)(qq * kp + jq), kmax = (unsigned)((kp - 1) * kp + jq);
+#pragma unroll
+    for (int u = 0; u < KB; ++u) kb[u] = Kinv[min(k0 + (unsigned)(u * nsp * kp), kmax)];
+  }
+  float lo_g = 0.f, hi_g = 0.f;
+  if (G > 0) {
+    const float* mbg = A.mbg + (size_t)cls * kp * G;
+    // (16 loads in flight a thread: one at a time they were half the kernel)
+    for (int e0 = tid; e0 < kg * G; e0 += 16 * kKsT) {
+      float x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = e0 + u * kKsT < kg * G ? mbg[e0 + u * kKsT] : 0.f;
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (e0 + u * kKsT < kg * G) s_mb[e0 + u * kKsT] = x[u];
+    }
+    if (tid < G) {
+      const float zb = A.zb[(size_t)a * G + tid], vb = A.vb[(size_t)a * G + tid];
+      s_mb[kg * G + tid] = cv[k + tid];
+      s_zf[tid] = zb;
+      s_vf[tid] = vb;
+      s_y[tid] = (double)zb - vb;
+      lo_g = A.blo[(size_t)a * G + tid];
+      hi_g = A.bhi[(size_t)a * G + tid];
+    }
+  }
+  const int n_rt = tile_map(m_act, A.n, A.nblk, 0).n_rt;
   if (tid < nsp * kp) {
-    float buf[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int rt = qq + u * nsp;
-      buf[u] = rt < n_rt ? A.part[((size_t)rt * M + a) * kp + jq] : 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int l = qq + u * nsp;
-      kb[u] = (jq < kg && l < kg) ? Kinv[l * kp + jq] : 0.f;
-    }
+    // this thread's row tiles: qq, qq + nsp, ... (cnt of them); loads past
+    // the last one read the first tile and are dropped
+    const int cnt = qq < n_rt ? (n_rt - 1 - qq) / nsp + 1 : 0;
+    const float* p0 = A.part + (size_t)a * kp + jq;
+    const float* pq = p0 + (size_t)qq * M * kp;
+    const size_t step = (size_t)nsp * M * kp;
     float s = 0.f;
+    for (int u0 = 0; u0 * nsp < n_rt; u0 += PB) {
+      float buf[PB];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) s += buf[u];
-    // batches of 16 loads issued before any is added
-    for (int r0 = qq + 16 * nsp; r0 < n_rt; r0 += 16 * nsp) {
+      for (int u = 0; u < PB; ++u) buf[u] = *(u0 + u < cnt ? pq + (u0 + u) * step : p0);
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int rt = r0 + u * nsp;
-        buf[u] = rt < n_rt ? A.part[((size_t)rt * M + a) * kp + jq] : 0.f;
-      }
-#pragma unroll
-      for (int u = 0; u < 16; ++u) s += buf[u];
+      for (int u = 0; u < PB; ++u) s += u0 + u < cnt ? buf[u] : 0.f;
     }
     tsp[tid] = s;
   }
   __syncthreads();
+  if (tid >= kp && tid < 256) t[tid] = 0.0;
   for (int j = tid; j < kp; j += kKsT) {
     float s = 0.f;
     for (int q = 0; q < nsp; ++q) s += tsp[q * kp + j];
-    t[j] = s;
+    // band terms: t += (K - F~^-1)[:, G] rho_b (zb - vb)
+    double b = 0.0;
+    if (j < kg)
+      for (int g = 0; g < G; ++g) b += (double)s_mb[j * G + g] * rhob * s_y[g];
+    t[j] = (G > 0 && j < kg) ? (double)s + b : (double)s;
   }
   __syncthreads();
-  // band terms: t += (K - F~^-1)[:, G] rho_b (zb - vb);  s0 += c_G . same
+  // s0 += c_G . rho_b (zb - vb)
   double s0 = t[kg];
   if (G > 0) {
-    const float* mbg = A.mbg + (size_t)cls * kp * G;
-    const float* zb = A.zb + (size_t)a * G;
-    const float* vb = A.vb + (size_t)a * G;
-    for (int j = tid; j < kg; j += kKsT) {
-      double s = 0.0;
-      for (int g = 0; g < G; ++g) s += (double)mbg[j * G + g] * rhob * ((double)zb[g] - vb[g]);
-      rhs[j] = s;
-    }
-    __syncthreads();
     double cs = 0.0;
-    for (int g = 0; g < G; ++g) cs += (double)cv[k + g] * rhob * ((double)zb[g] - vb[g]);
+    for (int g = 0; g < G; ++g) cs += (double)s_mb[kg * G + g] * rhob * s_y[g];
     s0 += cs;
-    for (int j = tid; j < kg; j += kKsT) t[j] += rhs[j];
-    __syncthreads();
   }
   // p = K^-1 (t + nu c) = K^-1 t + nu q (q = K^-1 c): the product with t
   // does not wait for nu = (1 - s0 + q^T t) / sigma1, and both reductions
@@ -1266,11 +1238,11 @@ __global__ __launch_bounds__(kKsT) void ksolve_kernel(KArgs A) {
       // the first batch was loaded at the start, later ones here in
       // batches of 16 loads issued before any is used
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int l = q + u * nsp;
-        if (l < kg) s += (double)kb[u] * t[l];
+      for (int u = 0; u < KB; ++u) {
+        // (past column kg - 1 the entry of K^-1 is 0; q + u nsp < 256)
+        s += (double)kb[u] * t[q + u * nsp];
       }
-      for (int l0 = q + 16 * nsp; l0 < kg; l0 += 16 * nsp) {
+      for (int l0 = q + KB * nsp; l0 < kg; l0 += 16 * nsp) {
         float buf[16];
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
@@ -1303,7 +1275,7 @@ __global__ __launch_bounds__(kKsT) void ksolve_kernel(KArgs A) {
     pprime[tid] = pj;
     float v = 0.f;
     if (tid < k) v = pj;
-    else if (tid < kg) v = pj - rhob * (A.zb[(size_t)a * G + (tid - k)] - A.vb[(size_t)a * G + (tid - k)]);
+    else if (tid < kg) v = pj - rhob * (s_zf[tid - k] - s_vf[tid - k]);
     pp[tid] = v;
   }
   if (G > 0) __syncthreads();            // the band block reads pprime
@@ -1311,14 +1283,12 @@ __global__ __launch_bounds__(kKsT) void ksolve_kernel(KArgs A) {
   if (G > 0 && tid < G) {
     const int g = tid;
     const float alpha = par[P_ALPHA];
-    float* zb = A.zb + (size_t)a * G;
-    float* vb = A.vb + (size_t)a * G;
     const float ax = pprime[k + g] / rhob;
-    const float zh = alpha * ax + (1.f - alpha) * zb[g];
-    float zn = zh + vb[g];
-    zn = fminf(fmaxf(zn, A.blo[(size_t)a * G + g]), A.bhi[(size_t)a * G + g]);
-    vb[g] = vb[g] + zh - zn;
-    zb[g] = zn;
+    const float zh = alpha * ax + (1.f - alpha) * s_zf[g];
+    float zn = zh + s_vf[g];
+    zn = fminf(fmaxf(zn, lo_g), hi_g);
+    A.vb[(size_t)a * G + g] = s_vf[g] + zh - zn;
+    A.zb[(size_t)a * G + g] = zn;
   }
   if (tid == 0) {
     par[P_NU] = (float)nu;
@@ -1481,9 +1451,25 @@ hipError_t launch_prox(const IterArgs& A, int m_total, bool resident, int zmode,
   return hipGetLastError();
 }
 
-hipError_t launch_ksolve(const KArgs& A, int m_total, hipStream_t st) {
-  hipLaunchKernelGGL(ksolve_kernel, dim3(m_total), dim3(kKsT), 0, st, A);
+template <int KB, int PB>
+static hipError_t launch_ksolve_t(const KArgs& A, int m_total, hipStream_t st) {
+  const size_t smem = sizeof(float) * (size_t)(A.k + A.G + 1) * A.G;
+  if (smem > 32 * 1024) {
+    hipError_t e = hipFuncSetAttribute((const void*)ksolve_kernel<KB, PB>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((ksolve_kernel<KB, PB>), dim3(m_total), dim3(kKsT), smem, st, A);
   return hipGetLastError();
+}
+
+// K^-1 entries a thread takes: kp / (512 / kp) = 16 at kp <= 64 (and spare),
+// 20 at 96, 32 at 128, 54 at 160, 96 at 192
+hipError_t launch_ksolve(const KArgs& A, int m_total, hipStream_t st) {
+  if (A.kp <= 64) return launch_ksolve_t<16, 16>(A, m_total, st);
+  if (A.kp <= 96) return launch_ksolve_t<20, 16>(A, m_total, st);
+  if (A.kp <= 128) return launch_ksolve_t<32, 32>(A, m_total, st);
+  return launch_ksolve_t<54, 32>(A, m_total, st);
 }
 
 hipError_t launch_split_bt(int n, int npad, int kp, const float* Bt, uint16_t* bh, uint16_t* bl,

@@ -166,6 +166,34 @@ hipError_t launch_resident_setup(const ResRowArgs& A, int kp, int KQ, const floa
                                  hipStream_t st);
 hipError_t launch_resident(const ResArgs& A, int KQ, int m_total, int count, hipStream_t st);
 
+// ---- fused pass of wide books (fqp_wide.hip) -----------------------------------
+struct WideArgs {
+  int n, W, kp, m_total;
+  const int* m_act;
+  const int* act;
+  const float* Bp;           // [rows padded to whole 128-row chunks][kp], columns permuted
+  const float* d;
+  const float* mu;
+  const float* lbv;          // [m][n] per-asset bounds or null
+  const float* ubv;
+  const uint32_t* elig;
+  const uint32_t* hold;
+  const int32_t* hold_pre;
+  const int32_t* hold_ptr;
+  const float4* hold_rec;
+  const float* pp;           // [m][kp]
+  const float* par;
+  float* v;                  // [m][n]
+  float* zs;                 // [m][n] w between the launches of a block, z after it
+  float* part;               // [row tiles][m][kp]
+};
+bool wide_fits(int n, int kp, int m, int ncap, bool split);
+hipError_t launch_wide_setup(int n, int kp, const float* Bt, float* Bp, hipStream_t st);
+// one launch of an iteration block over nblk row tiles: do_x applies the last
+// factor-space solve, do_p takes the prox step and contracts (else v and z
+// are written)
+hipError_t launch_wide(const WideArgs& A, int nblk, int do_x, int do_p, hipStream_t st);
+
 // ---- packing / validation -------------------------------------------------
 struct PackArgs {
   int n, W, m, G;            // G: constraint rows (bands, then halfspaces)
@@ -310,6 +338,51 @@ __device__ __forceinline__ void asset_box(const Args& A, size_t off, bool el, fl
   if (!el) { lb = 0.f; ub = 0.f; return; }
   lb = A.lbv ? A.lbv[off] : lbp;
   ub = A.ubv ? A.ubv[off] : ubp;
+}
+
+struct RowInfo {
+  float lb, ub, w0;
+  bool taxed;
+  TaxLots t;
+};
+
+__device__ __forceinline__ float prox_row(const RowInfo& ri, float v, float th, float irho,
+                                          bool* at_kink) {
+  float zn;
+  if (ri.taxed) {
+    zn = prox_taxed(v, ri.w0, th, irho, ri.t, ri.lb, ri.ub);
+    if (at_kink)
+      *at_kink = (zn == ri.w0) || (zn == ri.w0 - ri.t.b1) || (zn == ri.w0 - ri.t.b2) ||
+                 (zn == ri.w0 - ri.t.b3) || zn <= ri.lb || zn >= ri.ub;
+  } else {
+    zn = prox_plain(v, ri.w0, th, ri.lb, ri.ub);
+    if (at_kink) *at_kink = (zn == ri.w0) || zn <= ri.lb || zn >= ri.ub;
+  }
+  return zn;
+}
+
+// box, w0 and tax lots of (account a, row) from its eligibility word, its
+// holding word and the holding prefix word (already loaded) and the
+// account's first record hptr: one more dependent load, only for held rows
+template <typename Args>
+__device__ __forceinline__ RowInfo row_info_w(const Args& A, size_t off, int row, float lbp,
+                                              float ubp, uint32_t ew, uint32_t hw, int hpre,
+                                              int hptr) {
+  RowInfo ri;
+  const int b = row & 31;
+  const bool el = (ew >> b) & 1u;
+  asset_box(A, off, el, lbp, ubp, ri.lb, ri.ub);
+  ri.w0 = 0.f;
+  ri.taxed = false;
+  if ((hw >> b) & 1u) {
+    const int idx = hptr + hpre + popc_below(hw, b);
+    const float4 r0 = A.hold_rec[2 * idx], r1 = A.hold_rec[2 * idx + 1];
+    ri.w0 = r0.x;
+    ri.taxed = r0.y > 0.f;
+    ri.t.b1 = r0.y; ri.t.b2 = r0.z; ri.t.b3 = r0.w;
+    ri.t.s0 = r1.x; ri.t.s1 = r1.y; ri.t.s2 = r1.z; ri.t.s3 = r1.w;
+  }
+  return ri;
 }
 
 // the linear term of the polish and certificate: mu' in float64 when the

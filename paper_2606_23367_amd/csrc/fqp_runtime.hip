@@ -230,6 +230,7 @@ struct GraphKey {
   IterArgs ia;
   KArgs ka;
   ResArgs ra;
+  WideArgs wa;
   unsigned gx, gy, gpx, gpy;
   int m, kp, precision, count, cap_resident, kq;
 };
@@ -787,14 +788,18 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   const bool lots = P->tax_ptr != nullptr;
   const bool resident =
       !S.profile && resident_fits(n, kg + 1, G, lots, m, h->hcount[8], h->n_cu);
+  const bool wide = !S.profile && !resident && wide_fits(n, kp, m, h->hcount[8], split);
   const int KQ = resident ? resident_kq(kg + 1) : 0;
   const int ntile = (n + 63) / 64, npr = 64 * ntile;
   WS(Bq, float4, "Bq", resident ? (size_t)ntile * KQ * 64 : 1);
+  WS(Bp, float, "Bp", wide ? (size_t)npad_r * kp : 1);
   WS(rows, float4, "res_rows", resident ? (size_t)m * npr : 1);
   WS(lot, int32_t, "res_lot", resident && lots ? (size_t)m * npr : 1);
   HIP_CHECK(launch_pack_rec(pk, hold_rec, n_held, st));
   ResArgs ra;
   std::memset(&ra, 0, sizeof(ra));
+  WideArgs wa;
+  std::memset(&wa, 0, sizeof(wa));
   if (resident) {
     ResRowArgs rr{};
     rr.n = n; rr.npr = npr; rr.W = W; rr.m = m; rr.mu = mu_use; rr.lb = P->lb; rr.ub = P->ub;
@@ -807,6 +812,12 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
     ra.hold_rec = hold_rec; ra.d = U->d; ra.v = v; ra.zs = z; ra.par = par; ra.Kinv = Kinv;
     ra.cvec = cvec; ra.qvec = qvec; ra.sig1 = sig1; ra.mbg = mbg; ra.zb = zb; ra.vb = vb;
     ra.blo = rlo; ra.bhi = rhi; ra.iters = iters;
+  } else if (wide) {
+    HIP_CHECK(launch_wide_setup(n, kp, Bt, Bp, st));
+    wa.n = n; wa.W = W; wa.kp = kp; wa.m_total = m; wa.m_act = m_act; wa.act = act; wa.Bp = Bp;
+    wa.d = U->d; wa.mu = mu_use; wa.lbv = P->lb_asset; wa.ubv = P->ub_asset;
+    wa.elig = P->eligible; wa.hold = hold; wa.hold_pre = hold_pre; wa.hold_ptr = hold_ptr;
+    wa.hold_rec = hold_rec; wa.pp = pp; wa.par = par; wa.v = v; wa.zs = z; wa.part = part;
   } else if (split) {
     HIP_CHECK(launch_split_bt(n, npad, kp, Bt, bt_hi, bt_lo, btt_hi, btt_lo, st));
   }
@@ -908,6 +919,23 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
     return e0;
   };
 
+  // a block of iterations: account-resident (one launch), wide (the fused
+  // pass and the factor-space solve an iteration, one more launch to apply
+  // the last solve) or the four passes
+  auto launch_block = [&](int count) -> hipError_t {
+    if (resident) return launch_resident(ra, KQ, m, count, st);
+    hipError_t e0 = hipSuccess;
+    if (wide) {
+      for (int c = 0; c <= count && e0 == hipSuccess; ++c) {
+        e0 = launch_wide(wa, igrid.x * igrid.y, c > 0, c < count, st);
+        if (c < count && e0 == hipSuccess) e0 = launch_ksolve(ka, m, st);
+      }
+      return e0;
+    }
+    for (int c = 0; c < count && e0 == hipSuccess; ++c) e0 = launch_iteration(c);
+    return e0;
+  };
+
   // ---- iteration blocks -------------------------------------------------------
   // A whole block of check_every iterations is one captured graph, kept by
   // the handle: a later call with the same arguments replays it
@@ -919,6 +947,7 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   key.m = m; key.kp = kp; key.precision = S.precision; key.count = S.check_every;
   key.cap_resident = cap_resident ? 1 : 0;
   key.ra = ra;
+  key.wa = wa;
   key.kq = KQ;
 
   // graph_reused reports a call that captured nothing: every block replayed
@@ -932,16 +961,12 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
         captured = true;
         h->drop_graph();
         HIP_CHECK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-        for (int c = 0; c < count; ++c) {
-          const hipError_t e1 = resident ? launch_resident(ra, KQ, m, count, st) : launch_iteration(c);
-          if (resident) c = count;
-          if (e1 != hipSuccess) {
-            hipGraph_t tmp = nullptr;
-            (void)hipStreamEndCapture(st, &tmp);
-            if (tmp) (void)hipGraphDestroy(tmp);
-            h->err = "launch failed during graph capture";
-            return FQP_ERR_HIP;
-          }
+        if (launch_block(count) != hipSuccess) {
+          hipGraph_t tmp = nullptr;
+          (void)hipStreamEndCapture(st, &tmp);
+          if (tmp) (void)hipGraphDestroy(tmp);
+          h->err = "launch failed during graph capture";
+          return FQP_ERR_HIP;
         }
         HIP_CHECK(hipStreamEndCapture(st, &h->graph));
         HIP_CHECK(hipGraphInstantiate(&h->gexec, h->graph, nullptr, nullptr, 0));
@@ -950,8 +975,7 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
       }
       HIP_CHECK(hipGraphLaunch(h->gexec, st));
     } else {
-      if (resident) HIP_CHECK(launch_resident(ra, KQ, m, count, st));
-      else for (int c = 0; c < count; ++c) HIP_CHECK(launch_iteration(c));
+      HIP_CHECK(launch_block(count));
       if (S.profile) {
         HIP_CHECK(hipStreamSynchronize(st));
         const int cb = 2 * S.check_every;
@@ -1012,8 +1036,8 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
     if (done_iters < S.first_check && done_iters < S.max_iter) continue;
     HIP_CHECK(hipEventRecord(h->ev_t[2], st));
     // polish + certification rounds on z = prox(v; lam*)
-    // (account-resident blocks leave it behind)
-    if (!resident) HIP_CHECK(launch_prox(ia, m, cap_resident, 1, st));
+    // (account-resident and wide blocks leave it behind)
+    if (!resident && !wide) HIP_CHECK(launch_prox(ia, m, cap_resident, 1, st));
     pa.nf_gate = std::max(4 * k + 64, n / 8 + 4 * k);
     pa.nf_small = 2 * k + 32;
     pa.max_prop = 16;
@@ -1059,7 +1083,7 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   if (!count_known && (e = first_count()) != FQP_OK) return e;   // no block ran
   if (active > 0) {
     // last pattern from the current iterate, diagnostics, final statuses
-    if (!resident) HIP_CHECK(launch_prox(ia, m, cap_resident, 1, st));   // z = prox(v; lam*)
+    if (!resident && !wide) HIP_CHECK(launch_prox(ia, m, cap_resident, 1, st));   // z = prox(v; lam*)
     pa.first_round = 1;
     pa.nf_gate = 0;
     pa.nf_small = 0;
