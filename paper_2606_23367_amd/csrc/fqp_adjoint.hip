@@ -160,22 +160,11 @@ __global__ __launch_bounds__(256) void adjoint_solve_kernel(AdjArgs A) {
   }
   __syncthreads();
   // ---- Cholesky of Kf ------------------------------------------------------
-  for (int j = 0; j < k; ++j) {
-    if (tid == 0) Kf[j * k + j] = sqrt(fmax(Kf[j * k + j], 1e-300));
-    __syncthreads();
-    const double djj = Kf[j * k + j];
-    for (int i = j + 1 + tid; i < k; i += 256) Kf[i * k + j] /= djj;
-    __syncthreads();
-    const int mm = k - j - 1;
-    for (int e = tid; e < mm * mm; e += 256) {
-      const int i = j + 1 + e / mm, l = j + 1 + e % mm;
-      if (l <= i) Kf[i * k + l] -= Kf[i * k + j] * Kf[l * k + j];
-    }
-    __syncthreads();
-  }
+  __shared__ double s_inv[kMaxK];
+  chol_factor(Kf, k, k, s_inv);
   for (int e = tid; e < k * ncol; e += 256) Y[e] = Waug[e];
   __syncthreads();
-  chol_solve_cols(Kf, k, Y, ncol);
+  chol_solve_cols(Kf, k, k, s_inv, Y, ncol);
   for (int e = tid; e < nc * ncol; e += 256) {
     const int p = e / ncol, q = e % ncol;
     double s = CV[p * ncol + q];

@@ -98,37 +98,144 @@ __device__ __forceinline__ int popc_below(uint32_t word, int bit) {
   return __popc(word & ((1u << bit) - 1u));
 }
 
+// a double held by one lane, to all (the lane is uniform)
+__device__ __forceinline__ double lane_d(double x, int l) {
+  const long long b = __builtin_bit_cast(long long, x);
+  const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+
+// a / b from the correctly rounded reciprocal ib of b: the quotient with one
+// correction (Markstein), correctly rounded like the division it replaces
+// for finite operands in range, at three operations in a chain of them
+__device__ __forceinline__ double div_by(double a, double b, double ib) {
+  const double q = a * ib;
+  return fma(fma(-b, q, a), ib, q);
+}
+
+// Cholesky factor of the k x k matrix L (lower triangle, LDS, k <= 128,
+// leading dimension ld) by the whole workgroup, in panels of 8 columns: wave
+// 0 factors a panel with its rows in registers (pivots and multipliers pass
+// by readlane: no LDS or barrier inside it), then every thread updates a slice
+// of the trailing block by the panel's eight columns.  inv[j] takes 1 / L_jj.
+// A column at a time with two barriers took 46 us at k = 60, one wave reading
+// finished columns from LDS 29 us at k = 46; panels take 19 and 11 us.  Ends with a
+// barrier.
+__device__ inline void chol_factor(double* L, int k, int ld, double* inv) {
+  const int tid = threadIdx.x, nt = (int)blockDim.x;
+  for (int p0 = 0; p0 < k; p0 += 8) {
+    if (tid < 64) {
+      const int i0 = p0 + tid, i1 = p0 + 64 + tid;
+      const int nb = min(8, k - p0);
+      double r0[8], r1[8];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        r0[c] = (c < nb && i0 < k && c <= tid) ? L[i0 * ld + p0 + c] : 0.0;
+        r1[c] = (c < nb && i1 < k) ? L[i1 * ld + p0 + c] : 0.0;
+      }
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        if (c >= nb) break;                                   // uniform
+        // the root and its reciprocal from one estimate, refined to the last place
+        const double a = fmax(lane_d(r0[c], c), 1e-300);
+        double id = __builtin_amdgcn_rsq(a);
+        id = fma(0.5 * id, fma(-a * id, id, 1.0), id);
+        id = fma(0.5 * id, fma(-a * id, id, 1.0), id);
+        double d = a * id;
+        d = fma(0.5 * id, fma(-d, d, a), d);
+        id = fma(id, fma(-d, id, 1.0), id);
+        r0[c] = tid == c ? d : div_by(r0[c], d, id);
+        r1[c] = div_by(r1[c], d, id);
+        if (tid == c) inv[p0 + c] = id;
+#pragma unroll
+        for (int e = c + 1; e < 8; ++e) {
+          const double m = lane_d(r0[c], e);                  // L[p0 + e][p0 + c]
+          r0[e] -= r0[c] * m;
+          r1[e] -= r1[c] * m;
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        if (c < nb && i0 < k && c <= tid) L[i0 * ld + p0 + c] = r0[c];
+        if (c < nb && i1 < k) L[i1 * ld + p0 + c] = r1[c];
+      }
+    }
+    __syncthreads();
+    const int b0 = p0 + 8, m = k - b0;
+    if (m > 0) {
+      for (int e = tid; e < m * m; e += nt) {
+        const int i = b0 + e / m, l = b0 + e % m;
+        if (l > i) continue;
+        const double *ri = L + i * ld + p0, *rl = L + l * ld + p0;
+        double s = L[i * ld + l];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) s -= ri[c] * rl[c];
+        L[i * ld + l] = s;
+      }
+      __syncthreads();
+    }
+  }
+}
+
 // Y <- L^-T L^-1 Y for the k x ncol matrix Y (row-major, any memory), L
-// lower (k <= 128).  Columns are independent: wave q solves columns q,
-// q + nwaves, ... with lane i holding rows i and i + 64, so the substitution
-// runs on shuffles without workgroup barriers.  Ends with a barrier.
-__device__ inline void chol_solve_cols(const double* L, int k, double* Y, int ncol) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+// lower (k <= 128, leading dimension ld), inv its inverse diagonal.  Columns
+// are independent: wave q solves columns q, q + nwaves, ... with lane i holding
+// rows i and i + 64; a solved entry passes by readlane, and the entries of L
+// of eight steps are loaded before the first is used.  Ends with a barrier.
+__device__ inline void chol_solve_cols(const double* L, int k, int ld, const double* inv, double* Y,
+                                       int ncol) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = (int)(blockDim.x >> 6);
+  const int l0 = min(lane, k - 1), l1 = min(lane + 64, k - 1);
+  const bool two = k > 64;                                    // uniform
+  // the lane's own pivots and their reciprocals: each step's quotient is formed
+  // in the lane that holds the entry, and passes from there
+  const double d0 = L[l0 * ld + l0], e0 = inv[l0], d1 = L[l1 * ld + l1], e1 = inv[l1];
   for (int c = wv; c < ncol; c += nw) {
     double y0 = (lane < k) ? Y[lane * ncol + c] : 0.0;
     double y1 = (lane + 64 < k) ? Y[(lane + 64) * ncol + c] : 0.0;
-    for (int j = 0; j < k; ++j) {              // L z = y
-      const double yj = (j < 64) ? __shfl(y0, j, 64) : __shfl(y1, j - 64, 64);
-      const double zj = yj / L[j * k + j];
-      if (j < 64) {
-        if (lane == j) y0 = zj;
-        else if (lane > j && lane < k) y0 -= L[lane * k + j] * zj;
-      } else if (lane == j - 64) {
-        y1 = zj;
+    for (int j0 = 0; j0 < k; j0 += 8) {                       // L z = y
+      double a0[8], a1[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int j = min(j0 + u, k - 1);
+        a0[u] = L[l0 * ld + j];
+        a1[u] = two ? L[l1 * ld + j] : 0.0;
       }
-      if (lane + 64 > j && lane + 64 < k) y1 -= L[(lane + 64) * k + j] * zj;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int j = j0 + u;
+        if (j >= k) break;                                    // uniform
+        if (j < 64) {
+          const double z = div_by(y0, d0, e0), zj = lane_d(z, j);
+          y0 = lane == j ? z : (lane > j ? y0 - a0[u] * zj : y0);
+          y1 -= a1[u] * zj;
+        } else {
+          const double z = div_by(y1, d1, e1), zj = lane_d(z, j - 64);
+          y1 = lane == j - 64 ? z : (lane > j - 64 ? y1 - a1[u] * zj : y1);
+        }
+      }
     }
-    for (int j = k - 1; j >= 0; --j) {         // L^T x = z
-      const double zj = (j < 64) ? __shfl(y0, j, 64) : __shfl(y1, j - 64, 64);
-      const double xj = zj / L[j * k + j];
-      if (j < 64) {
-        if (lane == j) y0 = xj;
-        else if (lane < j) y0 -= L[j * k + lane] * xj;
-      } else {
-        if (lane == j - 64) y1 = xj;
-        else if (lane + 64 < j) y1 -= L[j * k + lane + 64] * xj;
-        y0 -= L[j * k + lane] * xj;            // every row i < 64 <= j
+    for (int j0 = (k - 1) & ~7; j0 >= 0; j0 -= 8) {           // L^T x = z
+      double a0[8], a1[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int j = min(j0 + u, k - 1);
+        a0[u] = L[j * ld + min(lane, j)];
+        a1[u] = two ? L[j * ld + min(lane + 64, j)] : 0.0;
+      }
+#pragma unroll
+      for (int u = 7; u >= 0; --u) {
+        const int j = j0 + u;
+        if (j >= k) continue;                                 // uniform
+        if (j < 64) {
+          const double z = div_by(y0, d0, e0), xj = lane_d(z, j);
+          y0 = lane == j ? z : (lane < j ? y0 - a0[u] * xj : y0);
+        } else {
+          const double z = div_by(y1, d1, e1), xj = lane_d(z, j - 64);
+          y1 = lane == j - 64 ? z : (lane < j - 64 ? y1 - a1[u] * xj : y1);
+          y0 -= a0[u] * xj;                                   // every row i < 64 <= j
+        }
       }
     }
     if (lane < k) Y[lane * ncol + c] = y0;

@@ -44,7 +44,6 @@ static_assert(kNPState <= kPStateStride, "polish bookkeeping does not fit");
 
 constexpr double kSnap = 1e-10;
 constexpr int kSmallF = 64;               // free sets solved in row space
-constexpr int kSchurL = 8;                // constraint systems solved in LDS
 constexpr int kMaxNull = 8;
 // the per-account kernels: one workgroup of 16 waves per account (their
 // serial parts are latency bound); the row passes run on row blocks below
@@ -297,32 +296,43 @@ __device__ __forceinline__ void set_band(int* ps, int g, bool act, bool up) {
   *pu = up ? (*pu | (1 << b)) : (*pu & ~(1 << b));
 }
 
-// block sum: wave shuffles, then one partial per wave
-template <typename T>
-__device__ T bsum(T v, T* sh) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-  __syncthreads();
-  T r = sh[0];
-  const int nw = (int)(blockDim.x >> 6);
-  for (int q = 1; q < nw; ++q) r += sh[q];
-  return r;
+// a double from another lane of the row of 16 (a DPP pattern)
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double x) {
+  const long long b = __builtin_bit_cast(long long, x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
 }
+// reduction over the 16 lanes of a row (all of them get it), and over a wave
+// (uniform): quad swaps and row mirrors instead of LDS permutes, 6 round
+// trips of which cost more than what is reduced here
+template <class F>
+__device__ __forceinline__ double row_red(double x, F f) {
+  x = f(x, dpp_d<0xB1>(x));                 // lanes 1 0 3 2
+  x = f(x, dpp_d<0x4E>(x));                 // lanes 2 3 0 1
+  x = f(x, dpp_d<0x141>(x));                // mirrored in eight
+  x = f(x, dpp_d<0x140>(x));                // mirrored in sixteen
+  return x;
+}
+template <class F>
+__device__ __forceinline__ double wave_red(double x, F f) {
+  x = row_red(x, f);
+  return f(f(lane_d(x, 0), lane_d(x, 16)), f(lane_d(x, 32), lane_d(x, 48)));
+}
+struct SumOp { __device__ double operator()(double a, double b) const { return a + b; } };
+struct MaxOp { __device__ double operator()(double a, double b) const { return fmax(a, b); } };
 
 // NS block sums and NM block maxima at once: one pair of barriers for all
-// (sh: (NS + NM) x nwaves doubles); every thread gets the results
+// (sh: (NS + NM) x nwaves doubles); every thread gets the results.  Whole
+// waves only.
 template <int NS, int NM>
 __device__ __forceinline__ void bred(double (&sv)[NS], double (&mv)[NM], double* sh) {
   const int nw = (int)(blockDim.x >> 6), wv = threadIdx.x >> 6;
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
+  for (int q = 0; q < NS; ++q) sv[q] = wave_red(sv[q], SumOp());
 #pragma unroll
-    for (int q = 0; q < NS; ++q) sv[q] += __shfl_xor(sv[q], o, 64);
-#pragma unroll
-    for (int q = 0; q < NM; ++q) mv[q] = fmax(mv[q], __shfl_xor(mv[q], o, 64));
-  }
+  for (int q = 0; q < NM; ++q) mv[q] = wave_red(mv[q], MaxOp());
   __syncthreads();
   if ((threadIdx.x & 63) == 0) {
 #pragma unroll
@@ -331,18 +341,18 @@ __device__ __forceinline__ void bred(double (&sv)[NS], double (&mv)[NM], double*
     for (int q = 0; q < NM; ++q) sh[(NS + q) * nw + wv] = mv[q];
   }
   __syncthreads();
+  // the waves' partials, one a lane of each row of 16
+  const int l = min((int)threadIdx.x & 15, nw - 1);
 #pragma unroll
-  for (int q = 0; q < NS; ++q) {
-    double r = sh[q * nw];
-    for (int w = 1; w < nw; ++w) r += sh[q * nw + w];
-    sv[q] = r;
-  }
+  for (int q = 0; q < NS; ++q)
+    sv[q] = lane_d(row_red(((int)threadIdx.x & 15) < nw ? sh[q * nw + l] : 0.0, SumOp()), 0);
 #pragma unroll
-  for (int q = 0; q < NM; ++q) {
-    double r = sh[(NS + q) * nw];
-    for (int w = 1; w < nw; ++w) r = fmax(r, sh[(NS + q) * nw + w]);
-    mv[q] = r;
-  }
+  for (int q = 0; q < NM; ++q) mv[q] = lane_d(row_red(sh[(NS + q) * nw + l], MaxOp()), 0);
+}
+__device__ __forceinline__ double bsum(double v, double* sh) {
+  double sv[1] = {v}, mv[1] = {0.0};
+  bred<1, 1>(sv, mv, sh);
+  return sv[0];
 }
 
 // row_coef / rows_dot with the row's label already loaded (grp, unused
@@ -424,31 +434,56 @@ __device__ void list_sums(const PolishArgs& A, const int32_t* list, int n, int c
 // Row-space solve of a small free set (nF <= kSmallF): with the free rows'
 // constraint coefficients V_r = [1, band coefficients, sgn_r | rhs_r] and
 // H = gamma Sigma_FF = gamma (B_F diag(f) B_F^T + diag(d_F)), it forms H,
-// factors it (Cholesky by one wave), solves X = H^-1 V and writes the Schur
-// block S = V_C^T X = C H^-1 [C^T | rhs] the factor-space path forms by
-// Woodbury.  It also adds sum_F sgn_r w0_r to the cap's right-hand side.
-// Returns X ([nF][ncol], LDS) for the free-row values.
-__device__ double* small_free_solve(const PolishArgs& A, int a, int nF, const int32_t* flist,
-                                    const int8_t* code, const int* ps, int nc, int ncol,
-                                    int cap_on, double gam, float lbf, float ubf, float kap,
-                                    bool phi, const Wk& wk, double* sm, double* shd,
-                                    double* hd, double* Sd, int& i_mine, float& w0_mine) {
-  const int k = A.k, G = A.G, tid = threadIdx.x, n = A.n;
-  double* Hs = sm;                                   // [nF][nF]
-  double* Vs = Hs + kSmallF * kSmallF;               // [nF][ncol]
-  double* Xs = Vs + kSmallF * ncol;                  // [nF][ncol]
-  double* fs = Xs + kSmallF * ncol;                  // [k]
-  double* fys = fs + k;                              // [k] F yX
-  double* crs = fys + k;                             // [nF] b_r . F yX
-  float* Bs = reinterpret_cast<float*>(crs + kSmallF);   // [nF][k]
-  // stage the free rows' B, f and F yX
-  for (int e = tid; e < nF * k; e += kPT) {
-    const int r = e / k, j = e % k;
-    Bs[e] = A.Bt[(size_t)flist[r] * A.kp + j];
+// factors it, solves X = H^-1 V and writes the Schur block
+// S = V_C^T X = C H^-1 [C^T | rhs] the factor-space path forms by Woodbury
+// (over H, which is done with by then).  It also adds sum_F sgn_r w0_r to the
+// cap's right-hand side.  LDS: H [nF][kHld], V and X [nF][ncol], f and F yX
+// [k], b_r . F yX [nF], 1 / L_jj [nF] (doubles), the free rows of B~'s first
+// k + G columns (floats).
+constexpr int kHld = kSmallF + 1;         // odd: a column of H spreads over the banks
+struct SmallLds {
+  double *Hs, *Vs, *Xs, *fs, *fys, *crs, *inv;
+  float* Bs;
+};
+__device__ __forceinline__ SmallLds small_lds(double* sm, int k, int ncol) {
+  SmallLds L;
+  L.Hs = sm;
+  L.Vs = L.Hs + kSmallF * kHld;
+  L.Xs = L.Vs + kSmallF * ncol;
+  L.fs = L.Xs + kSmallF * ncol;
+  L.fys = L.fs + k;
+  L.crs = L.fys + k;
+  L.inv = L.crs + kSmallF;
+  L.Bs = reinterpret_cast<float*>(L.inv + kSmallF);
+  return L;
+}
+
+__device__ __forceinline__ void small_free_solve(const PolishArgs& A, int a, int nF, const int32_t* flist,
+                                 const int8_t* code, const int* ps, int nc, int ncol, int cap_on,
+                                 double gam, float lbf, float ubf, float kap, bool phi,
+                                 const double* fy, const SmallLds& L, double* shd, double* hd,
+                                 double* Sd, int& i_mine, float& w0_mine) {
+  const int k = A.k, G = A.G, kg = k + G, tid = threadIdx.x, n = A.n;
+  double *Hs = L.Hs, *Vs = L.Vs, *Xs = L.Xs;
+  // stage the free rows' B~, f and F yX; the thread's own free row (nF <=
+  // kPT) starts its loads meanwhile
+  RowData rd;
+  int cd = 0;
+  double mu_r = 0.0;
+  if (tid < nF) {
+    i_mine = flist[tid];
+    cd = code[i_mine];
+    mu_r = mu_at(A, (size_t)a * n + i_mine);
+    rd = row_data(A, a, i_mine, lbf, ubf);
+    w0_mine = rd.w0;
+  }
+  for (int e = tid; e < nF * kg; e += kPT) {
+    const int r = e / kg, j = e % kg;
+    L.Bs[e] = A.Bt[(size_t)flist[r] * A.kp + j];
   }
   for (int j = tid; j < k; j += kPT) {
-    fs[j] = (double)A.f[j];
-    fys[j] = wk.Fy[j];
+    L.fs[j] = (double)A.f[j];
+    L.fys[j] = fy[j];
   }
   __syncthreads();
   // b_r . F yX: one wave per free row, its lanes over the factors
@@ -456,84 +491,56 @@ __device__ double* small_free_solve(const PolishArgs& A, int a, int nF, const in
     const int lane = tid & 63, wv = tid >> 6;
     for (int r = wv; r < nF; r += kPW) {
       double c = 0.0;
-      for (int j = lane; j < k; j += 64) c += (double)Bs[r * k + j] * fys[j];
+      for (int j = lane; j < k; j += 64) c += (double)L.Bs[r * kg + j] * L.fys[j];
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o, 64);
-      if (lane == 0) crs[r] = c;
+      if (lane == 0) L.crs[r] = c;
     }
   }
   __syncthreads();
-  // the constraint / rhs rows (free row r is the thread's own: nF <= kPT;
-  // its row and w0 are kept for the caller)
+  // the constraint / rhs row of the thread's free row
   double sgn_w0 = 0.0;
-  for (int r = tid; r < nF; r += kPT) {
-    const int i = flist[r];
-    RowData rd = row_data(A, a, i, lbf, ubf);
-    i_mine = i;
-    w0_mine = rd.w0;
+  if (tid < nF) {
+    const int r = tid;
     Geom g;
     make_geom(g, kap, phi, rd);
     double slope, sgn;
-    piece_slope(g, code[i] >> 1, slope, sgn);
-    const double cross = crs[r];
+    piece_slope(g, cd >> 1, slope, sgn);
     double* v = Vs + r * ncol;
     v[0] = 1.0;
     int col = 1;
     for (int gg = 0; gg < G; ++gg) {
       if (!band_active(ps, gg)) continue;
-      v[col++] = row_coef(A, i, gg);
+      v[col++] = (double)L.Bs[r * kg + k + gg];
     }
     if (cap_on) v[col++] = sgn;
-    v[col] = mu_at(A, (size_t)a * n + i) - slope - gam * cross;
-    sgn_w0 += sgn * (double)rd.w0;
+    v[col] = mu_r - slope - gam * L.crs[r];
+    sgn_w0 = sgn * (double)rd.w0;
   }
-  sgn_w0 = bsum<double>(sgn_w0, shd);            // (synchronises the staging)
+  sgn_w0 = bsum(sgn_w0, shd);            // (synchronises the staging)
   if (tid == 0 && cap_on) hd[nc - 1] += sgn_w0;
   // H, lower triangle
   for (int e = tid; e < nF * nF; e += kPT) {
     const int r = e / nF, c = e % nF;
     if (c > r) continue;
-    const float* br = Bs + r * k;
-    const float* bc = Bs + c * k;
+    const float* br = L.Bs + r * kg;
+    const float* bc = L.Bs + c * kg;
     double h = 0.0;
-    for (int j = 0; j < k; ++j) h += (double)br[j] * fs[j] * (double)bc[j];
+    for (int j = 0; j < k; ++j) h += (double)br[j] * L.fs[j] * (double)bc[j];
     if (r == c) h += (double)A.d[flist[r]];
-    Hs[e] = gam * h;
+    Hs[r * kHld + c] = gam * h;
   }
   for (int e = tid; e < nF * ncol; e += kPT) Xs[e] = Vs[e];
   __syncthreads();
-  // Cholesky by wave 0, column by column: at step j lane i >= j forms
-  // H_ij - sum_{l<j} L_il L_jl (the same subtractions, in the same order, as
-  // updating the trailing block after each column), reading only finished
-  // columns, so its loads do not wait on one another; the pivot comes from
-  // lane j by a shuffle.  (LDS accesses of one wave complete in order; the
-  // fences keep the compiler from moving them across the step boundary.)
-  if (tid < 64) {
-    const int i = tid;
-    for (int j = 0; j < nF; ++j) {
-      double sij = 0.0;
-      if (i >= j && i < nF) {
-        sij = Hs[i * nF + j];
-        for (int l = 0; l < j; ++l) sij -= Hs[i * nF + l] * Hs[j * nF + l];
-      }
-      const double djj = sqrt(fmax(__shfl(sij, j, 64), 1e-300));
-      if (i == j) Hs[j * nF + j] = djj;
-      else if (i > j && i < nF) Hs[i * nF + j] = sij / djj;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-  }
-  __syncthreads();
-  chol_solve_cols(Hs, nF, Xs, ncol);               // X = H^-1 V (ends synchronised)
+  chol_factor(Hs, nF, kHld, L.inv);
+  chol_solve_cols(Hs, nF, kHld, L.inv, Xs, ncol);        // X = H^-1 V (ends synchronised)
   // S = V_C^T X
   for (int e = tid; e < nc * ncol; e += kPT) {
-    const int p = e / ncol, q = e % ncol;
+    const int q0 = e / ncol, q = e % ncol;
     double s = 0.0;
-    for (int r = 0; r < nF; ++r) s += Vs[r * ncol + p] * Xs[r * ncol + q];
-    Sd[p * ncol + q] = s;
+    for (int r = 0; r < nF; ++r) s += Vs[r * ncol + q0] * Xs[r * ncol + q];
+    Sd[q0 * ncol + q] = s;
   }
-  return Xs;
 }
 
 // ---------------------------------------------------------------------------
@@ -725,6 +732,99 @@ __global__ __launch_bounds__(kRT) void polish_rows_kernel(PolishArgs A) {
   }
 }
 
+// The same system by one wave (nc <= kSchurW), lane i its row i: the pivot by
+// a maximum and a ballot, the pivot's column of the remaining matrix from S
+// and the factor's columns before it (Lt, a row of kSchurW doubles per step,
+// in LDS), one unknown a lane in the triangular solves.  One thread walking
+// the system through global memory was 78 us at 10 columns, 265 at 15
+// (8 x 384,800), more than the rest of the solve.
+constexpr int kSchurW = 44;               // S and Lt fit where H was
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ __forceinline__ int schur_solve_wave(int nc, int ncol, const double* S, const double* hv,
+                                                const double* e0, double* Lt, double* rr,
+                                                double* nul, int nul_stride) {
+  const int lane = threadIdx.x & 63, row = min(lane, nc - 1);
+  const bool on = lane < nc;
+  const double* Sr = S + row * ncol;
+  double dg = on ? Sr[row] : -INFINITY;               // the remaining matrix's diagonal
+  const double ptol = 1e-12 * fmax(wave_red(dg, MaxOp()), 0.0);
+  // pos: the row's place in the pivoted order; ord: lane l holds the row in
+  // place l; pos1: the place after the first exchange (an entry is read from
+  // the side of S that is its lower triangle then, as S is symmetric only up to
+  // rounding and the serial form below mirrors that side)
+  int pos = lane, ord = lane, pos1 = lane;
+  double ld = 1.0, id = 1.0;                          // L_pp of a pivot row, 1 / L_pp
+  int rank = 0;
+  for (int j = 0; j < nc; ++j) {
+    const double mx = wave_red(on && pos >= j ? dg : -INFINITY, MaxOp());
+    if (!(mx > ptol)) break;                          // uniform
+    // the largest remaining pivot, the first in place among equals
+    unsigned long long tie = __ballot(on && pos >= j && dg == mx);
+    int p = __ffsll(tie) - 1, pb = __builtin_amdgcn_readlane(pos, p);
+    for (tie &= tie - 1; tie; tie &= tie - 1) {
+      const int q = __ffsll(tie) - 1, qb = __builtin_amdgcn_readlane(pos, q);
+      if (qb < pb) { p = q; pb = qb; }
+    }
+    const int oj = __builtin_amdgcn_readlane(ord, j);  // the row in place j moves to place pb
+    pos = lane == p ? j : (lane == oj ? pb : pos);
+    ord = lane == j ? p : (lane == pb ? oj : ord);
+    // (with the pivot in place j already both lines change nothing)
+    if (j == 0) pos1 = pos;
+    double c = pos1 >= __builtin_amdgcn_readlane(pos1, p) ? Sr[p] : S[p * ncol + row];
+    for (int l = 0; l < j; ++l) c -= Lt[l * kSchurW + row] * Lt[l * kSchurW + p];
+    const double djj = sqrt(mx), ij = 1.0 / djj;
+    c = lane == p ? djj : div_by(c, djj, ij);
+    if (lane == p) { ld = djj; id = ij; }
+    if (on) Lt[j * kSchurW + lane] = c;
+    if (on && pos > j) dg -= c * c;
+    wave_sync();
+    ++rank;
+  }
+  // right-hand side on the pivot rows, null components from eta0
+  double x = (on && pos >= rank) ? e0[row] : 0.0;
+  double t = on ? Sr[nc] - hv[row] : 0.0;
+  for (int q = rank; q < nc; ++q) {
+    const int pq = __builtin_amdgcn_readlane(ord, q);
+    t -= Sr[pq] * lane_d(x, pq);
+  }
+  if (pos < rank) x = t;
+  for (int l = 0; l < rank; ++l) {                    // L11 z = rhs
+    const int p = __builtin_amdgcn_readlane(ord, l);
+    const double xl = div_by(lane_d(x, p), lane_d(ld, p), lane_d(id, p));
+    const double lv = Lt[l * kSchurW + row];
+    x = lane == p ? xl : (pos > l && pos < rank ? x - lv * xl : x);
+  }
+  // L11^T y = z for x and for the null directions v_piv = -L11^-T L21^T e_t,
+  // v_t = 1: a right-hand side a lane (0: x, 1 + q: null direction q), the
+  // unknowns of place l in xs[l][lane]
+  const int nd = min(nc - rank, kMaxNull);
+  double* xs = Lt + rank * kSchurW;                   // [rank][1 + kMaxNull]
+  constexpr int kR = 1 + kMaxNull;
+  const int r = min(lane, nd);
+  if (on && pos < rank) xs[pos * kR] = x;
+  wave_sync();
+  const int tl = r > 0 ? __builtin_amdgcn_ds_bpermute(4 * (rank + r - 1), ord) : 0;
+  for (int i = rank - 1; i >= 0; --i) {
+    const int p = __builtin_amdgcn_readlane(ord, i);
+    double y = r > 0 ? -Lt[i * kSchurW + tl] : xs[i * kR];
+    for (int l = i + 1; l < rank; ++l)
+      y -= Lt[i * kSchurW + __builtin_amdgcn_readlane(ord, l)] * xs[l * kR + r];
+    y = div_by(y, lane_d(ld, p), lane_d(id, p));
+    if (lane <= nd) xs[i * kR + r] = y;
+    wave_sync();
+  }
+  if (on) {
+    rr[lane] = pos < rank ? xs[pos * kR] : x;
+    for (int q = 0; q < nd; ++q)
+      nul[q * nul_stride + lane] = pos < rank ? xs[pos * kR + 1 + q] : (pos == rank + q ? 1.0 : 0.0);
+  }
+  return nd;
+}
+
 // S eta = C H^-1 rhs - h for the multipliers of the active constraint
 // columns, with S = C H^-1 C^T positive semidefinite (nc x ncol, the rhs
 // column last).  A pivoted Cholesky finds the rank r; the pivot components
@@ -797,105 +897,141 @@ __device__ __forceinline__ int schur_solve(int nc, int ncol, const double* Sv, c
   return nd;
 }
 
-__global__ __launch_bounds__(kPT) void polish_solve_kernel(PolishArgs A) {
-  extern __shared__ double smem_d[];
-  const int k = A.k, G = A.G, n = A.n;
-  double* Kf = smem_d;                      // [k][k]
-  // the Kf region also stages 64 float B rows before Kf is built
-  const int kfsz = max(k * k, (64 * (k + 1) + 1) / 2);
-  double* stg = Kf + kfsz;                  // staging: 16 rows x (k + 4)
-  __shared__ double shd[kPW];
-  __shared__ int s_same;
-  // the constraint system when nc <= kSchurL
-  __shared__ double s_S[kSchurL * (kSchurL + 1)], s_Sm[kSchurL * kSchurL];
-  __shared__ double s_h[kSchurL], s_e0[kSchurL], s_eta[kSchurL], s_x[kSchurL], s_v[kSchurL];
-  __shared__ int s_perm[kSchurL];
-  __shared__ double s_m0[kMaxG + 2];       // multipliers of the previous pattern
-  const int slot = blockIdx.x;
-  if (slot >= *A.m_act) return;
-  const int a = A.act[slot];
-  const int tid = threadIdx.x;
-  int* ps = A.pstate + (size_t)a * kPStateStride;
-  const float* par = A.par + (size_t)a * kNPar;
-  const float lbf = par[P_LB], ubf = par[P_UB], kap = par[P_KAPPA], tauf = par[P_TAU];
-  const double gam = par[P_GAMMA];
-  const bool phi = (kap > 0.f) || isfinite(tauf) || (par[P_HASTAX] != 0.f);
-  Wk wk = wk_of(A, a);
-  int8_t* code = A.code + (size_t)a * n;
-  int32_t* flist = A.flist + (size_t)a * n;         // free rows from the front
-  double* w = A.wout + (size_t)a * n;
+// leading dimension of Kf in LDS: odd where the space allows (a column then
+// spreads over the banks)
+__host__ __device__ __forceinline__ int kf_ld(int k) { return k <= 100 ? (k | 1) : k; }
 
-  if (A.first_round) {
-    if (tid == 0) {
-      ps[PS_CAP] = isfinite(tauf) && par[P_LAM] > 0.f;
-      ps[PS_DONE] = 0;
-      ps[PS_ROUNDS] = 0;
-      ps[PS_STALL] = 0;
-      ps[PS_BACT0] = ps[PS_BACT1] = ps[PS_BUP0] = ps[PS_BUP1] = 0;
-      double* mult = A.mult + (size_t)a * (2 + G);
-      mult[0] = par[P_NU];
-      mult[1] = fmax((double)par[P_LAM], 0.0);
-      for (int g = 0; g < G; ++g) {
-        const float zb = A.zb[(size_t)a * G + g];
-        const float lo = A.blo[(size_t)a * G + g], hi = A.bhi[(size_t)a * G + g];
-        if (zb >= hi) set_band(ps, g, true, true);
-        else if (zb <= lo) set_band(ps, g, true, false);
-        mult[2 + g] = (double)par[P_RHOB] * (double)A.vb[(size_t)a * G + g];
-      }
+// rows staged at a time by the factor-space path: [b | V | pad | 1 / d]
+__host__ __device__ __forceinline__ int stage_stride(int k, int ncol) {
+  return 4 * ((k + ncol + 3) / 4) + 4;
+}
+__host__ __device__ __forceinline__ int stage_rows(int k, int G) {
+  // as many of 64 rows as fit beside Kf in 144 KB, at least 16
+  const int left = 144 * 1024 - 8 * k * kf_ld(k);
+  const int r = left / (8 * stage_stride(k, G + 3));
+  return r >= 64 ? 64 : r >= 32 ? 32 : 16;
+}
+
+// what the per-account phases of a refinement round hand on in LDS
+struct AcctLds {
+  double mult[2 + kMaxG];      // in: of the previous pattern, out: of this one
+  double fy[kMaxK];            // F B_X^T w_X (fixed rows)
+  double gfix[kMaxG];          // the fixed rows' constraint-row sums
+  double yF[kMaxK + 16];       // F B^T w of the polished w
+  double gsum[kMaxG];          // its constraint-row sums
+  double sh[2 * kPW];
+};
+
+// the fixed rows' side of a pattern (yx, f: column tid < k)
+struct PatternSums {
+  int nF, nX;                  // free rows, nonzero fixed rows
+  double sx, sturn;            // budget and turnover of the fixed rows
+  double yx, f;
+  unsigned sig;
+};
+
+// first round of a pass: the active rows, the cap and the multipliers of
+// the iterate (by the first wave; the caller synchronises)
+__device__ __forceinline__ void begin_pass(const PolishArgs& A, int a, const float* par, int* ps,
+                                           double* mult) {
+  const int tid = threadIdx.x, G = A.G;
+  if (tid >= 64) return;
+  // active rows, one lane each (G <= 64: one wave)
+  bool act = false, up = false;
+  if (tid < G) {
+    const float zb = A.zb[(size_t)a * G + tid];
+    const float lo = A.blo[(size_t)a * G + tid], hi = A.bhi[(size_t)a * G + tid];
+    up = zb >= hi;
+    act = up || zb <= lo;
+    mult[2 + tid] = (double)par[P_RHOB] * (double)A.vb[(size_t)a * G + tid];
+  }
+  const unsigned long long ma = __ballot(act), mu = __ballot(up);
+  if (tid == 0) {
+    ps[PS_CAP] = isfinite(par[P_TAU]) && par[P_LAM] > 0.f;
+    ps[PS_DONE] = 0;
+    ps[PS_ROUNDS] = 0;
+    ps[PS_STALL] = 0;
+    ps[PS_BACT0] = (int)(unsigned)ma;
+    ps[PS_BACT1] = (int)(unsigned)(ma >> 32);
+    ps[PS_BUP0] = (int)(unsigned)mu;
+    ps[PS_BUP1] = (int)(unsigned)(mu >> 32);
+    mult[0] = par[P_NU];
+    mult[1] = fmax((double)par[P_LAM], 0.0);
+  }
+}
+
+// Whether this round leaves the account to the next block of iterations: a
+// pattern with many free coordinates belongs to an iterate that is far from
+// the optimum's vertex structure (the solve is costly), and a larger free set
+// is solved only when the iterate shows the same pattern at two consecutive
+// checks.  Uniform (s_same: one int of LDS; ends synchronised).
+__device__ __forceinline__ bool gated(const PolishArgs& A, int first, int* ps,
+                                      const PatternSums& X, int* s_same) {
+  if (first) {
+    if (threadIdx.x == 0) {
+      const unsigned sig = X.sig + (unsigned)ps[PS_CAP] * 97u + (unsigned)ps[PS_BACT0] * 31u +
+                           (unsigned)ps[PS_BACT1] * 7u + (unsigned)ps[PS_BUP0] * 5u +
+                           (unsigned)ps[PS_BUP1] * 3u;
+      *s_same = (unsigned)ps[PS_SIG] == sig;
+      ps[PS_SIG] = (int)sig;
     }
     __syncthreads();
-  } else if (ps[PS_DONE] || ps[PS_STALL]) {
-    return;
   }
-  const int cap_on = ps[PS_CAP];
+  if ((A.nf_gate > 0 && X.nF > A.nf_gate) ||
+      (first && A.nf_small > 0 && X.nF > A.nf_small && !*s_same)) {
+    if (threadIdx.x == 0) { ps[PS_STALL] = 1; ps[PS_NF] = X.nF; atomicAdd(A.pcount + 1, 1); }
+    return true;
+  }
+  if (threadIdx.x == 0) atomicAdd(A.pcount, 1);
+  return false;
+}
 
-  // ---- gather the row blocks of polish_rows: the free list at the front of
-  // flist and the nonzero fixed list at its back (both in ascending row
-  // order), the budget and turnover sums of the fixed rows, the pattern's
-  // signature, yX = B_X^T w_X and the fixed rows' constraint-row sums
+// the row blocks of polish_rows gathered: the free list at the front of
+// flist and the nonzero fixed list at its back (both in ascending row
+// order), the budget and turnover sums of the fixed rows, the pattern's
+// signature, yX = B_X^T w_X and the fixed rows' constraint-row sums (ends
+// synchronised)
+__device__ __forceinline__ PatternSums gather_pattern(const PolishArgs& A, int a, double* smem_d,
+                                                      AcctLds& W) {
+  const int k = A.k, G = A.G, n = A.n, tid = threadIdx.x;
+  int32_t* flist = A.flist + (size_t)a * n;         // free rows from the front
+  PatternSums X;
   const int S = A.n_sb, kg = k + G, rps = rpart_stride(k, G);
   const double* rp = A.rpart + (size_t)a * S * rps;
   const int32_t* fseg = A.fseg + (size_t)a * n;
-  int* s_of = reinterpret_cast<int*>(Kf);       // [S + 1] free-list offsets (Kf not built yet)
-  int* s_ox = s_of + (S + 1);                    // [S + 1] nonzero-list offsets
-  __shared__ double s_gfix[kMaxG];
+  double* s_part = smem_d;                      // [parts][kg + 2] column sums of a share of the blocks
+  int* s_of = reinterpret_cast<int*>(smem_d + kPT);   // [S + 1] free-list offsets (Kf not built yet)
+  int* s_ox = s_of + (S + 1);                   // [S + 1] nonzero-list offsets
   __shared__ double s_sx[2];
   __shared__ unsigned s_sig;
+  if (tid == 0) s_sig = 0u;
   for (int bb = tid; bb < S; bb += kPT) {
     s_of[bb + 1] = (int)rp[(size_t)bb * rps + kg + 2];
     s_ox[bb + 1] = (int)rp[(size_t)bb * rps + kg + 3];
   }
-  // the multipliers of the previous pattern, for the constraint system
-  // below (the first round's were written above)
-  for (int e = tid; e < 2 + G; e += kPT) s_m0[e] = A.mult[(size_t)a * (2 + G) + e];
-  // column j of the partials summed in block order, sixteen blocks' loads
-  // in flight at a time (past the last block: zeros, added at the end); the
-  // signature (column kg + 4) by one thread
-  unsigned sig = 0u;
-  double yx_mine = 0.0, f_mine = 0.0;       // column tid < k: yX and f
-  for (int j = tid; j < kg + 5; j += kPT) {
-    if (j >= kg + 2 && !(A.first_round && j == kg + 4)) continue;
-    double v = 0.0;
+  __syncthreads();
+  if (A.first_round) {                          // the pattern's signature: any order
     unsigned su = 0u;
-    for (int bb = 0; bb < S; bb += 16) {
+    for (int bb = tid; bb < S; bb += kPT) su += (unsigned)rp[(size_t)bb * rps + kg + 4];
+    if (su) atomicAdd(&s_sig, su);
+  }
+  // columns of the partials: a share of the blocks per part, sixteen blocks'
+  // loads in flight a thread (past the share's end its last block's, dropped)
+  const int cols = kg + 2;
+  const int parts = max(1, min(kPT / cols, (S + 15) / 16));
+  const int share = (S + parts - 1) / parts;
+  if (tid < parts * cols) {
+    const int j = tid % cols, b0 = (tid / cols) * share, b1 = min(S, b0 + share);
+    double v = 0.0;
+    for (int bb = b0; bb < b1; bb += 16) {
       double x[16];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) x[u] = bb + u < S ? rp[(size_t)(bb + u) * rps + j] : 0.0;
+      for (int u = 0; u < 16; ++u) x[u] = rp[(size_t)min(bb + u, b1 - 1) * rps + j];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) { v += x[u]; su += (unsigned)x[u]; }
+      for (int u = 0; u < 16; ++u) v += bb + u < b1 ? x[u] : 0.0;
     }
-    if (j < k) {
-      const double fj = (double)A.f[j];
-      wk.yX[j] = v;
-      wk.Fy[j] = v * fj;
-      yx_mine = v;                          // (j = tid: kg + 5 <= kPT)
-      f_mine = fj;
-    }
-    else if (j < kg) s_gfix[j - k] = v;
-    else if (j < kg + 2) s_sx[j - kg] = v;
-    else s_sig = su;
+    s_part[tid] = v;
   }
-  __syncthreads();
   // block offsets of the two lists: prefix sums (a wave scan when the
   // account has at most 64 row blocks)
   if (S <= 64) {
@@ -909,16 +1045,41 @@ __global__ __launch_bounds__(kPT) void polish_solve_kernel(PolishArgs A) {
       if (tid < S) { s_of[tid + 1] = vf; s_ox[tid + 1] = vx; }
       if (tid == 0) { s_of[0] = 0; s_ox[0] = 0; }
     }
-  } else if (tid == 0) {
-    s_of[0] = 0;
-    s_ox[0] = 0;
-    for (int bb = 0; bb < S; ++bb) {
-      s_of[bb + 1] += s_of[bb];
-      s_ox[bb + 1] += s_ox[bb];
+  } else if (tid < 64) {
+    // 64 blocks at a time, the running totals carried by every lane
+    int cf = 0, cx = 0;
+    if (tid == 0) { s_of[0] = 0; s_ox[0] = 0; }
+    for (int b0 = 0; b0 < S; b0 += 64) {
+      const int bb = b0 + tid;
+      int vf = bb < S ? s_of[bb + 1] : 0, vx = bb < S ? s_ox[bb + 1] : 0;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int uf = __shfl_up(vf, o, 64), ux = __shfl_up(vx, o, 64);
+        if (tid >= o) { vf += uf; vx += ux; }
+      }
+      if (bb < S) { s_of[bb + 1] = cf + vf; s_ox[bb + 1] = cx + vx; }
+      cf += __shfl(vf, 63, 64);
+      cx += __shfl(vx, 63, 64);
     }
   }
   __syncthreads();
+  X.yx = 0.0;
+  X.f = 0.0;
+  if (tid < cols) {
+    double v = s_part[tid];
+    for (int q = 1; q < parts; ++q) v += s_part[q * cols + tid];
+    if (tid < k) {
+      const double fj = (double)A.f[tid];
+      W.fy[tid] = v * fj;
+      X.yx = v;
+      X.f = fj;
+    }
+    else if (tid < kg) W.gfix[tid - k] = v;
+    else s_sx[tid - kg] = v;
+  }
   const int nF = s_of[S], nX = s_ox[S];
+  X.nF = nF;
+  X.nX = nX;
   // entry e of a list lies in the last block whose offset is <= e
   auto block_of = [&](const int* off, int e) {
     int lo = 0, hi = S;
@@ -936,269 +1097,262 @@ __global__ __launch_bounds__(kPT) void polish_solve_kernel(PolishArgs A) {
     const int bb = block_of(s_ox, e);
     flist[n - 1 - e] = fseg[(size_t)bb * kRB + rows_in_block(n, bb) - 1 - (e - s_ox[bb])];
   }
-  const double sx = s_sx[0], sturn = s_sx[1];
-  if (A.first_round) {
-    if (tid == 0) {
-      sig = s_sig + (unsigned)ps[PS_CAP] * 97u + (unsigned)ps[PS_BACT0] * 31u + (unsigned)ps[PS_BACT1] * 7u +
-             (unsigned)ps[PS_BUP0] * 5u + (unsigned)ps[PS_BUP1] * 3u;
-      s_same = (unsigned)ps[PS_SIG] == sig;
-      ps[PS_SIG] = (int)sig;
-    }
-    __syncthreads();
-  }
-  // a pattern with many free coordinates belongs to an iterate that is far
-  // from the optimum's vertex structure: skip the (costly) solve for now
-  if ((A.nf_gate > 0 && nF > A.nf_gate) ||
-      // a larger free set is solved only when the iterate shows the same
-      // pattern at two consecutive checks
-      (A.first_round && A.nf_small > 0 && nF > A.nf_small && !s_same)) {
-    if (tid == 0) { ps[PS_STALL] = 1; ps[PS_NF] = nF; atomicAdd(A.pcount + 1, 1); }
-    return;
-  }
-  if (tid == 0) atomicAdd(A.pcount, 1);
-  __syncthreads();                          // the lists are complete; s_of / s_ox are dead
+  __syncthreads();
+  X.sx = s_sx[0];
+  X.sturn = s_sx[1];
+  X.sig = s_sig;
+  return X;
+}
+
+// the solve of one account's pattern by a workgroup of kPT threads; smem_d:
+// dynamic LDS of polish_smem bytes; ps: its bookkeeping (global or LDS).
+// Leaves the free rows' weights in wout, W.mult, W.yF, W.gsum (not
+// synchronised) and returns the turnover of the polished weights.
+__device__ __forceinline__ double solve_pattern(const PolishArgs& A, int a, const float* par, int* ps,
+                                                const PatternSums& X, double* smem_d, AcctLds& W) {
+  const int k = A.k, G = A.G, n = A.n, tid = threadIdx.x;
+  const float lbf = par[P_LB], ubf = par[P_UB], kap = par[P_KAPPA], tauf = par[P_TAU];
+  const double gam = par[P_GAMMA];
+  const bool phi = (kap > 0.f) || isfinite(tauf) || (par[P_HASTAX] != 0.f);
+  const Wk wk = wk_of(A, a);
+  const int8_t* code = A.code + (size_t)a * n;
+  const int32_t* flist = A.flist + (size_t)a * n;
+  double* w = A.wout + (size_t)a * n;
+  double* Kf = smem_d;                      // [k][kf_ld]
+  double* const shd = W.sh;
+  // the constraint system's vectors when it is solved in LDS
+  __shared__ double s_h[kSchurW], s_e0[kSchurW], s_eta[kSchurW];
+  __shared__ double s_wf[kSmallF];         // small free sets: the free weights
+  __shared__ double s_inv[kMaxK];          // 1 / L_jj of Kf
+  const int cap_on = ps[PS_CAP], nF = X.nF, kg = k + G;
 
   // active constraint columns: 0 budget, bands (active order), cap
-  int nb = 0;
-  for (int g = 0; g < G; ++g) nb += band_active(ps, g) ? 1 : 0;
+  const unsigned act0 = (unsigned)ps[PS_BACT0], act1 = (unsigned)ps[PS_BACT1];
+  const int nb = __popc(act0) + __popc(act1);
   const int nc = 1 + nb + (cap_on ? 1 : 0);
   const int ncol = nc + 1;                      // + rhs column
-  // a constraint system of at most kSchurL columns lives in LDS (h, S and
-  // its factor): its thread-0 solve below is then a chain of LDS accesses,
-  // not of global memory round trips
-  const bool sl = nc <= kSchurL;
+  // the column of active row g
+  auto col_of = [&](int g) {
+    return g < 32 ? 1 + __popc(act0 & ((1u << g) - 1u))
+                  : 1 + __popc(act0) + __popc(act1 & ((1u << (g - 32)) - 1u));
+  };
+  // a constraint system of at most kSchurW columns lives in LDS and is
+  // solved by one wave
+  const bool sl = nc <= kSchurW;
   double* hd = sl ? s_h : wk.h;
-  double* Sd = sl ? s_S : wk.S;
-  {
-    if (tid == 0) {
-      hd[0] = 1.0 - sx;
-      int col = 1;
-      for (int g = 0; g < G; ++g) {
-        if (!band_active(ps, g)) continue;
-        const double bnd = band_upper(ps, g) ? A.bhi[(size_t)a * G + g] : A.blo[(size_t)a * G + g];
-        hd[col] = bnd - s_gfix[g];
-        ++col;
-      }
-      if (cap_on) hd[col] = (double)tauf - sturn;     // + sum_F sgn w0 added below
-      ps[PS_NF] = nF;
-      ps[PS_NX] = nX;
-      ps[PS_NC] = nc;
-    }
+  double* Sd = sl ? smem_d : wk.S;              // where H or Kf was, once they are done with
+  if (tid < G && band_active(ps, tid)) {
+    const double bnd = band_upper(ps, tid) ? A.bhi[(size_t)a * G + tid] : A.blo[(size_t)a * G + tid];
+    hd[col_of(tid)] = bnd - W.gfix[tid];
   }
-  __syncthreads();
+  if (tid == 0) {
+    hd[0] = 1.0 - X.sx;
+    if (cap_on) hd[nc - 1] = (double)tauf - X.sturn;     // + sum_F sgn w0 added below
+    ps[PS_NF] = nF;
+    ps[PS_NX] = X.nX;
+    ps[PS_NC] = nc;
+  }
+  __syncthreads();                          // the lists are complete, smem_d is free
 
   // A free set of at most kSmallF rows is solved in row space (its
-  // gamma Sigma_FF is at most 64 x 64: one wave factors it); a larger one
-  // through the factor space below.
+  // gamma Sigma_FF is at most 64 x 64); a larger one through the factor space
+  // below.
   const bool small = nF <= kSmallF;
-  double* Xs = nullptr;                   // small path: H^-1 [C | rhs] (LDS)
+  const SmallLds L = small_lds(smem_d, k, ncol);
   int i_mine = 0;                         // small path: the thread's free row, its w0
   float w0_mine = 0.f;
   if (small) {
-    Xs = small_free_solve(A, a, nF, flist, code, ps, nc, ncol, cap_on, gam, lbf, ubf, kap,
-                          phi, wk, smem_d, shd, hd, Sd, i_mine, w0_mine);
+    small_free_solve(A, a, nF, flist, code, ps, nc, ncol, cap_on, gam, lbf, ubf, kap, phi, W.fy, L,
+                     shd, hd, Sd, i_mine, w0_mine);
   } else {
-  // ---- Kf = diag(1/f) + sum_F b b^T / d  (lower triangle, LDS) -----------
-  // one 4 x 4 register tile of the lower triangle per thread; staged rows
-  // are zero-padded to a multiple of 4 columns, 1/d_i follows them
-  for (int e = tid; e < k * k; e += kPT) Kf[e] = 0.0;
-  const int kt = (k + 3) >> 2;
-  const int SR = 16, SS = 4 * kt + 4;
+  // ---- one pass over the free rows, SR staged at a time: Kf = diag(1/f) +
+  // sum_F b b^T / d (lower triangle), Waug = sum_F b V^T / d and CV = sum_F
+  // V V^T / d with V_i = [1, constraint rows (active order), sgn_i (cap),
+  // rhs_i], rhs_i = mu_i - slope_i - gamma b_i . F yX.  A 4 x 4 register tile a
+  // thread: the first ntile threads on Kf, the next on X^T D^-1 V, X = [b | V].
+  const int ld = kf_ld(k), SR = stage_rows(k, G), SS = stage_stride(k, ncol);
+  double* stg = Kf + k * ld;                // [SR][SS], 1 / d_i at index SS - 4
+  const int kx = k + ncol, xt = (kx + 3) >> 2, vt = (ncol + 3) >> 2;
+  double sgn_w0 = 0.0;
   {
-    double acc[16];
-#pragma unroll
-    for (int c = 0; c < 16; ++c) acc[c] = 0.0;
+    const int kt = (k + 3) >> 2;
     const int ntile = kt * (kt + 1) / 2;
-    const bool own = tid < ntile;
+    const bool own_k = tid < ntile;
+    // Waug / CV tiles: from the other end of the workgroup
+    const int t2 = kPT - 1 - tid;
+    const bool own_v = !own_k && t2 < xt * vt;
     int tj = 0, tl = 0;
-    if (own) {
+    if (own_k) {
       int j = (int)((sqrt(8.0 * tid + 1.0) - 1.0) * 0.5);
       while ((j + 1) * (j + 2) / 2 <= tid) ++j;
       while (j * (j + 1) / 2 > tid) --j;
       tj = j;
       tl = tid - j * (j + 1) / 2;
+    } else if (own_v) {
+      tj = t2 / vt;
+      tl = t2 % vt;
     }
-    for (int f0 = 0; f0 < nF; f0 += SR) {
-      const int rows = min(SR, nF - f0);
-      __syncthreads();
-      for (int e = tid; e < rows * 4 * kt; e += kPT) {
-        const int rr = e / (4 * kt), j = e % (4 * kt);
-        const int i = flist[f0 + rr];
-        stg[rr * SS + j] = (j < k) ? (double)A.Bt[(size_t)i * A.kp + j] : 0.0;
+    // (both sets fit one workgroup up to ntile + xt vt <= kPT; wider systems
+    // take their Waug / CV tiles in further rounds below)
+    const bool fits = ntile + xt * vt <= kPT;
+    const int rounds = fits ? 1 : 1 + (xt * vt + kPT - 1) / kPT;
+    for (int rd = 0; rd < rounds; ++rd) {
+      const bool do_k = rd == 0 && own_k;
+      bool do_v = fits && own_v;
+      if (rd > 0) {
+        const int t3 = (rd - 1) * kPT + tid;
+        do_v = t3 < xt * vt;
+        tj = do_v ? t3 / vt : 0;
+        tl = do_v ? t3 % vt : 0;
       }
-      for (int rr = tid; rr < rows; rr += kPT) stg[rr * SS + 4 * kt] = 1.0 / (double)A.d[flist[f0 + rr]];
-      __syncthreads();
-      if (own) {
-        for (int rr = 0; rr < rows; ++rr) {
-          const double* b = stg + rr * SS;
-          const double id = b[4 * kt];
-          double bj[4], bl[4];
+      double acc[16];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) { bj[q] = b[4 * tj + q] * id; bl[q] = b[4 * tl + q]; }
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[q * 4 + r] += bj[q] * bl[r];
+      for (int c = 0; c < 16; ++c) acc[c] = 0.0;
+      for (int f0 = 0; f0 < nF; f0 += SR) {
+        const int rows = min(SR, nF - f0);
+        __syncthreads();
+        // the row's own data, while its loadings are staged
+        RowData r;
+        int i = 0, cd = 0;
+        double mu_r = 0.0, d_r = 1.0;
+        int grp = 0;
+        if (tid < rows) {
+          i = flist[f0 + tid];
+          cd = code[i];
+          mu_r = mu_at(A, (size_t)a * n + i);
+          d_r = (double)A.d[i];
+          if (A.Gl) grp = A.group[i];
+          r = row_data(A, a, i, lbf, ubf);
         }
-      }
-    }
-    if (own) {
+        for (int e = tid; e < rows * k; e += kPT) {
+          const int rr = e / k, j = e % k;
+          stg[rr * SS + j] = (double)A.Bt[(size_t)flist[f0 + rr] * A.kp + j];
+        }
+        __syncthreads();
+        if (tid < rows) {
+          Geom g;
+          make_geom(g, kap, phi, r);
+          double slope, sgn;
+          piece_slope(g, cd >> 1, slope, sgn);
+          double* x = stg + tid * SS;
+          double cross = 0.0;
+          for (int j = 0; j < k; ++j) cross += x[j] * W.fy[j];
+          double* v = x + k;
+          v[0] = 1.0;
+          int col = 1;
+          for (int gg = 0; gg < G; ++gg) {
+            if (!band_active(ps, gg)) continue;
+            v[col++] = row_coef_g(A, i, grp, gg);
+          }
+          if (cap_on) v[col++] = sgn;
+          v[col] = mu_r - slope - gam * cross;
+          for (int q = kx; q < 4 * xt; ++q) x[q] = 0.0;
+          x[SS - 4] = 1.0 / d_r;
+          if (rd == 0) sgn_w0 += sgn * (double)r.w0;
+        }
+        __syncthreads();
+        if (do_k || do_v) {
+          const double* bj = stg + 4 * tj;
+          const double* bl = stg + (do_k ? 4 * tl : k + 4 * tl);
+          const int lim = do_k ? 4 : ncol - 4 * tl;           // columns past it are not stored
+          for (int rr = 0; rr < rows; ++rr) {
+            const double id = stg[rr * SS + SS - 4];
+            double xj[4], xl[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
+            for (int q = 0; q < 4; ++q) {
+              xj[q] = bj[rr * SS + q] * id;
+              xl[q] = q < lim ? bl[rr * SS + q] : 0.0;
+            }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int j = 4 * tj + q, l = 4 * tl + r;
-          if (j < k && l <= j) {
-            double v = acc[q * 4 + r];
-            if (j == l) v += 1.0 / (double)A.f[j];
-            Kf[j * k + l] = v;
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+              for (int s = 0; s < 4; ++s) acc[q * 4 + s] += xj[q] * xl[s];
           }
         }
-    }
-  }
-  __syncthreads();
-
-  // ---- Waug = sum_F b V^T / d,  CV = sum_F V V^T / d  ---------------------
-  // V_i = [1, band indicators (active order), sgn_i (cap), rhs_i],
-  // rhs_i = mu_i - slope_i - gamma b_i . F yX.  With X_i = [b_i | V_i] both
-  // blocks are X^T D^-1 V: one 4 x 4 register tile per thread.
-  double sgn_w0 = 0.0;
-  {
-    const int kx = k + ncol;
-    const int xt = (kx + 3) >> 2, vt = (ncol + 3) >> 2;
-    const int CS = 4 * xt + 4;                // 1/d_i at index 4 xt
-    const bool own = tid < xt * vt;
-    const int tj = own ? tid / vt : 0, tl = own ? tid % vt : 0;
-    double acc[16];
-#pragma unroll
-    for (int c = 0; c < 16; ++c) acc[c] = 0.0;
-    for (int f0 = 0; f0 < nF; f0 += SR) {
-      const int rows = min(SR, nF - f0);
-      __syncthreads();
-      for (int e = tid; e < rows * 4 * xt; e += kPT) {
-        const int rr = e / (4 * xt), j = e % (4 * xt);
-        const int i = flist[f0 + rr];
-        stg[rr * CS + j] = (j < k) ? (double)A.Bt[(size_t)i * A.kp + j] : 0.0;
       }
-      __syncthreads();
-      if (tid < rows) {
-        const int rr = tid;
-        const int i = flist[f0 + rr];
-        RowData r = row_data(A, a, i, lbf, ubf);
-        Geom g;
-        make_geom(g, kap, phi, r);
-        double slope, sgn;
-        piece_slope(g, code[i] >> 1, slope, sgn);
-        double* x = stg + rr * CS;
-        double cross = 0.0;
-        for (int j = 0; j < k; ++j) cross += x[j] * wk.Fy[j];
-        double* v = x + k;
-        v[0] = 1.0;
-        int col = 1;
-        for (int gg = 0; gg < G; ++gg) {
-          if (!band_active(ps, gg)) continue;
-          v[col++] = row_coef(A, i, gg);
-        }
-        if (cap_on) v[col++] = sgn;
-        v[col] = mu_at(A, (size_t)a * n + i) - slope - gam * cross;
-        x[4 * xt] = 1.0 / (double)A.d[i];
-        sgn_w0 += sgn * (double)r.w0;
-      }
-      __syncthreads();
-      if (own) {
-        for (int rr = 0; rr < rows; ++rr) {
-          const double* x = stg + rr * CS;
-          const double id = x[4 * xt];
-          double xl[4], vr[4];
+      if (do_k) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            xl[q] = x[4 * tj + q] * id;
-            vr[q] = (4 * tl + q < ncol) ? x[k + 4 * tl + q] : 0.0;
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const int j = 4 * tj + q, l = 4 * tl + s;
+            if (j < k && l <= j) {
+              double v = acc[q * 4 + s];
+              if (j == l) v += 1.0 / (double)A.f[j];
+              Kf[j * ld + l] = v;
+            }
           }
+      }
+      if (do_v) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[q * 4 + r] += xl[q] * vr[r];
-        }
+          for (int s = 0; s < 4; ++s) {
+            const int j = 4 * tj + q, l = 4 * tl + s;
+            if (j >= kx || l >= ncol) continue;
+            if (j < k) {
+              wk.Waug[j * ncol + l] = acc[q * 4 + s];
+              wk.Y[j * ncol + l] = acc[q * 4 + s];
+            } else {
+              wk.CV[(j - k) * ncol + l] = acc[q * 4 + s];
+            }
+          }
       }
     }
-    if (own) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int j = 4 * tj + q, l = 4 * tl + r;
-          if (j >= kx || l >= ncol) continue;
-          if (j < k) wk.Waug[j * ncol + l] = acc[q * 4 + r];
-          else wk.CV[(j - k) * ncol + l] = acc[q * 4 + r];
-        }
-    }
   }
-  sgn_w0 = bsum<double>(sgn_w0, shd);
+  sgn_w0 = bsum(sgn_w0, shd);
   if (tid == 0 && cap_on) hd[nc - 1] += sgn_w0;
   __syncthreads();
-
-  // ---- Cholesky of Kf (lower, in LDS) -------------------------------------
-  for (int j = 0; j < k; ++j) {
-    // every thread takes the pivot itself; thread 0 stores it after the
-    // barrier that ends this step's reads of the unscaled diagonal
-    const double djj = sqrt(fmax(Kf[j * k + j], 1e-300));
-    for (int i = j + 1 + tid; i < k; i += kPT) Kf[i * k + j] /= djj;
-    __syncthreads();
-    if (tid == 0) Kf[j * k + j] = djj;
-    const int m = k - j - 1;
-    for (int e = tid; e < m * m; e += kPT) {
-      const int i = j + 1 + e / m, l = j + 1 + e % m;
-      if (l <= i) Kf[i * k + l] -= Kf[i * k + j] * Kf[l * k + j];
-    }
-    __syncthreads();
-  }
-  // ---- Y = Kf^-1 Waug -------------------------------------------------------
-  for (int e = tid; e < k * ncol; e += kPT) wk.Y[e] = wk.Waug[e];
-  __syncthreads();
-  chol_solve_cols(Kf, k, wk.Y, ncol);
+  // ---- Y = Kf^-1 Waug
+  chol_factor(Kf, k, ld, s_inv);
+  chol_solve_cols(Kf, k, ld, s_inv, wk.Y, ncol);
   // ---- Schur system on the constraint columns ------------------------------
   // gamma * C H^-1 V = CV[C, V] - Waug[:, C]^T Y[:, V]
   for (int e = tid; e < nc * ncol; e += kPT) {
     const int p = e / ncol, q = e % ncol;
     double s = wk.CV[p * ncol + q];
+#pragma unroll 8
     for (int j = 0; j < k; ++j) s -= wk.Waug[j * ncol + p] * wk.Y[j * ncol + q];
     Sd[p * ncol + q] = s / gam;
   }
   }                                       // factor-space path
+  // eta0: multipliers of the previous pattern (first pattern: ADMM's):
+  // -nu, band duals, lam_cap
+  if (sl) {
+    if (tid < G && band_active(ps, tid)) s_e0[col_of(tid)] = W.mult[2 + tid];
+    if (tid == 0) {
+      s_e0[0] = -W.mult[0];
+      if (cap_on) s_e0[nc - 1] = fmax(W.mult[1], 0.0);
+    }
+  }
   __syncthreads();
-  if (tid == 0) {
-    // eta0: multipliers of the previous pattern (first pattern: ADMM's):
-    // -nu, band duals, lam_cap
-    const double* m0 = s_m0;
-    double e0l[kMaxG + 3];
-    double* e0 = sl ? s_e0 : e0l;
-    e0[0] = -m0[0];
-    int col = 1;
-    for (int g = 0; g < G; ++g) {
-      if (!band_active(ps, g)) continue;
-      e0[col++] = m0[2 + g];
+  if (sl) {
+    if (tid < 64) {
+      const int nd = schur_solve_wave(nc, ncol, smem_d, s_h, s_e0, smem_d + nc * ncol, s_eta,
+                                      wk.nul, G + 3);
+      if (tid == 0) ps[PS_ND] = nd;
     }
-    if (cap_on) e0[col++] = fmax(m0[1], 0.0);
-    int nd;
-    if (sl) {
-      nd = schur_solve(nc, ncol, s_S, s_h, s_e0, s_Sm, s_eta, s_perm, s_x, s_v, wk.nul, G + 3);
-    } else {
-      int perm[kMaxG + 3];
-      double x[kMaxG + 3], v[kMaxG + 3];
-      nd = schur_solve(nc, ncol, wk.S, wk.h, e0l, wk.CV, wk.eta, perm, x, v, wk.nul, G + 3);
-    }
-    ps[PS_ND] = nd;
+    __syncthreads();
     // multipliers in the build's convention
-    const double* rr = sl ? s_eta : wk.eta;
-    double* mult = A.mult + (size_t)a * (2 + G);
-    mult[0] = -rr[0];
-    col = 1;
-    for (int g = 0; g < G; ++g) {
-      if (band_active(ps, g)) mult[2 + g] = rr[col++];
-      else mult[2 + g] = 0.0;
+    if (tid < G) W.mult[2 + tid] = band_active(ps, tid) ? s_eta[col_of(tid)] : 0.0;
+    if (tid == 0) {
+      W.mult[0] = -s_eta[0];
+      W.mult[1] = cap_on ? s_eta[nc - 1] : 0.0;
     }
-    mult[1] = cap_on ? rr[col] : 0.0;
+  } else if (tid == 0) {
+    double e0[kMaxG + 3];
+    e0[0] = -W.mult[0];
+    int col = 1;
+    for (int g = 0; g < G; ++g)
+      if (band_active(ps, g)) e0[col++] = W.mult[2 + g];
+    if (cap_on) e0[col++] = fmax(W.mult[1], 0.0);
+    int perm[kMaxG + 3];
+    double x[kMaxG + 3], v[kMaxG + 3];
+    ps[PS_ND] = schur_solve(nc, ncol, wk.S, wk.h, e0, wk.CV, wk.eta, perm, x, v, wk.nul, G + 3);
+    W.mult[0] = -wk.eta[0];
+    col = 1;
+    for (int g = 0; g < G; ++g) W.mult[2 + g] = band_active(ps, g) ? wk.eta[col++] : 0.0;
+    W.mult[1] = cap_on ? wk.eta[col] : 0.0;
   }
   __syncthreads();
   const double* etav = sl ? s_eta : wk.eta;
@@ -1207,10 +1361,11 @@ __global__ __launch_bounds__(kPT) void polish_solve_kernel(PolishArgs A) {
     // w_F = H^-1 (rhs - C^T eta) = X[:, rhs] - X[:, C] eta
     if (tid < nF) {
       const int t = tid;
-      double v = Xs[t * ncol + nc];
-      for (int p = 0; p < nc; ++p) v -= Xs[t * ncol + p] * etav[p];
+      double v = L.Xs[t * ncol + nc];
+      for (int p = 0; p < nc; ++p) v -= L.Xs[t * ncol + p] * etav[p];
       const int i = i_mine;
       w[i] = v;
+      s_wf[t] = v;
       turn_f += fabs(v - (double)w0_mine);
     }
   } else {
@@ -1221,48 +1376,91 @@ __global__ __launch_bounds__(kPT) void polish_solve_kernel(PolishArgs A) {
     wk.sol[j] = s;
   }
   __syncthreads();
-  // ---- free rows: w_i = (rhs_i - C_i^T eta - b_i . sol) / (gamma d_i) ----
-  for (int t = tid; t < nF; t += kPT) {
+  // ---- free rows: w_i = (rhs_i - C_i^T eta - b_i . sol) / (gamma d_i), 16
+  // threads a row for the products
+  for (int t0 = 0; t0 < nF; t0 += kPT / 16) {
+    const int t = min(t0 + (tid >> 4), nF - 1), q = tid & 15;
     const int i = flist[t];
-    RowData r = row_data(A, a, i, lbf, ubf);
-    Geom g;
-    make_geom(g, kap, phi, r);
-    double slope, sgn;
-    piece_slope(g, code[i] >> 1, slope, sgn);
     double cross = 0.0, bs = 0.0;
-    for (int j = 0; j < k; ++j) {
+    for (int j = q; j < k; j += 16) {
       const double b = (double)A.Bt[(size_t)i * A.kp + j];
-      cross += b * wk.Fy[j];
+      cross += b * W.fy[j];
       bs += b * wk.sol[j];
     }
-    const double rhs = mu_at(A, (size_t)a * n + i) - slope - gam * cross;
-    double ct = etav[0];
-    int col = 1;
-    for (int gg = 0; gg < G; ++gg) {
-      if (!band_active(ps, gg)) continue;
-      ct += row_coef(A, i, gg) * etav[col];
-      ++col;
+#pragma unroll
+    for (int o = 8; o >= 1; o >>= 1) {
+      cross += __shfl_xor(cross, o, 16);
+      bs += __shfl_xor(bs, o, 16);
     }
-    if (cap_on) ct += sgn * etav[col];
-    const double wi = (rhs - ct - bs) / (gam * (double)A.d[i]);
-    w[i] = wi;
-    turn_f += fabs(wi - (double)r.w0);
+    if (q == 0 && t0 + (tid >> 4) < nF) {
+      RowData r = row_data(A, a, i, lbf, ubf);
+      Geom g;
+      make_geom(g, kap, phi, r);
+      double slope, sgn;
+      piece_slope(g, code[i] >> 1, slope, sgn);
+      const double rhs = mu_at(A, (size_t)a * n + i) - slope - gam * cross;
+      double ct = etav[0];
+      int col = 1;
+      const int grp = A.Gl ? A.group[i] : 0;
+      for (int gg = 0; gg < G; ++gg) {
+        if (!band_active(ps, gg)) continue;
+        ct += row_coef_g(A, i, grp, gg) * etav[col];
+        ++col;
+      }
+      if (cap_on) ct += sgn * etav[col];
+      const double wi = (rhs - ct - bs) / (gam * (double)A.d[i]);
+      w[i] = wi;
+      turn_f += fabs(wi - (double)r.w0);
+    }
   }
   }                                       // factor-space path
   // turnover of the polished w: the fixed rows' (from the row blocks) plus
   // the free rows'
-  turn_f = bsum<double>(turn_f, shd);
-  if (tid == 0) wk.misc[3] = sturn + turn_f;
+  turn_f = bsum(turn_f, shd);
   // ---- y = F B^T w and the row sums of the polished w (nonzero rows), for
   // the gradient base and the certification: the fixed rows' parts from
   // above plus the free rows' --------------------------------------------
   __syncthreads();
-  {
+  if (small) {
+    if (tid < kg) {
+      double s = 0.0;
+      for (int r = 0; r < nF; ++r) s += (double)L.Bs[r * kg + tid] * s_wf[r];
+      if (tid < k) W.yF[tid] = (X.yx + s) * X.f;
+      else W.gsum[tid - k] = W.gfix[tid - k] + s;
+    }
+  } else {
     double ys = 0.0, gs = 0.0;
     list_sums(A, flist, n, nF, 0, w, Kf, ys, gs);     // the solve is done with Kf
-    if (tid < k) wk.yF[tid] = (yx_mine + ys) * f_mine;
-    if (tid < G) wk.gsum[tid] = s_gfix[tid] + gs;
+    if (tid < k) W.yF[tid] = (X.yx + ys) * X.f;
+    if (tid < G) W.gsum[tid] = W.gfix[tid] + gs;
   }
+  return X.sturn + turn_f;
+}
+
+__global__ __launch_bounds__(kPT) void polish_solve_kernel(PolishArgs A) {
+  extern __shared__ double smem_d[];
+  __shared__ AcctLds W;
+  __shared__ int s_same;
+  const int slot = blockIdx.x;
+  if (slot >= *A.m_act) return;
+  const int a = A.act[slot], tid = threadIdx.x, k = A.k, G = A.G;
+  int* ps = A.pstate + (size_t)a * kPStateStride;
+  if (!A.first_round && (ps[PS_DONE] || ps[PS_STALL])) return;
+  const float* par = A.par + (size_t)a * kNPar;
+  double* mult = A.mult + (size_t)a * (2 + G);
+  if (A.first_round) begin_pass(A, a, par, ps, W.mult);
+  else
+    for (int e = tid; e < 2 + G; e += kPT) W.mult[e] = mult[e];
+  const PatternSums X = gather_pattern(A, a, smem_d, W);
+  if (gated(A, A.first_round, ps, X, &s_same)) return;
+  const double turn = solve_pattern(A, a, par, ps, X, smem_d, W);
+  // for the passes after it (a thread's own entries of yF and gsum)
+  const Wk wk = wk_of(A, a);
+  if (tid < k) wk.yF[tid] = W.yF[tid];
+  __syncthreads();
+  if (tid < G) wk.gsum[tid] = W.gsum[tid];
+  if (tid < 2 + G) mult[tid] = W.mult[tid];
+  if (tid == 0) wk.misc[3] = turn;
 }
 
 // ---------------------------------------------------------------------------
@@ -2066,23 +2264,22 @@ __global__ __launch_bounds__(64) void polish_decide_kernel(PolishArgs A, fqp_res
 }
 
 static size_t polish_smem(int k, int G, int n_sb) {
-  // Kf (k^2 doubles) and a staging region; the Kf region also holds the
-  // list sums' per-wave partials (16 (k + G) doubles) and, before Kf is
-  // built, the row blocks' list offsets (2 (n_sb + 1) ints)
-  const size_t a = sizeof(double) * ((size_t)k * k);
-  size_t b = sizeof(double) * (kPT / 64) * (size_t)(k + G);
-  const size_t c = sizeof(int) * 2 * ((size_t)n_sb + 1);
-  if (c > b) b = c;
-  // staging: 16 rows of [b | V | pad | 1/d]
-  const size_t rest = sizeof(double) * 16 * (size_t)(4 * ((k + kMaxG + 3 + 3) / 4) + 4);
-  const size_t factor = (a > b ? a : b) + rest;
-  // row-space path: H, V, X, f, F yX, b.F yX (doubles), the free rows of B (floats)
+  // factor-space path: Kf and the staged rows (then the list sums' per-wave
+  // partials over Kf: 16 (k + G) doubles)
+  const size_t stage = sizeof(double) * (size_t)stage_rows(k, G) * stage_stride(k, G + 3);
+  const size_t lists = sizeof(double) * (kPT / 64) * (size_t)(k + G);
+  size_t factor = sizeof(double) * (size_t)k * kf_ld(k) + stage;
+  if (lists > factor) factor = lists;
+  // row-space path: H, V, X, f, F yX, b.F yX, 1 / L_jj (doubles), the free
+  // rows of B~ (floats)
   const size_t ncol = (size_t)G + 3;
-  const size_t rows = sizeof(double) * (kSmallF * kSmallF + 2 * kSmallF * ncol + 2 * (size_t)k +
-                                        kSmallF) +
-                      sizeof(float) * kSmallF * (size_t)k;
+  const size_t rows = sizeof(double) * (kSmallF * kHld + 2 * kSmallF * ncol + 2 * (size_t)k +
+                                        2 * kSmallF) +
+                      sizeof(float) * kSmallF * (size_t)(k + G);
+  // the gather: a double a thread, then the row blocks' list offsets
+  const size_t gather = sizeof(double) * kPT + sizeof(int) * 2 * ((size_t)n_sb + 1);
   const size_t both = factor > rows ? factor : rows;
-  return both > c ? both : c;
+  return both > gather ? both : gather;
 }
 
 hipError_t launch_polish_solve(const PolishArgs& A, hipStream_t st) {

@@ -67,11 +67,6 @@ __device__ __forceinline__ double ror_d(double x) {
   const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x120 + N, 0xf, 0xf, true);
   return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
 }
-__device__ __forceinline__ double lane_d(double x, int l) {
-  const long long b = __builtin_bit_cast(long long, x);
-  const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
-}
 __device__ __forceinline__ double wave_sum(double x) {
   x += ror_d<1>(x);
   x += ror_d<2>(x);

@@ -1,0 +1,41 @@
+"""GPU tests of the active-set refinement at the edges of its solves: the
+constraint system in one wave's lanes and above them, panels of the
+factorisation, free sets on either side of the row-space solve."""
+import pytest
+
+from workloads import make_config
+from _gpu_helpers import run_gpu, check_account
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # narrow bands bind nearly all of them: 1 + groups constraint columns
+    # against the 44 one wave solves; factor counts around the panels of 8
+    # and the 64 lanes
+    dict(N=700, M=3, k=7, groups=42, band_halfwidth=1e-5, ub=0.02),
+    dict(N=700, M=3, k=8, groups=43, band_halfwidth=1e-5, ub=0.02),
+    dict(N=700, M=3, k=9, groups=44, band_halfwidth=1e-5, ub=0.02),
+    dict(N=900, M=2, k=65, groups=64, band_halfwidth=1e-5, ub=0.02),
+    dict(N=900, M=2, k=100, groups=63, band_halfwidth=1e-5, ub=0.02),
+    # no trade cost and loose boxes: hundreds of free rows (factor space);
+    # factor counts at the panel and stride edges
+    dict(N=600, M=2, k=16, groups=5, tax=False, kappa=0.0,
+         gamma=1000.0, ub=0.05),
+    dict(N=600, M=2, k=64, groups=5, tax=False, kappa=0.0,
+         gamma=1000.0, ub=0.05),
+    dict(N=600, M=2, k=101, groups=5, tax=False, kappa=0.0,
+         gamma=1000.0, ub=0.05),
+    dict(N=600, M=2, k=127, groups=0, band_halfwidth=None, tax=False, kappa=0.0,
+         gamma=1000.0, ub=0.05),
+]
+
+
+@pytest.mark.parametrize("over", CASES)
+def test_against_the_oracle(over):
+    uni, book = make_config("c5", 43, held=(60, 90), **over)
+    print(f"case {over}", flush=True)
+    host, _ = run_gpu(uni, book, rho=10.0, max_iter=4000)
+    # (the accounts the oracle itself solves to 1e-11 and the iteration settles
+    # within max_iter)
+    for a in (1,) if over["groups"] == 44 else (0, 1):
+        check_account(uni, book, a, host)
