@@ -113,6 +113,18 @@ __device__ __forceinline__ double div_by(double a, double b, double ib) {
   return fma(fma(-b, q, a), ib, q);
 }
 
+// sqrt(a) and its reciprocal (a normal, positive) from one estimate, refined
+// to the last place: a third of the chain of a root and a division
+__device__ __forceinline__ void root_recip(double a, double& d, double& id) {
+  double y = __builtin_amdgcn_rsq(a);
+  y = fma(0.5 * y, fma(-a * y, y, 1.0), y);
+  y = fma(0.5 * y, fma(-a * y, y, 1.0), y);
+  double s = a * y;
+  s = fma(0.5 * y, fma(-s, s, a), s);
+  d = s;
+  id = fma(y, fma(-s, y, 1.0), y);
+}
+
 // Cholesky factor of the k x k matrix L (lower triangle, LDS, k <= 128,
 // leading dimension ld) by the whole workgroup, in panels of 8 columns: wave
 // 0 factors a panel with its rows in registers (pivots and multipliers pass
@@ -136,14 +148,8 @@ __device__ inline void chol_factor(double* L, int k, int ld, double* inv) {
 #pragma unroll
       for (int c = 0; c < 8; ++c) {
         if (c >= nb) break;                                   // uniform
-        // the root and its reciprocal from one estimate, refined to the last place
-        const double a = fmax(lane_d(r0[c], c), 1e-300);
-        double id = __builtin_amdgcn_rsq(a);
-        id = fma(0.5 * id, fma(-a * id, id, 1.0), id);
-        id = fma(0.5 * id, fma(-a * id, id, 1.0), id);
-        double d = a * id;
-        d = fma(0.5 * id, fma(-d, d, a), d);
-        id = fma(id, fma(-d, id, 1.0), id);
+        double d, id;
+        root_recip(fmax(lane_d(r0[c], c), 1e-300), d, id);
         r0[c] = tid == c ? d : div_by(r0[c], d, id);
         r1[c] = div_by(r1[c], d, id);
         if (tid == c) inv[p0 + c] = id;

@@ -52,7 +52,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // exactly as the one-hot band rows do)
 // ---------------------------------------------------------------------------
 __global__ void build_bt_kernel(int n, int k, int G, int H, int kp, const float* B,
-                                const int32_t* group, const float* half, float* Bt) {
+                                const int32_t* group, const float* half, float* Bt, float* Bq) {
   size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   size_t total = (size_t)n * kp;
   if (e >= total) return;
@@ -63,6 +63,8 @@ __global__ void build_bt_kernel(int n, int k, int G, int H, int kp, const float*
   else if (j < k + G + H) v = half[(size_t)(j - k - G) * n + i];
   else if (j == k + G + H) v = 1.f;
   Bt[e] = v;
+  // the first k columns by fours, rows consecutive within a group of four
+  if (Bq && j < ((k + 3) & ~3)) Bq[((size_t)(j >> 2) * n + i) * 4 + (j & 3)] = v;
 }
 
 // partial Gram  sum_i B~_ij B~_il / Delta_i  over a chunk of rows, for
@@ -1482,10 +1484,11 @@ hipError_t launch_split_bt(int n, int npad, int kp, const float* Bt, uint16_t* b
 }
 
 hipError_t launch_build_bt(int n, int k, int G, int H, int kp, const float* B,
-                           const int32_t* group, const float* half, float* Bt, hipStream_t st) {
+                           const int32_t* group, const float* half, float* Bt, float* Bq,
+                           hipStream_t st) {
   size_t total = (size_t)n * kp;
   hipLaunchKernelGGL(build_bt_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                     n, k, G, H, kp, B, group, half, Bt);
+                     n, k, G, H, kp, B, group, half, Bt, Bq);
   return hipGetLastError();
 }
 

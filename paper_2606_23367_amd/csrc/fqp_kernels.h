@@ -107,8 +107,10 @@ bool cap_resident_fits(int n, int max_held);
 hipError_t launch_prox(const IterArgs& A, int m_total, bool resident, int zmode,
                        hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 hipError_t launch_ksolve(const KArgs& A, int m_total, hipStream_t st);
+// Bq (or null): [ceil(k / 4)][n] float4, the first k columns by fours
 hipError_t launch_build_bt(int n, int k, int G, int H, int kp, const float* B,
-                           const int32_t* group, const float* half, float* Bt, hipStream_t st);
+                           const int32_t* group, const float* half, float* Bt, float* Bq,
+                           hipStream_t st);
 hipError_t launch_gram(int n, int kp, int kg, int nparts, int rows_per_blk, const float* Bt,
                        const float* d, double gamma, double rho, double* part, hipStream_t st);
 hipError_t launch_kfactor(int k, int G, int kp, int nparts, const double* part, const float* f,
@@ -253,6 +255,7 @@ struct PolishArgs {
   const float* f;            // [k]
   const float* d;            // [n]
   const int32_t* group;      // [n] or null
+  const float* half;         // [G - Gl][n] halfspace rows or null
   const float* mu;           // [m][n]
   const float* z;            // [m][n]  ADMM iterate
   const uint32_t* elig;
@@ -292,6 +295,8 @@ struct PolishArgs {
   double* spart;             // [m][n_sb][4] null-direction sweep partials
   double* cpart;             // [m][n_sb][8] diagnostic partials
 };
+// whether one workgroup per account runs a pass's rounds (launch_polish_pass)
+bool polish_pass_fits(int n, int k, int G);
 hipError_t launch_polish_solve(const PolishArgs& A, hipStream_t st);
 // pact / pm_act: the accounts of act / m_act that neither certified nor stalled;
 // host_count (pinned host memory, device address, or null) also receives the count

@@ -66,22 +66,11 @@ struct Geom {
   __device__ __forceinline__ double pt(int i) const {
     return i <= 0 ? p0 : i == 1 ? p1 : i == 2 ? p2 : i == 3 ? p3 : i == 4 ? p4 : p5;
   }
-  __device__ __forceinline__ float ptf(int i) const {
-    return i <= 0 ? f0 : i == 1 ? f1 : i == 2 ? f2 : i == 3 ? f3 : i == 4 ? f4 : f5;
-  }
   __device__ __forceinline__ double kink(int i) const {
     return i <= 0 ? k0 : i == 1 ? k1 : i == 2 ? k2 : k3;
   }
   __device__ __forceinline__ double ks(int i) const {
     return i <= 0 ? s0 : i == 1 ? s1 : i == 2 ? s2 : i == 3 ? s3 : s4;
-  }
-  // point i <- (x, xf) when `on` (i in 1..5)
-  __device__ __forceinline__ void put(int i, bool on, double x, float xf) {
-    p1 = (on && i == 1) ? x : p1; f1 = (on && i == 1) ? xf : f1;
-    p2 = (on && i == 2) ? x : p2; f2 = (on && i == 2) ? xf : f2;
-    p3 = (on && i == 3) ? x : p3; f3 = (on && i == 3) ? xf : f3;
-    p4 = (on && i == 4) ? x : p4; f4 = (on && i == 4) ? xf : f4;
-    p5 = (on && i == 5) ? x : p5; f5 = (on && i == 5) ? xf : f5;
   }
 };
 
@@ -185,21 +174,27 @@ __device__ __forceinline__ void make_geom(Geom& g, float kap, bool phi, const Ro
   g.s2 = tx ? -(kd + r.s1) : 0.0;
   g.s3 = tx ? -(kd + r.s0) : 0.0;
   g.s4 = tx ? kd : 0.0;
-  // points: lb, the kinks strictly inside (lb, ub) (ascending), ub
-  g.np = 1;
+  // points: lb, the kinks strictly inside (lb, ub), ub.  The kinks ascend, so
+  // those inside are cnt of them after the first s: the list shifted by s
+  // (two selects a slot), ub behind its cnt entries.  (Placing one kink after
+  // another through the slots took three times the instructions, and the row
+  // passes are bound by their issue.)
+  const bool e0 = g.nk > 0, e1 = g.nk > 1, e2 = g.nk > 2, e3 = g.nk > 3;
+  const bool a0 = g.k0 > lb, a1 = g.k1 > lb, a2 = g.k2 > lb, a3 = g.k3 > lb;
+  const int s = (e0 && !a0 ? 1 : 0) + (e1 && !a1 ? 1 : 0) + (e2 && !a2 ? 1 : 0) +
+                (e3 && !a3 ? 1 : 0);
+  const int cnt = (e0 && a0 && g.k0 < ub ? 1 : 0) + (e1 && a1 && g.k1 < ub ? 1 : 0) +
+                  (e2 && a2 && g.k2 < ub ? 1 : 0) + (e3 && a3 && g.k3 < ub ? 1 : 0);
+  const bool s1 = s & 1, s2 = s & 2;
+  const double t0 = s1 ? g.k1 : g.k0, t1 = s1 ? g.k2 : g.k1, t2 = s1 ? g.k3 : g.k2;
+  const float h0 = s1 ? kf1 : kf0, h1 = s1 ? kf2 : kf1, h2 = s1 ? kf3 : kf2;
   g.p0 = lb; g.f0 = r.lb;
-  g.p1 = g.p2 = g.p3 = g.p4 = g.p5 = 0.0;
-  g.f1 = g.f2 = g.f3 = g.f4 = g.f5 = 0.f;
-  const bool in0 = g.nk > 0 && g.k0 > lb && g.k0 < ub;
-  g.put(g.np, in0, g.k0, kf0); g.np += in0 ? 1 : 0;
-  const bool in1 = g.nk > 1 && g.k1 > lb && g.k1 < ub;
-  g.put(g.np, in1, g.k1, kf1); g.np += in1 ? 1 : 0;
-  const bool in2 = g.nk > 2 && g.k2 > lb && g.k2 < ub;
-  g.put(g.np, in2, g.k2, kf2); g.np += in2 ? 1 : 0;
-  const bool in3 = g.nk > 3 && g.k3 > lb && g.k3 < ub;
-  g.put(g.np, in3, g.k3, kf3); g.np += in3 ? 1 : 0;
-  const bool top = ub > lb;
-  g.put(g.np, top, ub, r.ub); g.np += top ? 1 : 0;
+  g.p1 = cnt > 0 ? (s2 ? t2 : t0) : ub;   g.f1 = cnt > 0 ? (s2 ? h2 : h0) : r.ub;
+  g.p2 = cnt > 1 ? (s2 ? g.k3 : t1) : ub; g.f2 = cnt > 1 ? (s2 ? kf3 : h1) : r.ub;
+  g.p3 = cnt > 2 ? t2 : ub;               g.f3 = cnt > 2 ? h2 : r.ub;
+  g.p4 = cnt > 3 ? g.k3 : ub;             g.f4 = cnt > 3 ? kf3 : r.ub;
+  g.p5 = ub;                              g.f5 = r.ub;
+  g.np = 1 + cnt + (ub > lb ? 1 : 0);
 }
 
 // number of kinks below x (the kinks ascend)
@@ -218,20 +213,16 @@ __device__ __forceinline__ void piece_slope(const Geom& g, int q, double& slope,
 // subdifferential interval of phi + lam |. - w0| + N_box at x (with snap)
 __device__ __forceinline__ void subdiff(const Geom& g, double x, double lam, double lb,
                                         double ub, double& lo, double& hi, double& snap) {
-  snap = 0.0;
   // the first kink within kSnap of x, or -1
   const int at = (g.nk > 0 && fabs(x - g.k0) <= kSnap) ? 0
                : (g.nk > 1 && fabs(x - g.k1) <= kSnap) ? 1
                : (g.nk > 2 && fabs(x - g.k2) <= kSnap) ? 2
                : (g.nk > 3 && fabs(x - g.k3) <= kSnap) ? 3 : -1;
-  if (at >= 0) {
-    lo = g.ks(at) + ((at < g.nk) ? -lam : lam);
-    hi = g.ks(at + 1) + ((at + 1 < g.nk) ? -lam : lam);
-    snap = fabs(x - g.kink(at));
-  } else {
-    const int s = kinks_below(g, x);
-    lo = hi = g.ks(s) + ((s < g.nk) ? -lam : lam);
-  }
+  // the piece below x, the piece above it
+  const int il = at >= 0 ? at : kinks_below(g, x), ih = at >= 0 ? at + 1 : il;
+  lo = g.ks(il) + ((il < g.nk) ? -lam : lam);
+  hi = g.ks(ih) + ((ih < g.nk) ? -lam : lam);
+  snap = at >= 0 ? fabs(x - g.kink(at)) : 0.0;
   if (g.nk == 0) lo = hi = 0.0;
   if (x <= lb + kSnap) { lo = -INFINITY; snap = fmax(snap, fmax(x - lb, 0.0)); }
   if (x >= ub - kSnap) { hi = INFINITY; snap = fmax(snap, fmax(ub - x, 0.0)); }
@@ -288,14 +279,6 @@ __device__ __forceinline__ bool band_active(const int* ps, int g) {
 __device__ __forceinline__ bool band_upper(const int* ps, int g) {
   return g < 32 ? ((ps[PS_BUP0] >> g) & 1) : ((ps[PS_BUP1] >> (g - 32)) & 1);
 }
-__device__ __forceinline__ void set_band(int* ps, int g, bool act, bool up) {
-  const int w = g < 32 ? 0 : 1, b = g & 31;
-  int* pa = ps + PS_BACT0 + w;
-  int* pu = ps + PS_BUP0 + w;
-  *pa = act ? (*pa | (1 << b)) : (*pa & ~(1 << b));
-  *pu = up ? (*pu | (1 << b)) : (*pu & ~(1 << b));
-}
-
 // a double from another lane of the row of 16 (a DPP pattern)
 template <int CTRL>
 __device__ __forceinline__ double dpp_d(double x) {
@@ -320,8 +303,47 @@ __device__ __forceinline__ double wave_red(double x, F f) {
   x = row_red(x, f);
   return f(f(lane_d(x, 0), lane_d(x, 16)), f(lane_d(x, 32), lane_d(x, 48)));
 }
+// x of lane l to lane `to` (a permutation of the lanes)
+__device__ __forceinline__ double push_d(double x, int to) {
+  const long long b = __builtin_bit_cast(long long, x);
+  const int lo = __builtin_amdgcn_ds_permute(4 * to, (int)b);
+  const int hi = __builtin_amdgcn_ds_permute(4 * to, (int)(b >> 32));
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
 struct SumOp { __device__ double operator()(double a, double b) const { return a + b; } };
 struct MaxOp { __device__ double operator()(double a, double b) const { return fmax(a, b); } };
+
+// Four quantities reduced at once: each exchange hands on half of what a lane
+// still carries, so four cost little more than one.  Lane l returns quantity
+// l & 3 over its row of 16.
+template <class F>
+__device__ __forceinline__ double row_red4(const double (&v)[4], F f) {
+  const int l = threadIdx.x;
+  const bool b0 = l & 1, b1 = l & 2;
+  const double x = f(b0 ? v[1] : v[0], dpp_d<0xB1>(b0 ? v[0] : v[1]));
+  const double y = f(b0 ? v[3] : v[2], dpp_d<0xB1>(b0 ? v[2] : v[3]));
+  double z = f(b1 ? y : x, dpp_d<0x4E>(b1 ? x : y));
+  z = f(z, dpp_d<0x128>(z));                // rotated by 8, by 4: the same quantity
+  return f(z, dpp_d<0x124>(z));
+}
+// ... over the workgroup, for its first wave (the others get nothing): sh
+// takes 64 doubles a wave and 4 quantities; the caller has a barrier between
+// the two halves and before sh is used again
+template <class F>
+__device__ __forceinline__ void put_red4(const double (&v)[4], double* sh, F f) {
+  const double z = row_red4(v, f);
+  if ((threadIdx.x & 12) == 0) sh[4 * (threadIdx.x >> 4) + (threadIdx.x & 3)] = z;
+}
+template <class F>
+__device__ __forceinline__ void get_red4(double (&v)[4], const double* sh, F f) {
+  // kPT / 16 = 64 partials of each quantity, one a lane
+  const double4* s4 = reinterpret_cast<const double4*>(sh) + (threadIdx.x & 63);
+  v[0] = s4->x; v[1] = s4->y; v[2] = s4->z; v[3] = s4->w;
+  const double z = row_red4(v, f);
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    v[q] = f(f(lane_d(z, q), lane_d(z, 16 + q)), f(lane_d(z, 32 + q), lane_d(z, 48 + q)));
+}
 
 // NS block sums and NM block maxima at once: one pair of barriers for all
 // (sh: (NS + NM) x nwaves doubles); every thread gets the results.  Whole
@@ -358,12 +380,20 @@ __device__ __forceinline__ double bsum(double v, double* sh) {
 // row_coef / rows_dot with the row's label already loaded (grp, unused
 // without band rows)
 __device__ __forceinline__ double row_coef_g(const PolishArgs& A, int i, int grp, int g) {
-  return g < A.Gl ? (grp == g ? 1.0 : 0.0) : (double)A.Bt[(size_t)i * A.kp + A.k + g];
+  return g < A.Gl ? (grp == g ? 1.0 : 0.0) : (double)A.half[(size_t)(g - A.Gl) * A.n + i];
 }
 __device__ __forceinline__ double rows_dot_g(const PolishArgs& A, int i, int grp,
                                             const double* x) {
   double s = A.Gl ? x[grp] : 0.0;
-  for (int g = A.Gl; g < A.G; ++g) s += (double)A.Bt[(size_t)i * A.kp + A.k + g] * x[g];
+  // the halfspace rows four at a time (loads in flight together)
+  for (int g0 = A.Gl; g0 < A.G; g0 += 4) {
+    float b[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) b[u] = A.half[(size_t)(min(g0 + u, A.G - 1) - A.Gl) * A.n + i];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (g0 + u < A.G) s += (double)b[u] * x[g0 + u];
+  }
   return s;
 }
 
@@ -377,9 +407,9 @@ __device__ __forceinline__ double rows_dot_g(const PolishArgs& A, int i, int grp
 // columns (lane, lane + 64, lane + 128).  The waves' partials meet in red
 // (nwaves x (k + G) doubles of LDS), summed in wave order.
 constexpr int kLU = 8;
-__device__ void list_sums(const PolishArgs& A, const int32_t* list, int n, int cnt, int rev,
-                          const double* w, double* red, double& ys, double& gs) {
-  const int k = A.k, G = A.G, kg = k + G, tid = threadIdx.x;
+__device__ void list_sums(const PolishArgs& A, int tid, const int32_t* list, int n, int cnt,
+                          int rev, const double* w, double* red, double& ys, double& gs) {
+  const int k = A.k, G = A.G, kg = k + G;
   const int lane = tid & 63, wv = tid >> 6, nw = (int)(blockDim.x >> 6);
   const bool on0 = lane < kg, on1 = lane + 64 < kg, on2 = lane + 128 < kg;
   double s0 = 0.0, s1 = 0.0, s2 = 0.0;
@@ -458,12 +488,12 @@ __device__ __forceinline__ SmallLds small_lds(double* sm, int k, int ncol) {
   return L;
 }
 
-__device__ __forceinline__ void small_free_solve(const PolishArgs& A, int a, int nF, const int32_t* flist,
+__device__ __forceinline__ void small_free_solve(const PolishArgs& A, int a, int tid, int nF, const int32_t* flist,
                                  const int8_t* code, const int* ps, int nc, int ncol, int cap_on,
                                  double gam, float lbf, float ubf, float kap, bool phi,
                                  const double* fy, const SmallLds& L, double* shd, double* hd,
                                  double* Sd, int& i_mine, float& w0_mine) {
-  const int k = A.k, G = A.G, kg = k + G, tid = threadIdx.x, n = A.n;
+  const int k = A.k, G = A.G, kg = k + G, n = A.n;
   double *Hs = L.Hs, *Vs = L.Vs, *Xs = L.Xs;
   // stage the free rows' B~, f and F yX; the thread's own free row (nF <=
   // kPT) starts its loads meanwhile
@@ -567,30 +597,32 @@ __host__ __device__ __forceinline__ int rpart_stride(int k, int G) { return k + 
 // rows of block b: [b kRB, b kRB + rows_in_block)
 __device__ __forceinline__ int rows_in_block(int n, int b) { return min(kRB, n - b * kRB); }
 
-// polish_rows: (first round) the pattern of the iterate, else the
+// Rows of block b, by kRT threads (tid; the whole workgroup calls it, with the
+// block's number or -1): (first round) the pattern of the iterate, else the
 // proposals of the last failed check adopted as the pattern; the fixed
 // rows' values; the block's free rows (front of its fseg segment, ascending)
 // and nonzero fixed rows (back of the segment, ascending from the end); the
 // partials above
-__global__ __launch_bounds__(kRT) void polish_rows_kernel(PolishArgs A) {
-  __shared__ int s_wc[kRR][kRW][2];
-  __shared__ int s_nz[kRB];
-  __shared__ double s_red[kRW * (kMaxK + kMaxG)];
-  __shared__ double s_sh[3 * kRW];
-  __shared__ unsigned s_sg[kRW];
-  const int k = A.k, G = A.G, n = A.n, tid = threadIdx.x;
-  const int b = blockIdx.x, slot = blockIdx.y;
-  if (slot >= *A.m_act) return;
-  const int a = A.act[slot];
-  const int* ps = A.pstate + (size_t)a * kPStateStride;
-  if (!A.first_round && (ps[PS_DONE] || ps[PS_STALL])) return;
+struct RowsLds {
+  double red[kRW * (kMaxK + kMaxG)];
+  double sh[2 * kRW];
+  double nw[kRB];              // the nonzero fixed rows' weights
+  int wc[kRR][kRW][2];
+  int nz[kRB];
+  unsigned sg[kRW];
+};
+__device__ __forceinline__ void rows_block(const PolishArgs& A, int a, int b, int tid, int first,
+                                           RowsLds& L) {
+  const int k = A.k, G = A.G, n = A.n;
+  const bool live = b >= 0;
+  b = live ? b : 0;
   const float* par = A.par + (size_t)a * kNPar;
   const float lbf = par[P_LB], ubf = par[P_UB], kap = par[P_KAPPA], tauf = par[P_TAU];
   const bool phi = (kap > 0.f) || isfinite(tauf) || (par[P_HASTAX] != 0.f);
   int8_t* code = A.code + (size_t)a * n;
   const int8_t* prop = A.code_next + (size_t)a * n;
   double* w = A.wout + (size_t)a * n;
-  const int nrow = rows_in_block(n, b);
+  const int nrow = live ? rows_in_block(n, b) : 0;
   int32_t* seg = A.fseg + (size_t)a * n + (size_t)b * kRB;
   const int lane = tid & 63, wv = tid >> 6;
   const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -600,23 +632,24 @@ __global__ __launch_bounds__(kRT) void polish_rows_kernel(PolishArgs A) {
   for (int u = 0; u < kRR; ++u) {
     ii[u] = b * kRB + u * kRT + tid;
     const int ic = min(ii[u], n - 1);
-    zz[u] = A.first_round ? A.z[(size_t)a * n + ic] : 0.f;
-    cc[u] = A.first_round ? 0 : (int)prop[ic];
+    zz[u] = first ? A.z[(size_t)a * n + ic] : 0.f;
+    cc[u] = first ? 0 : (int)prop[ic];
   }
   RowData rd[kRR];
   row_data_n<kRR>(A, a, ii, lbf, ubf, rd);
   unsigned sig = 0u;                          // signature of the pattern
   double sx = 0.0, sturn = 0.0;
   unsigned long long mf[kRR], mn[kRR];
+  double vv[kRR] = {};
 #pragma unroll
   for (int u = 0; u < kRR; ++u) {
     const int i = ii[u];
     int isfree = 0, isnz = 0;
-    if (i < n) {
+    if (live && i < n) {
       Geom g;
       make_geom(g, kap, phi, rd[u]);
       int c = cc[u];
-      if (A.first_round) {
+      if (first) {
         const float z = zz[u];
         // at point j (the float32 value the prox lands on), else inside the
         // piece above the inner points below z (the points ascend)
@@ -640,6 +673,7 @@ __global__ __launch_bounds__(kRT) void polish_rows_kernel(PolishArgs A) {
       } else {
         const double v = g.pt(c >> 1);
         w[i] = v;
+        vv[u] = v;
         isnz = (v != 0.0);
         sx += v;
         sturn += fabs(v - (double)rd[u].w0);
@@ -651,8 +685,8 @@ __global__ __launch_bounds__(kRT) void polish_rows_kernel(PolishArgs A) {
   if (lane == 0) {
 #pragma unroll
     for (int u = 0; u < kRR; ++u) {
-      s_wc[u][wv][0] = __popcll(mf[u]);
-      s_wc[u][wv][1] = __popcll(mn[u]);
+      L.wc[u][wv][0] = __popcll(mf[u]);
+      L.wc[u][wv][1] = __popcll(mn[u]);
     }
   }
   __syncthreads();
@@ -662,7 +696,7 @@ __global__ __launch_bounds__(kRT) void polish_rows_kernel(PolishArgs A) {
     int bf = 0, bn = 0, tf = 0, tn = 0;
 #pragma unroll
     for (int q = 0; q < kRW; ++q) {
-      const int xf = s_wc[u][q][0], xn = s_wc[u][q][1];
+      const int xf = L.wc[u][q][0], xn = L.wc[u][q][1];
       bf += (q < wv) ? xf : 0;
       bn += (q < wv) ? xn : 0;
       tf += xf;
@@ -672,64 +706,77 @@ __global__ __launch_bounds__(kRT) void polish_rows_kernel(PolishArgs A) {
     if ((mn[u] >> lane) & 1ull) {
       const int t = pn + bn + __popcll(mn[u] & below);
       seg[nrow - 1 - t] = ii[u];
-      s_nz[t] = ii[u];
+      L.nz[t] = ii[u];
+      L.nw[t] = vv[u];
     }
     pf += tf;
     pn += tn;
   }
   __syncthreads();
-  // column sums over the nonzero fixed rows: one wave per row, four rows at
-  // a time, the lanes over the columns (lane, lane + 64, lane + 128)
+  // column sums over the nonzero fixed rows: one wave per row, four rows a
+  // step and two steps' loads in flight, the lanes over the columns (lane,
+  // lane + 64, lane + 128; past the last column its repeats, dropped)
   const int kg = k + G;
   const bool on0 = lane < kg, on1 = lane + 64 < kg, on2 = lane + 128 < kg;
+  const int j0 = min(lane, kg - 1), j1 = min(lane + 64, kg - 1), j2 = min(lane + 128, kg - 1);
+  const bool wide1 = kg > 64, wide2 = kg > 128;            // uniform
   double c0 = 0.0, c1 = 0.0, c2 = 0.0;
-  for (int t0 = 4 * wv; t0 < pn; t0 += 4 * kRW) {
-    double wt[4];
-    float b0[4], b1[4], b2[4];
+  for (int t0 = 4 * wv; t0 < pn; t0 += 8 * kRW) {
+    double wt[8];
+    float b0[8], b1[8], b2[8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = s_nz[min(t0 + u, pn - 1)];
-      const float* row = A.Bt + (size_t)i * A.kp;
-      wt[u] = (t0 + u < pn) ? w[i] : 0.0;
-      b0[u] = on0 ? row[lane] : 0.f;
-      b1[u] = on1 ? row[lane + 64] : 0.f;
-      b2[u] = on2 ? row[lane + 128] : 0.f;
+    for (int u = 0; u < 8; ++u) {
+      const int t = t0 + (u & 3) + (u >> 2) * 4 * kRW, tc = min(t, pn - 1);
+      const float* row = A.Bt + (size_t)L.nz[tc] * A.kp;
+      wt[u] = t < pn ? L.nw[tc] : 0.0;
+      b0[u] = row[j0];
+      if (wide1) b1[u] = row[j1];
+      if (wide2) b2[u] = row[j2];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < 8; ++u) {
       c0 += (double)b0[u] * wt[u];
-      c1 += (double)b1[u] * wt[u];
-      c2 += (double)b2[u] * wt[u];
+      if (wide1) c1 += (double)b1[u] * wt[u];
+      if (wide2) c2 += (double)b2[u] * wt[u];
     }
   }
-  if (on0) s_red[wv * kg + lane] = c0;
-  if (on1) s_red[wv * kg + lane + 64] = c1;
-  if (on2) s_red[wv * kg + lane + 128] = c2;
+  if (on0) L.red[wv * kg + lane] = c0;
+  if (on1) L.red[wv * kg + lane + 64] = c1;
+  if (on2) L.red[wv * kg + lane + 128] = c2;
   // budget, turnover and signature partials
-  {
-    double sv[2] = {sx, sturn}, mv[1] = {0.0};
-    bred<2, 1>(sv, mv, s_sh);
-    sx = sv[0]; sturn = sv[1];
-  }
+  sx = wave_red(sx, SumOp());
+  sturn = wave_red(sturn, SumOp());
+  if (lane == 0) { L.sh[wv] = sx; L.sh[kRW + wv] = sturn; }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) sig += __shfl_xor(sig, o, 64);
-  if (lane == 0) s_sg[wv] = sig;
+  if (lane == 0) L.sg[wv] = sig;
   __syncthreads();
+  if (!live) return;
   double* rp = A.rpart + ((size_t)a * A.n_sb + b) * rpart_stride(k, G);
   for (int j = tid; j < kg; j += kRT) {
     double v = 0.0;
-    for (int q = 0; q < kRW; ++q) v += s_red[q * kg + j];
+    for (int q = 0; q < kRW; ++q) v += L.red[q * kg + j];
     rp[j] = v;
   }
   if (tid == 0) {
     unsigned sg = 0u;
-    for (int q = 0; q < kRW; ++q) sg += s_sg[q];
-    rp[kg] = sx;
-    rp[kg + 1] = sturn;
+    for (int q = 0; q < kRW; ++q) sg += L.sg[q];
+    rp[kg] = (L.sh[0] + L.sh[1]) + (L.sh[2] + L.sh[3]);
+    rp[kg + 1] = (L.sh[kRW] + L.sh[kRW + 1]) + (L.sh[kRW + 2] + L.sh[kRW + 3]);
     rp[kg + 2] = pf;
     rp[kg + 3] = pn;
     rp[kg + 4] = (double)sg;
   }
+}
+
+__global__ __launch_bounds__(kRT) void polish_rows_kernel(PolishArgs A) {
+  __shared__ RowsLds L;
+  const int slot = blockIdx.y;
+  if (slot >= *A.m_act) return;
+  const int a = A.act[slot];
+  const int* ps = A.pstate + (size_t)a * kPStateStride;
+  if (!A.first_round && (ps[PS_DONE] || ps[PS_STALL])) return;
+  rows_block(A, a, blockIdx.x, threadIdx.x, A.first_round, L);
 }
 
 // The same system by one wave (nc <= kSchurW), lane i its row i: the pivot by
@@ -760,7 +807,9 @@ __device__ __forceinline__ int schur_solve_wave(int nc, int ncol, const double* 
   double ld = 1.0, id = 1.0;                          // L_pp of a pivot row, 1 / L_pp
   int rank = 0;
   for (int j = 0; j < nc; ++j) {
-    const double mx = wave_red(on && pos >= j ? dg : -INFINITY, MaxOp());
+    double mx = on && pos >= j ? dg : -INFINITY;
+    if (nc <= 16) mx = lane_d(row_red(mx, MaxOp()), 0);   // uniform: one row holds them all
+    else mx = wave_red(mx, MaxOp());
     if (!(mx > ptol)) break;                          // uniform
     // the largest remaining pivot, the first in place among equals
     unsigned long long tie = __ballot(on && pos >= j && dg == mx);
@@ -775,8 +824,20 @@ __device__ __forceinline__ int schur_solve_wave(int nc, int ncol, const double* 
     // (with the pivot in place j already both lines change nothing)
     if (j == 0) pos1 = pos;
     double c = pos1 >= __builtin_amdgcn_readlane(pos1, p) ? Sr[p] : S[p * ncol + row];
-    for (int l = 0; l < j; ++l) c -= Lt[l * kSchurW + row] * Lt[l * kSchurW + p];
-    const double djj = sqrt(mx), ij = 1.0 / djj;
+    for (int l0 = 0; l0 < j; l0 += 4) {                // four columns' loads together
+      double x4[4], y4[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int l = min(l0 + u, j - 1);
+        x4[u] = Lt[l * kSchurW + row];
+        y4[u] = Lt[l * kSchurW + p];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (l0 + u < j) c -= x4[u] * y4[u];            // uniform
+    }
+    double djj, ij;
+    root_recip(mx, djj, ij);
     c = lane == p ? djj : div_by(c, djj, ij);
     if (lane == p) { ld = djj; id = ij; }
     if (on) Lt[j * kSchurW + lane] = c;
@@ -792,35 +853,59 @@ __device__ __forceinline__ int schur_solve_wave(int nc, int ncol, const double* 
     t -= Sr[pq] * lane_d(x, pq);
   }
   if (pos < rank) x = t;
-  for (int l = 0; l < rank; ++l) {                    // L11 z = rhs
-    const int p = __builtin_amdgcn_readlane(ord, l);
-    const double xl = div_by(lane_d(x, p), lane_d(ld, p), lane_d(id, p));
-    const double lv = Lt[l * kSchurW + row];
-    x = lane == p ? xl : (pos > l && pos < rank ? x - lv * xl : x);
-  }
-  // L11^T y = z for x and for the null directions v_piv = -L11^-T L21^T e_t,
-  // v_t = 1: a right-hand side a lane (0: x, 1 + q: null direction q), the
-  // unknowns of place l in xs[l][lane]
-  const int nd = min(nc - rank, kMaxNull);
-  double* xs = Lt + rank * kSchurW;                   // [rank][1 + kMaxNull]
-  constexpr int kR = 1 + kMaxNull;
-  const int r = min(lane, nd);
-  if (on && pos < rank) xs[pos * kR] = x;
-  wave_sync();
-  const int tl = r > 0 ? __builtin_amdgcn_ds_bpermute(4 * (rank + r - 1), ord) : 0;
-  for (int i = rank - 1; i >= 0; --i) {
-    const int p = __builtin_amdgcn_readlane(ord, i);
-    double y = r > 0 ? -Lt[i * kSchurW + tl] : xs[i * kR];
-    for (int l = i + 1; l < rank; ++l)
-      y -= Lt[i * kSchurW + __builtin_amdgcn_readlane(ord, l)] * xs[l * kR + r];
-    y = div_by(y, lane_d(ld, p), lane_d(id, p));
-    if (lane <= nd) xs[i * kR + r] = y;
+  // everything in place order from here: lane l the unknown of place l, Lt[l]
+  // the factor's column l by place
+  for (int l0 = 0; l0 < rank; l0 += 8) {
+    double x8[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x8[u] = Lt[min(l0 + u, rank - 1) * kSchurW + row];
     wave_sync();
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (on && l0 + u < rank) Lt[(l0 + u) * kSchurW + pos] = x8[u];
   }
-  if (on) {
-    rr[lane] = pos < rank ? xs[pos * kR] : x;
-    for (int q = 0; q < nd; ++q)
-      nul[q * nul_stride + lane] = pos < rank ? xs[pos * kR + 1 + q] : (pos == rank + q ? 1.0 : 0.0);
+  wave_sync();
+  x = push_d(x, pos);
+  ld = push_d(ld, pos);
+  id = push_d(id, pos);
+  for (int l0 = 0; l0 < rank; l0 += 8) {              // L11 z = rhs
+    double lv[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) lv[u] = Lt[min(l0 + u, rank - 1) * kSchurW + row];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int l = l0 + u;
+      if (l >= rank) break;                           // uniform
+      const double z = div_by(x, ld, id), xl = lane_d(z, l);
+      x = lane == l ? z : (lane > l && lane < rank ? x - lv[u] * xl : x);
+    }
+  }
+  // L11^T y = z, each unknown's sum in ascending order of places
+  auto back = [&](double y) {
+    for (int i0 = (rank - 1) & ~7; i0 >= 0; i0 -= 8) {
+      double lv[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) lv[u] = Lt[min(i0 + u, rank - 1) * kSchurW + row];
+#pragma unroll
+      for (int u = 7; u >= 0; --u) {
+        const int i = i0 + u;
+        if (i >= rank) continue;                      // uniform
+        double s = lane_d(y, i);
+        for (int l = i + 1; l < rank; ++l) s -= lane_d(lv[u], l) * lane_d(y, l);
+        s = div_by(s, lane_d(ld, i), lane_d(id, i));
+        y = lane == i ? s : y;
+      }
+    }
+    return y;
+  };
+  x = back(x);
+  if (on) rr[ord] = x;
+  // null directions: v_piv = -L11^-T L21^T e_t, v_t = 1
+  const int nd = min(nc - rank, kMaxNull);
+  for (int q = 0; q < nd; ++q) {
+    double v = lane < rank ? -Lt[lane * kSchurW + rank + q] : (lane == rank + q ? 1.0 : 0.0);
+    v = back(v);
+    if (on) nul[q * nul_stride + ord] = v;
   }
   return nd;
 }
@@ -991,9 +1076,9 @@ __device__ __forceinline__ bool gated(const PolishArgs& A, int first, int* ps,
 // order), the budget and turnover sums of the fixed rows, the pattern's
 // signature, yX = B_X^T w_X and the fixed rows' constraint-row sums (ends
 // synchronised)
-__device__ __forceinline__ PatternSums gather_pattern(const PolishArgs& A, int a, double* smem_d,
-                                                      AcctLds& W) {
-  const int k = A.k, G = A.G, n = A.n, tid = threadIdx.x;
+__device__ __forceinline__ PatternSums gather_pattern(const PolishArgs& A, int a, int tid, int first,
+                                                      double* smem_d, AcctLds& W) {
+  const int k = A.k, G = A.G, n = A.n;
   int32_t* flist = A.flist + (size_t)a * n;         // free rows from the front
   PatternSums X;
   const int S = A.n_sb, kg = k + G, rps = rpart_stride(k, G);
@@ -1010,7 +1095,7 @@ __device__ __forceinline__ PatternSums gather_pattern(const PolishArgs& A, int a
     s_ox[bb + 1] = (int)rp[(size_t)bb * rps + kg + 3];
   }
   __syncthreads();
-  if (A.first_round) {                          // the pattern's signature: any order
+  if (first) {                          // the pattern's signature: any order
     unsigned su = 0u;
     for (int bb = tid; bb < S; bb += kPT) su += (unsigned)rp[(size_t)bb * rps + kg + 4];
     if (su) atomicAdd(&s_sig, su);
@@ -1108,9 +1193,10 @@ __device__ __forceinline__ PatternSums gather_pattern(const PolishArgs& A, int a
 // dynamic LDS of polish_smem bytes; ps: its bookkeeping (global or LDS).
 // Leaves the free rows' weights in wout, W.mult, W.yF, W.gsum (not
 // synchronised) and returns the turnover of the polished weights.
-__device__ __forceinline__ double solve_pattern(const PolishArgs& A, int a, const float* par, int* ps,
-                                                const PatternSums& X, double* smem_d, AcctLds& W) {
-  const int k = A.k, G = A.G, n = A.n, tid = threadIdx.x;
+__device__ __forceinline__ double solve_pattern(const PolishArgs& A, int a, int tid, const float* par,
+                                                int* ps, const PatternSums& X, double* smem_d,
+                                                AcctLds& W) {
+  const int k = A.k, G = A.G, n = A.n;
   const float lbf = par[P_LB], ubf = par[P_UB], kap = par[P_KAPPA], tauf = par[P_TAU];
   const double gam = par[P_GAMMA];
   const bool phi = (kap > 0.f) || isfinite(tauf) || (par[P_HASTAX] != 0.f);
@@ -1162,7 +1248,7 @@ __device__ __forceinline__ double solve_pattern(const PolishArgs& A, int a, cons
   int i_mine = 0;                         // small path: the thread's free row, its w0
   float w0_mine = 0.f;
   if (small) {
-    small_free_solve(A, a, nF, flist, code, ps, nc, ncol, cap_on, gam, lbf, ubf, kap, phi, W.fy, L,
+    small_free_solve(A, a, tid, nF, flist, code, ps, nc, ncol, cap_on, gam, lbf, ubf, kap, phi, W.fy, L,
                      shd, hd, Sd, i_mine, w0_mine);
   } else {
   // ---- one pass over the free rows, SR staged at a time: Kf = diag(1/f) +
@@ -1430,7 +1516,7 @@ __device__ __forceinline__ double solve_pattern(const PolishArgs& A, int a, cons
     }
   } else {
     double ys = 0.0, gs = 0.0;
-    list_sums(A, flist, n, nF, 0, w, Kf, ys, gs);     // the solve is done with Kf
+    list_sums(A, tid, flist, n, nF, 0, w, Kf, ys, gs);     // the solve is done with Kf
     if (tid < k) W.yF[tid] = (X.yx + ys) * X.f;
     if (tid < G) W.gsum[tid] = W.gfix[tid] + gs;
   }
@@ -1451,9 +1537,9 @@ __global__ __launch_bounds__(kPT) void polish_solve_kernel(PolishArgs A) {
   if (A.first_round) begin_pass(A, a, par, ps, W.mult);
   else
     for (int e = tid; e < 2 + G; e += kPT) W.mult[e] = mult[e];
-  const PatternSums X = gather_pattern(A, a, smem_d, W);
+  const PatternSums X = gather_pattern(A, a, tid, A.first_round, smem_d, W);
   if (gated(A, A.first_round, ps, X, &s_same)) return;
-  const double turn = solve_pattern(A, a, par, ps, X, smem_d, W);
+  const double turn = solve_pattern(A, a, tid, par, ps, X, smem_d, W);
   // for the passes after it (a thread's own entries of yF and gsum)
   const Wk wk = wk_of(A, a);
   if (tid < k) wk.yF[tid] = W.yF[tid];
@@ -1702,15 +1788,16 @@ __device__ __forceinline__ void step_bounds(const PolishArgs& A, int a, const do
 }
 
 // the step along D given the rows' bounds [Lo, Up] (keys kLo, kUp): updates
-// mult; *block takes the row to release when one blocks the target
-__device__ void sweep_step(const PolishArgs& A, const int* ps, const SweepDir& D, const StepRows& R,
-                           double Lo, double Up, int kLo, int kUp, double thr, double turn0,
-                           float tauf, double* mult, int* block) {
-  const int G = A.G;
+// mult; *block takes the row to release when one blocks the target.  One
+// wave, a constraint row a lane (G <= 64).
+__device__ __forceinline__ void sweep_step(const PolishArgs& A, const int* ps, const SweepDir& D,
+                                           const StepRows& R, double Lo, double Up, int kLo,
+                                           int kUp, double thr, double turn0, float tauf,
+                                           double* mult, int* block) {
+  const int lane = threadIdx.x & 63, g = min(lane, max(A.G - 1, 0));
   const double ncap = D.ncap, lamc = D.lamc;
-  const unsigned act0 = (unsigned)ps[PS_BACT0], act1 = (unsigned)ps[PS_BACT1];
-  const unsigned up0 = (unsigned)ps[PS_BUP0], up1 = (unsigned)ps[PS_BUP1];
   const bool cap_on = ps[PS_CAP];
+  const bool act = lane < A.G && band_active(ps, g), up = band_upper(ps, g);
   // targets along this direction, by priority: (1) an active constraint the
   // solve could not enforce (dependent row) and that is violated: push its
   // multiplier outward until a fixed row blocks, and release that row; (2)
@@ -1724,39 +1811,51 @@ __device__ void sweep_step(const PolishArgs& A, const int* ps, const SweepDir& D
     else if (ncap < -1e-12) { const double u = -lamc / ncap; if (u < Up) { Up = u; kUp = INT_MAX; } }
     const double sl = (double)tauf - turn0;
     if (fabs(ncap) > 1e-12) {
-      if (sl < -vtol && -sl > worst) {
+      if (sl < -vtol) {
         worst = -sl; tgt = (ncap > 0.0) ? INFINITY : -INFINITY; has_tgt = true;
-      } else if (worst == 0.0) {
+      } else {
         const double v = fabs(lamc) * fmax(sl, 0.0);
-        if (v > thr && v > best) { best = v; tgt = -lamc / ncap; has_tgt = true; }
+        if (v > thr) { best = v; tgt = -lamc / ncap; has_tgt = true; }
       }
     }
   }
-  for (int gg = 0; gg < G; ++gg) {
-    if (!(((gg < 32 ? act0 : act1) >> (gg & 31)) & 1u)) continue;
-    const double nbv = R.nv[gg];
-    const double cur = mult[2 + gg];
-    const bool up = ((gg < 32 ? up0 : up1) >> (gg & 31)) & 1u;
+  if (A.G) {
+    const double nbv = act ? R.nv[g] : 0.0;
+    const double cur = mult[2 + g];
     // upper band: lam >= 0 ; lower band: lam <= 0
     const double sgn_req = up ? 1.0 : -1.0;
     const double aa = sgn_req * nbv, bb = sgn_req * cur;   // bb + s aa >= 0
-    if (aa > 1e-12) { const double u = -bb / aa; if (u > Lo) { Lo = u; kLo = INT_MAX; } }
-    else if (aa < -1e-12) { const double u = -bb / aa; if (u < Up) { Up = u; kUp = INT_MAX; } }
-    if (fabs(nbv) <= 1e-12) continue;
-    const double sl = up ? (double)R.hi[gg] - R.gs[gg] : R.gs[gg] - (double)R.lo[gg];
-    if (sl < -vtol && -sl > worst) {
-      worst = -sl; tgt = (aa > 0.0) ? INFINITY : -INFINITY; has_tgt = true;
+    const double ul = aa > 1e-12 ? -bb / aa : -INFINITY, uu = aa < -1e-12 ? -bb / aa : INFINITY;
+    const double ml = wave_red(ul, MaxOp()), mu = -wave_red(-uu, MaxOp());
+    if (ml > Lo) { Lo = ml; kLo = INT_MAX; }
+    if (mu < Up) { Up = mu; kUp = INT_MAX; }
+    // the worst violation (the first row among equals), else the largest
+    // slack product
+    const bool in = act && fabs(nbv) > 1e-12;
+    const double sl = up ? (double)R.hi[g] - R.gs[g] : R.gs[g] - (double)R.lo[g];
+    const double viol = in && sl < -vtol ? -sl : 0.0;
+    const double wv = wave_red(viol, MaxOp());
+    if (wv > worst) {
+      const int l = __ffsll((unsigned long long)__ballot(viol == wv)) - 1;
+      tgt = (lane_d(aa, l) > 0.0) ? INFINITY : -INFINITY;
+      has_tgt = true;
     } else if (worst == 0.0) {
-      const double v = fabs(cur) * fmax(sl, 0.0);
-      if (v > thr && v > best) { best = v; tgt = -cur / nbv; has_tgt = true; }
+      const double v0 = in ? fabs(cur) * fmax(sl, 0.0) : 0.0, v = v0 > thr ? v0 : 0.0;
+      const double wb = wave_red(v, MaxOp());
+      if (wb > best) {
+        const int l = __ffsll((unsigned long long)__ballot(v == wb)) - 1;
+        tgt = lane_d(-cur / nbv, l);
+        has_tgt = true;
+      }
     }
   }
   double st;
+  int blk = -1;
   if (Lo <= Up) {
     st = fmin(fmax(tgt, Lo), Up);
     if (has_tgt) {
       const int key = (tgt < Lo) ? kLo : (tgt > Up) ? kUp : INT_MAX;
-      if (key != INT_MAX && *block < 0) *block = key;
+      if (key != INT_MAX) blk = key;
     } else if (isfinite(Lo) && isfinite(Up)) {
       st += 1e-3 * (0.5 * (Lo + Up) - st);
     }
@@ -1765,10 +1864,12 @@ __device__ void sweep_step(const PolishArgs& A, const int* ps, const SweepDir& D
   }
   if (!isfinite(st)) st = 0.0;
   // eta += st * v  ->  nu -= st v0, bands += st v_b, lam_cap += st v_cap
-  mult[0] -= st * D.n0;
-  for (int gg = 0; gg < G; ++gg)
-    if (((gg < 32 ? act0 : act1) >> (gg & 31)) & 1u) mult[2 + gg] += st * R.nv[gg];
-  if (cap_on) mult[1] += st * ncap;
+  if (act) mult[2 + g] += st * R.nv[g];
+  if (lane == 0) {
+    if (blk >= 0 && *block < 0) *block = blk;
+    mult[0] -= st * D.n0;
+    if (cap_on) mult[1] += st * ncap;
+  }
 }
 
 // the check passes' per-row inputs of U rows (all loads issued together)
@@ -1779,12 +1880,12 @@ struct CheckIn {
   RowData rd[U];
 };
 template <int U>
-__device__ __forceinline__ void check_in(const PolishArgs& A, int a, int base, int stride,
+__device__ __forceinline__ void check_in(const PolishArgs& A, int a, int tid, int base, int stride,
                                          bool want_mu, float lbf, float ubf, CheckIn<U>& I) {
   const int n = A.n;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    I.ii[u] = base + u * stride + (int)threadIdx.x;
+    I.ii[u] = base + u * stride + tid;
     const int ic = min(I.ii[u], n - 1);
     const size_t off = (size_t)a * n + ic;
     I.cc[u] = A.code[off];
@@ -1843,7 +1944,7 @@ __global__ __launch_bounds__(kRT) void polish_sweep_kernel(PolishArgs A, int fin
   dir_rows(ps, G, nul, s_nv);
   if (tid == 0) { s_key[0] = INT_MAX; s_key[1] = INT_MAX; }
   CheckIn<kRR> I;
-  check_in(A, a, b * kRB, kRT, false, lbf, ubf, I);
+  check_in(A, a, tid, b * kRB, kRT, false, lbf, ubf, I);
   __syncthreads();
   const SweepDir D = sweep_dir(ps, nul, mult);
   double Lo = -INFINITY, Up = INFINITY;
@@ -1866,6 +1967,43 @@ __global__ __launch_bounds__(kRT) void polish_sweep_kernel(PolishArgs A, int fin
     sp[2] = s_key[0];
     sp[3] = s_key[1];
   }
+}
+
+// One null direction swept by the whole workgroup (every row's bounds, then
+// the step): one sweep over the directions a round (a second one, for
+// directions that interact, cost a full pass per direction and certified no
+// more accounts: the next refinement round revisits them anyway).  Ends
+// synchronised.
+__device__ __forceinline__ void sweep_one(const PolishArgs& A, int a, int tid, const int* ps,
+                                          const double* nul, float lbf, float ubf, float kap,
+                                          bool phi, double thr, double turn0, float tauf,
+                                          double* mult, StepRows& R, double* sh, int* key,
+                                          int* block) {
+  const int n = A.n, nt = (int)blockDim.x;
+  const SweepDir D = sweep_dir(ps, nul, mult);
+  dir_rows(ps, A.G, nul, R.nv);
+  if (threadIdx.x == 0) { key[0] = INT_MAX; key[1] = INT_MAX; }
+  __syncthreads();
+  double Lo = -INFINITY, Up = INFINITY;
+  int loKey = INT_MAX, upKey = INT_MAX;
+  for (int base = 0; base < n; base += kPU * nt) {
+    CheckIn<kPU> I;
+    check_in(A, a, tid, base, nt, false, lbf, ubf, I);
+#pragma unroll
+    for (int u = 0; u < kPU; ++u)
+      if (I.ii[u] < n)
+        sweep_row(A, D, R.nv, mult, I.ii[u], I.cc[u], I.gb[u], I.w[u], I.grp[u], I.rd[u], kap, phi,
+                  Lo, Up, loKey, upKey);
+  }
+  double sv[1] = {0.0}, mv[2] = {Lo, -Up};
+  bred<1, 2>(sv, mv, sh);
+  const double Lb = mv[0], Ub = -mv[1];
+  if (Lo == Lb && isfinite(Lb)) atomicMin(&key[0], loKey);
+  if (Up == Ub && isfinite(Ub)) atomicMin(&key[1], upKey);
+  __syncthreads();
+  if (threadIdx.x < 64)
+    sweep_step(A, ps, D, R, Lb, Ub, key[0], key[1], thr, turn0, tauf, mult, block);
+  __syncthreads();
 }
 
 // per account: the gradient scale (from polish_gbase's blocks), then the
@@ -1919,44 +2057,15 @@ __global__ __launch_bounds__(kPTC) void polish_pre_kernel(PolishArgs A, int fina
     int kLo, kUp;
     dir_rows(ps, G, wkc.nul, s_nv);
     gather_bounds(A, a, s_red6, s_key, Lo, Up, kLo, kUp);
-    if (tid == 0) {
+    if (tid < 64) {
       const SweepDir D = sweep_dir(ps, wkc.nul, mult);
       sweep_step(A, ps, D, R, Lo, Up, kLo, kUp, thr, turn0, tauf, mult, &s_block);
     }
     __syncthreads();
   } else if (nd > 1 && A.n_sb < kSplitDir) {
-    // one sweep over the directions (a second one, for directions that
-    // interact, cost a full pass per direction and certified no more
-    // accounts: the next refinement round revisits them anyway)
-    for (int sweep = 0; sweep < 1; ++sweep) {
-      for (int q = 0; q < nd; ++q) {
-        const SweepDir D = sweep_dir(ps, wkc.nul + q * ncol, mult);
-        dir_rows(ps, G, wkc.nul + q * ncol, s_nv);
-        __syncthreads();
-        double Lo = -INFINITY, Up = INFINITY;
-        int loKey = INT_MAX, upKey = INT_MAX;
-        for (int base = 0; base < n; base += kPU * kPTC) {
-          CheckIn<kPU> I;
-          check_in(A, a, base, kPTC, false, lbf, ubf, I);
-#pragma unroll
-          for (int u = 0; u < kPU; ++u)
-            if (I.ii[u] < n)
-              sweep_row(A, D, s_nv, mult, I.ii[u], I.cc[u], I.gb[u], I.w[u], I.grp[u], I.rd[u],
-                        kap, phi, Lo, Up, loKey, upKey);
-        }
-        double sv[1] = {0.0}, mv[2] = {Lo, -Up};
-        bred<1, 2>(sv, mv, s_red6);
-        const double Lb = mv[0], Ub = -mv[1];
-        if (tid == 0) { s_key[0] = INT_MAX; s_key[1] = INT_MAX; }
-        __syncthreads();
-        if (Lo == Lb && isfinite(Lb)) atomicMin(&s_key[0], loKey);
-        if (Up == Ub && isfinite(Ub)) atomicMin(&s_key[1], upKey);
-        __syncthreads();
-        if (tid == 0)
-          sweep_step(A, ps, D, R, Lb, Ub, s_key[0], s_key[1], thr, turn0, tauf, mult, &s_block);
-        __syncthreads();
-      }
-    }
+    for (int q = 0; q < nd; ++q)
+      sweep_one(A, a, tid, ps, wkc.nul + q * ncol, lbf, ubf, kap, phi, thr, turn0, tauf, mult, R,
+                s_red6, s_key, &s_block);
   }
   for (int q = tid; q < 2 + G; q += kPTC) gmult[q] = mult[q];
   if (tid == 0) {
@@ -1997,7 +2106,7 @@ __global__ __launch_bounds__(kRT) void polish_dir_kernel(PolishArgs A, int final
   dir_rows(ps, G, wk.nul + q * (G + 3), s_nv);
   if (tid == 0) { s_key[0] = INT_MAX; s_key[1] = INT_MAX; }
   CheckIn<kRR> I;
-  check_in(A, a, b * kRB, kRT, false, lbf, ubf, I);
+  check_in(A, a, tid, b * kRB, kRT, false, lbf, ubf, I);
   __syncthreads();
   const SweepDir D = sweep_dir(ps, wk.nul + q * (G + 3), mult);
   double Lo = -INFINITY, Up = INFINITY;
@@ -2029,15 +2138,67 @@ __global__ __launch_bounds__(kRT) void polish_dir_kernel(PolishArgs A, int final
   double Lg, Ug;
   int kLo, kUp;
   gather_bounds(A, a, s_sh, s_key, Lg, Ug, kLo, kUp);
-  if (tid == 0) {
+  if (tid < 64) {
     const double thr = 0.01 * A.eps_comp * wk.misc[0];
-    s_block = ps[PS_BLOCK];
+    if (tid == 0) s_block = ps[PS_BLOCK];
     sweep_step(A, ps, D, R, Lg, Ug, kLo, kUp, thr, wk.misc[1], tauf, mult, &s_block);
-    ps[PS_BLOCK] = s_block;
-    ps[PS_TICK] = 0;
+    if (tid == 0) {
+      ps[PS_BLOCK] = s_block;
+      ps[PS_TICK] = 0;
+    }
   }
   __syncthreads();
   for (int e = tid; e < 2 + G; e += kRT) gmult[e] = mult[e];
+}
+
+// one row's diagnostics and its refinement proposal
+struct CheckSums {
+  double sw = 0.0, turn = 0.0, dmax = 0.0, box = 0.0, snapm = 0.0, obj = 0.0, bad = 0.0;
+  int changed = 0;
+};
+__device__ __forceinline__ int check_row(const PolishArgs& A, int i, int c, double gbi, double wi,
+                                         double mui, int grp, const RowData& r, const double* mult,
+                                         float kap, bool phi, double gam, CheckSums& S) {
+  const double nu = mult[0], lam = mult[1];
+  Geom g;
+  make_geom(g, kap, phi, r);
+  const double lb = r.lb, ub = r.ub;
+  const double sig = (gbi + mui) / gam;
+  double gi = gbi - nu;
+  if (A.G) gi += rows_dot_g(A, i, grp, mult + 2);
+  double lo, hi, snap;
+  subdiff(g, wi, lam, lb, ub, lo, hi, snap);
+  const double t = -gi;
+  const double dist = fmax(fmax(lo - t, t - hi), 0.0);
+  S.sw += wi;
+  S.turn += fabs(wi - g.w0);
+  S.dmax = fmax(S.dmax, dist);
+  if (!isfinite(dist)) S.bad = 1.0;
+  S.box = fmax(S.box, fmax(lb - wi, wi - ub));
+  S.snapm = fmax(S.snapm, snap);
+  // objective: (gamma/2) w.Sigma w - mu w + trade cost
+  double tc = (double)kap * fabs(wi - g.w0);
+  if (r.taxed && wi < g.w0) tc += lot_tax(g.w0 - wi, r);
+  S.obj += 0.5 * gam * wi * sig - mui * wi + tc;
+  // refinement proposal (applied only if the pattern fails)
+  int cn = c;
+  if (g.np > 1) {
+    const double tolm = A.eps_dual * 0.1;
+    if (c & 1) {
+      const int q = c >> 1;
+      if (wi > g.pt(q + 1)) cn = 2 * (q + 1);
+      else if (wi < g.pt(q)) cn = 2 * q;
+    } else {
+      // move off a point when -g lies outside its subdifferential (a fixed
+      // row's weight is its point: the interval above)
+      const int j = c >> 1;
+      const double sc = fmax(fabs(mui), 1e-12);
+      if (t > hi + tolm * sc && j + 1 < g.np) cn = 2 * j + 1;
+      else if (t < lo - tolm * sc && j > 0) cn = 2 * (j - 1) + 1;
+    }
+  }
+  S.changed += (cn != c) ? 1 : 0;
+  return cn;
 }
 
 // per-block diagnostics of the pattern's w and the refinement proposals
@@ -2063,62 +2224,18 @@ __global__ __launch_bounds__(kRT) void polish_check_rows_kernel(PolishArgs A, in
   for (int q = tid; q < 2 + G; q += kRT) mult[q] = gmult[q];
   if (tid == 0) s_ch = 0;
   CheckIn<kRR> I;
-  check_in(A, a, b * kRB, kRT, true, lbf, ubf, I);
+  check_in(A, a, tid, b * kRB, kRT, true, lbf, ubf, I);
   __syncthreads();
-  const double nu = mult[0], lam = mult[1];
-  double sw = 0.0, turn = 0.0, dmax = 0.0, box = 0.0, snapm = 0.0, obj = 0.0, bad = 0.0;
-  int changed = 0;
+  CheckSums S;
 #pragma unroll
   for (int u = 0; u < kRR; ++u) {
     const int i = I.ii[u];
     if (i >= n) continue;
-    const RowData& r = I.rd[u];
-    Geom g;
-    make_geom(g, kap, phi, r);
-    const double lb = r.lb, ub = r.ub;
-    const double wi = I.w[u];
-    const double mui = I.mu[u];
-    const double sig = (I.gb[u] + mui) / gam;
-    double gi = I.gb[u] - nu;
-    if (G) gi += rows_dot_g(A, i, I.grp[u], mult + 2);
-    double lo, hi, snap;
-    subdiff(g, wi, lam, lb, ub, lo, hi, snap);
-    const double t = -gi;
-    const double dist = fmax(fmax(lo - t, t - hi), 0.0);
-    sw += wi;
-    turn += fabs(wi - g.w0);
-    dmax = fmax(dmax, dist);
-    if (!isfinite(dist)) bad = 1.0;
-    box = fmax(box, fmax(lb - wi, wi - ub));
-    snapm = fmax(snapm, snap);
-    // objective: (gamma/2) w.Sigma w - mu w + trade cost
-    double tc = (double)kap * fabs(wi - g.w0);
-    if (r.taxed && wi < g.w0) tc += lot_tax(g.w0 - wi, r);
-    obj += 0.5 * gam * wi * sig - mui * wi + tc;
-    // refinement proposal (applied only if the pattern fails)
-    const int c = I.cc[u];
-    int cn = c;
-    if (g.np > 1) {
-      const double tolm = A.eps_dual * 0.1;
-      if (c & 1) {
-        const int q = c >> 1;
-        if (wi > g.pt(q + 1)) cn = 2 * (q + 1);
-        else if (wi < g.pt(q)) cn = 2 * q;
-      } else {
-        // move off a point when -g lies outside its subdifferential
-        const int j = c >> 1;
-        double l2, h2, sn2;
-        subdiff(g, g.pt(j), lam, lb, ub, l2, h2, sn2);
-        const double sc = fmax(fabs(mui), 1e-12);
-        if (t > h2 + tolm * sc && j + 1 < g.np) cn = 2 * j + 1;
-        else if (t < l2 - tolm * sc && j > 0) cn = 2 * (j - 1) + 1;
-      }
-    }
-    code[i] = (int8_t)cn;
-    changed += (cn != c) ? 1 : 0;
+    code[i] = (int8_t)check_row(A, i, I.cc[u], I.gb[u], I.w[u], I.mu[u], I.grp[u], I.rd[u], mult,
+                                kap, phi, gam, S);
   }
-  if (changed) atomicAdd(&s_ch, changed);
-  double sv[3] = {sw, turn, obj}, mv[4] = {dmax, box, snapm, bad};
+  if (S.changed) atomicAdd(&s_ch, S.changed);
+  double sv[3] = {S.sw, S.turn, S.obj}, mv[4] = {S.dmax, S.box, S.snapm, S.bad};
   bred<3, 4>(sv, mv, s_sh);                 // (its barriers also publish s_ch)
   if (tid == 0) {
     double* cp = A.cpart + ((size_t)a * A.n_sb + b) * 8;
@@ -2129,89 +2246,60 @@ __global__ __launch_bounds__(kRT) void polish_check_rows_kernel(PolishArgs A, in
   }
 }
 
-// per account: the diagnostics gathered in block order, the certificate,
-// and on failure the refinement of bands / cap and the row a null-direction
-// step releases (the next round's polish_rows adopts the proposals)
-__global__ __launch_bounds__(64) void polish_decide_kernel(PolishArgs A, fqp_result R,
-                                                           int final_pass) {
-  __shared__ int s_done;
-  // the constraint rows' values, bounds and multipliers (one thread walks them)
-  __shared__ double s_gs[kMaxG], s_ml[2 + kMaxG];
-  __shared__ float s_lo[kMaxG], s_hi[kMaxG];
-  const int G = A.G, tid = threadIdx.x;
-  const int slot = blockIdx.x;
-  if (slot >= *A.m_act) return;
-  const int a = A.act[slot];
-  int* ps = A.pstate + (size_t)a * kPStateStride;
-  if (ps[PS_DONE] || (ps[PS_STALL] && !final_pass)) return;
-  // lane l takes blocks l, l + 64, ... in order; then a fixed butterfly
-  double sw = 0.0, turn = 0.0, obj = 0.0, dmax = 0.0, box = 0.0, snapm = 0.0, chg = 0.0,
-         bad = 0.0;
-  for (int bb = tid; bb < A.n_sb; bb += 64) {
-    const double* cp = A.cpart + ((size_t)a * A.n_sb + bb) * 8;
-    sw += cp[0]; turn += cp[1]; obj += cp[2];
-    dmax = fmax(dmax, cp[3]); box = fmax(box, cp[4]); snapm = fmax(snapm, cp[5]);
-    chg += cp[6]; bad = fmax(bad, cp[7]);
+// the diagnostics of a pattern over its rows
+struct Diag {
+  double sw, turn, obj, dmax, box, snapm, chg;   // chg: refinement proposals
+  bool bad;                                      // something was not finite
+};
+// The certificate, and on failure the refinement of bands / cap and the row a
+// null-direction step releases (the next round's pattern adopts the
+// proposals): one wave, a constraint row a lane.  blk: the row to release or
+// -1.  Returns whether the account is certified.
+__device__ __forceinline__ bool decide_account(const PolishArgs& A, const fqp_result& R, int a,
+                                               int* ps, float tauf, const double* mult,
+                                               const double* gsum, const Diag& X, double scale,
+                                               int blk, int final_pass) {
+  const int G = A.G, lane = threadIdx.x & 63, g = min(lane, max(G - 1, 0));
+  const bool on = lane < G;
+  const double lo = on ? (double)A.blo[(size_t)a * G + g] : -INFINITY;
+  const double hi = on ? (double)A.bhi[(size_t)a * G + g] : INFINITY;
+  const double gs = on ? gsum[g] : 0.0, lg = on ? mult[2 + g] : 0.0;
+  const double nu = mult[0], lam = mult[1];
+  // comp: the largest |multiplier| x slack; gap: their sum, the duality
+  // gap the multipliers leave (with stationarity and feasibility exact,
+  // f(w) - f* <= gap)
+  const double rexp = wave_red(on ? fmax(fmax(lo - gs, gs - hi), 0.0) : 0.0, MaxOp());
+  // (a one-sided row's other slack is infinite)
+  const double pr = lg != 0.0 ? fabs(lg) * fabs(lg > 0.0 ? hi - gs : gs - lo) : 0.0;
+  double comp = fmax(wave_red(pr, MaxOp()), 0.0), gap = wave_red(pr, SumOp());
+  const double tau = tauf;
+  double rturn = 0.0;
+  if (isfinite(tauf)) {
+    rturn = fmax(X.turn - tau, 0.0);
+    comp = fmax(comp, fmax(lam, 0.0) * fabs(tau - X.turn));
+    gap += fmax(lam, 0.0) * fabs(tau - X.turn);
+  } else {
+    comp = fmax(comp, fabs(lam));
   }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    sw += __shfl_xor(sw, o, 64); turn += __shfl_xor(turn, o, 64); obj += __shfl_xor(obj, o, 64);
-    dmax = fmax(dmax, __shfl_xor(dmax, o, 64)); box = fmax(box, __shfl_xor(box, o, 64));
-    snapm = fmax(snapm, __shfl_xor(snapm, o, 64)); chg += __shfl_xor(chg, o, 64);
-    bad = fmax(bad, __shfl_xor(bad, o, 64));
-  }
-  const float* par = A.par + (size_t)a * kNPar;
-  const float tauf = par[P_TAU];
-  const double* gmult = A.mult + (size_t)a * (2 + G);
-  const Wk wkc = wk_of(A, a);
-  for (int g = tid; g < G; g += 64) {
-    s_gs[g] = wkc.gsum[g];
-    s_lo[g] = A.blo[(size_t)a * G + g];
-    s_hi[g] = A.bhi[(size_t)a * G + g];
-  }
-  for (int g = tid; g < 2 + G; g += 64) s_ml[g] = gmult[g];
-  const double* mult = s_ml;
-  int8_t* code = A.code_next + (size_t)a * A.n;
-  __syncthreads();
-  if (tid == 0) {
-    const double scale = wkc.misc[0];
-    const bool s_bad = wkc.misc[2] != 0.0 || bad != 0.0;
-    const double nu = mult[0], lam = mult[1];
-    // comp: the largest |multiplier| x slack; gap: their sum, the duality
-    // gap the multipliers leave (with stationarity and feasibility exact,
-    // f(w) - f* <= gap)
-    double rexp = 0.0, comp = 0.0, gap = 0.0;
-    for (int g = 0; g < G; ++g) {
-      const double lo = s_lo[g], hi = s_hi[g];
-      rexp = fmax(rexp, fmax(lo - s_gs[g], s_gs[g] - hi));
-      const double lg = mult[2 + g];
-      if (lg != 0.0) {              // (a one-sided row's other slack is infinite)
-        const double slack = (lg > 0.0) ? hi - s_gs[g] : s_gs[g] - lo;
-        comp = fmax(comp, fabs(lg) * fabs(slack));
-        gap += fabs(lg) * fabs(slack);
-      }
-    }
-    const double tau = tauf;
-    double rturn = 0.0;
-    if (isfinite(tauf)) {
-      rturn = fmax(turn - tau, 0.0);
-      comp = fmax(comp, fmax(lam, 0.0) * fabs(tau - turn));
-      gap += fmax(lam, 0.0) * fabs(tau - turn);
-    } else {
-      comp = fmax(comp, fabs(lam));
-    }
-    const double obj_full = obj + (A.obj_const ? A.obj_const[a] : 0.0);
-    const double r_prim = fmax(fmax(fabs(sw - 1.0), fmax(box, 0.0)), fmax(rexp, rturn)) + snapm;
-    const double r_dual = fmax(dmax, fmax(-lam, 0.0)) / scale;
-    const double r_comp = comp / scale;
-    const bool finite = !s_bad && isfinite(sw) && isfinite(obj) && isfinite(nu) &&
-                        isfinite(lam) && isfinite(r_prim) && isfinite(r_dual) &&
-                        isfinite(r_comp);
-    // the certificate also bounds the relative objective error: the gap
-    // against |f| (when |f| is below the gradient scale, as a benchmark term
-    // can make it, r_comp <= eps alone does not)
-    const bool ok = finite && r_prim <= A.eps_prim && r_dual <= A.eps_dual &&
-                    r_comp <= A.eps_comp && gap <= A.eps_comp * fmax(fabs(obj_full), 1e-12);
+  const double obj_full = X.obj + (A.obj_const ? A.obj_const[a] : 0.0);
+  const double r_prim = fmax(fmax(fabs(X.sw - 1.0), fmax(X.box, 0.0)), fmax(rexp, rturn)) + X.snapm;
+  const double r_dual = fmax(X.dmax, fmax(-lam, 0.0)) / scale;
+  const double r_comp = comp / scale;
+  const bool finite = !X.bad && isfinite(X.sw) && isfinite(X.obj) && isfinite(nu) &&
+                      isfinite(lam) && isfinite(r_prim) && isfinite(r_dual) &&
+                      isfinite(r_comp);
+  // the certificate also bounds the relative objective error: the gap
+  // against |f| (when |f| is below the gradient scale, as a benchmark term
+  // can make it, r_comp <= eps alone does not)
+  const bool ok = finite && r_prim <= A.eps_prim && r_dual <= A.eps_dual &&
+                  r_comp <= A.eps_comp && gap <= A.eps_comp * fmax(fabs(obj_full), 1e-12);
+  // bands to drop or to take up
+  const bool act = on && band_active(ps, g), up = on && band_upper(ps, g);
+  const unsigned long long drop = __ballot(act && ((up && lg < 0.0) || (!up && lg > 0.0)));
+  const bool above = on && !act && gs > hi + 0.1 * A.eps_prim;
+  const unsigned long long add_hi = __ballot(above);
+  const unsigned long long add_lo = __ballot(on && !act && !above && gs < lo - 0.1 * A.eps_prim);
+  if (lane == 0) {
     ps[PS_ROUNDS] += 1;
     // keep the diagnostics of the latest pattern in the result arrays
     if (ok || final_pass) {
@@ -2223,34 +2311,31 @@ __global__ __launch_bounds__(64) void polish_decide_kernel(PolishArgs A, fqp_res
       if (R.nu) R.nu[a] = nu;
       if (R.lam_cap) R.lam_cap[a] = lam;
     }
-    s_done = ok ? 1 : 0;
     if (ok) {
       ps[PS_DONE] = 1;
       R.status[a] = FQP_SOLVED;
     } else if (final_pass) {
       // the paper's quality gates (Sec. "Quality Gates and Failure
       // Vocabulary"): budget <= 1e-4 and bound violation <= 1e-6
-      const bool gates = fabs(sw - 1.0) <= 1e-4 && box <= 1e-6 && rexp <= 1e-6 && rturn <= 1e-6;
+      const bool gates =
+          fabs(X.sw - 1.0) <= 1e-4 && X.box <= 1e-6 && rexp <= 1e-6 && rturn <= 1e-6;
       R.status[a] = gates ? FQP_FEASIBLE_UNCERTIFIED : FQP_MAX_ITER;
     } else {
       // bands / cap refinement
-      int nchg = (int)chg;
-      const int blk = ps[PS_BLOCK];
+      int nchg = (int)X.chg;
       if (blk >= 0) {                    // release the row that blocks
-        code[blk >> 4] = (int8_t)(blk & 15);
+        A.code_next[(size_t)a * A.n + (blk >> 4)] = (int8_t)(blk & 15);
         ++nchg;
       }
-      for (int g = 0; g < G; ++g) {
-        const double lo = s_lo[g], hi = s_hi[g];
-        const bool act = band_active(ps, g), up = band_upper(ps, g);
-        const double lg = mult[2 + g];
-        if (act && ((up && lg < 0.0) || (!up && lg > 0.0))) { set_band(ps, g, false, false); ++nchg; }
-        else if (!act && s_gs[g] > hi + 0.1 * A.eps_prim) { set_band(ps, g, true, true); ++nchg; }
-        else if (!act && s_gs[g] < lo - 0.1 * A.eps_prim) { set_band(ps, g, true, false); ++nchg; }
-      }
+      nchg += __popcll(drop) + __popcll(add_hi) + __popcll(add_lo);
+      const unsigned long long added = add_hi | add_lo;
+      ps[PS_BACT0] = (ps[PS_BACT0] & ~(int)(unsigned)drop) | (int)(unsigned)added;
+      ps[PS_BACT1] = (ps[PS_BACT1] & ~(int)(drop >> 32)) | (int)(added >> 32);
+      ps[PS_BUP0] = (ps[PS_BUP0] & ~(int)(unsigned)(drop | add_lo)) | (int)(unsigned)add_hi;
+      ps[PS_BUP1] = (ps[PS_BUP1] & ~(int)((drop | add_lo) >> 32)) | (int)(add_hi >> 32);
       if (isfinite(tauf)) {
         if (ps[PS_CAP] && lam < 0.0) { ps[PS_CAP] = 0; ++nchg; }
-        else if (!ps[PS_CAP] && turn > tau + 0.1 * A.eps_prim) { ps[PS_CAP] = 1; ++nchg; }
+        else if (!ps[PS_CAP] && X.turn > tau + 0.1 * A.eps_prim) { ps[PS_CAP] = 1; ++nchg; }
       }
       // no proposal: further rounds on this iterate cannot help; many
       // proposals: the iterate is still far from its final pattern, and the
@@ -2258,9 +2343,159 @@ __global__ __launch_bounds__(64) void polish_decide_kernel(PolishArgs A, fqp_res
       if (nchg == 0 || nchg > A.max_prop) ps[PS_STALL] = 1;
     }
   }
+  if ((final_pass || ok) && R.lam_band && on) R.lam_band[(size_t)a * G + g] = lg;
+  return ok;
+}
+
+// per account: the diagnostics gathered in block order, the certificate and
+// the refinement
+__global__ __launch_bounds__(64) void polish_decide_kernel(PolishArgs A, fqp_result R,
+                                                           int final_pass) {
+  const int G = A.G, tid = threadIdx.x;
+  const int slot = blockIdx.x;
+  if (slot >= *A.m_act) return;
+  const int a = A.act[slot];
+  int* ps = A.pstate + (size_t)a * kPStateStride;
+  if (ps[PS_DONE] || (ps[PS_STALL] && !final_pass)) return;
+  // lane l takes blocks l, l + 64, ... in order, then the wave's reduction
+  double sw = 0.0, turn = 0.0, obj = 0.0, dmax = 0.0, box = 0.0, snapm = 0.0, chg = 0.0,
+         bad = 0.0;
+  for (int bb = tid; bb < A.n_sb; bb += 64) {
+    const double* cp = A.cpart + ((size_t)a * A.n_sb + bb) * 8;
+    sw += cp[0]; turn += cp[1]; obj += cp[2];
+    dmax = fmax(dmax, cp[3]); box = fmax(box, cp[4]); snapm = fmax(snapm, cp[5]);
+    chg += cp[6]; bad = fmax(bad, cp[7]);
+  }
+  const Wk wkc = wk_of(A, a);
+  Diag X;
+  X.sw = wave_red(sw, SumOp());
+  X.turn = wave_red(turn, SumOp());
+  X.obj = wave_red(obj, SumOp());
+  X.dmax = wave_red(dmax, MaxOp());
+  X.box = wave_red(box, MaxOp());
+  X.snapm = wave_red(snapm, MaxOp());
+  X.chg = wave_red(chg, SumOp());
+  X.bad = wkc.misc[2] != 0.0 || wave_red(bad, MaxOp()) != 0.0;
+  decide_account(A, R, a, ps, A.par[(size_t)a * kNPar + P_TAU], A.mult + (size_t)a * (2 + G),
+                 wkc.gsum, X, wkc.misc[0], ps[PS_BLOCK], final_pass);
+}
+
+// ---------------------------------------------------------------------------
+// A whole certification pass of one account in one workgroup: the rounds of
+// the passes above, back to back, with the account's bookkeeping in LDS.
+// A round of separate launches is bound by what lies between the phases: on a
+// book of 64 x 2,000 with every rule its eight kernels take 101 us, of which the
+// solve is 33, the gaps between them come on top, every round waits for the
+// slowest account, and the host reads a count back between rounds.  Here a
+// round is 55 us: 27 the solve (serial steps of one wave), the rest the
+// instructions of 16 waves over 2,000 rows.
+// Same arithmetic in the same order as the row-block passes (their sums over
+// rows differ in rounding only).
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kPT) void polish_pass_kernel(PolishArgs A, fqp_result R, int rounds,
+                                                          const float4* Bq) {
+  extern __shared__ double smem_d[];
+  __shared__ AcctLds W;
+  __shared__ StepRows SR;
+  __shared__ double s_red[3 * kPW];
+  __shared__ double4 s_sum4[kPT / 16], s_max4[kPT / 16];
+  double *const s_sum = &s_sum4[0].x, *const s_max = &s_max4[0].x;
+  __shared__ int s_ps[kPStateStride], s_same, s_block, s_key[2], s_flag;
+  const int n = A.n, k = A.k, G = A.G;
+  const int slot = blockIdx.x;
+  if (slot >= *A.m_act) return;
+  const int a = A.act[slot];
+  int* ps = A.pstate + (size_t)a * kPStateStride;
+  const float* par = A.par + (size_t)a * kNPar;
+  const float lbf = par[P_LB], ubf = par[P_UB], kap = par[P_KAPPA], tauf = par[P_TAU];
+  const double gam = par[P_GAMMA];
+  const bool phi = (kap > 0.f) || isfinite(tauf) || (par[P_HASTAX] != 0.f);
+  const Wk wk = wk_of(A, a);
+  const size_t off = (size_t)a * n;
+  const int k4 = (k + 3) >> 2;
+  if (threadIdx.x < kPStateStride) s_ps[threadIdx.x] = ps[threadIdx.x];
   __syncthreads();
-  if ((final_pass || s_done) && R.lam_band && G)
-    for (int g = tid; g < G; g += 64) R.lam_band[(size_t)a * G + g] = mult[2 + g];
+  for (int r = 0;; ++r) {
+    const int first = r == 0;
+    // what depends on the thread is formed anew each round (kept across the
+    // rounds it would not fit the registers)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    if (first) begin_pass(A, a, par, s_ps, W.mult);
+    // ---- the pattern, kPT / kRT row blocks at a time
+    RowsLds* L = reinterpret_cast<RowsLds*>(smem_d) + tid / kRT;
+    for (int b0 = 0; b0 < A.n_sb; b0 += kPT / kRT) {
+      const int b = b0 + tid / kRT;
+      rows_block(A, a, b < A.n_sb ? b : -1, tid % kRT, first, *L);
+      __syncthreads();
+    }
+    const PatternSums X = gather_pattern(A, a, tid, first, smem_d, W);
+    if (gated(A, first, s_ps, X, &s_same)) break;             // uniform
+    const double turn0 = solve_pattern(A, a, tid, par, s_ps, X, smem_d, W);
+    if (tid < 4 * k4 - k) W.yF[k + tid] = 0.0;
+    __syncthreads();
+    // ---- gradient base: a row a thread, B~ by columns of four (coalesced)
+    double gmax = 0.0, mumax = 0.0, bad = 0.0;
+    for (int i = tid; i < n; i += kPT) {
+      const double wi = A.wout[off + i], mui = mu_at(A, off + i), di = (double)A.d[i];
+      double sig = 0.0;
+#pragma unroll 4
+      for (int j = 0; j < k4; ++j) {
+        const float4 b = Bq[(size_t)j * n + i];
+        const double* y = W.yF + 4 * j;
+        sig += (double)b.x * y[0] + (double)b.y * y[1] + (double)b.z * y[2] + (double)b.w * y[3];
+      }
+      const double sg = sig + di * wi;
+      const double v = gam * sg - mui;
+      A.gbase[off + i] = v;
+      gmax = fmax(gmax, fabs(gam * sg));
+      mumax = fmax(mumax, fabs(mui));
+      if (!isfinite(v) || !isfinite(wi)) bad = 1.0;
+    }
+    // ---- the gradient scale, the multipliers the free rows leave open
+    step_bounds(A, a, W.gsum, SR);
+    if (tid == 0) s_block = -1;
+    double gv[4] = {gmax, mumax, bad, 0.0};   // (of use to the first wave only)
+    put_red4(gv, s_sum, MaxOp());
+    __syncthreads();                          // (also publishes SR)
+    if (tid < 64) get_red4(gv, s_sum, MaxOp());
+    const double scale = fmax(fmax(gv[0], gv[1]), 1e-12);
+    const int nd = s_ps[PS_ND];
+    const double thr = 0.01 * A.eps_comp * scale;
+    for (int q = 0; q < nd; ++q)
+      sweep_one(A, a, tid, s_ps, wk.nul + q * (G + 3), lbf, ubf, kap, phi, thr, turn0, tauf, W.mult, SR,
+                s_red, s_key, &s_block);
+    // ---- diagnostics and proposals
+    CheckSums S;
+    for (int base = 0; base < n; base += kPU * kPT) {
+      CheckIn<kPU> I;
+      check_in(A, a, tid, base, kPT, true, lbf, ubf, I);
+#pragma unroll
+      for (int u = 0; u < kPU; ++u) {
+        if (I.ii[u] >= n) continue;
+        A.code_next[off + I.ii[u]] = (int8_t)check_row(A, I.ii[u], I.cc[u], I.gb[u], I.w[u], I.mu[u],
+                                                       I.grp[u], I.rd[u], W.mult, kap, phi, gam, S);
+      }
+    }
+    double sv[4] = {S.sw, S.turn, S.obj, (double)S.changed}, mv[4] = {S.dmax, S.box, S.snapm, S.bad};
+    put_red4(sv, s_sum, SumOp());
+    put_red4(mv, s_max, MaxOp());
+    __syncthreads();
+    if (tid < 64) {
+      get_red4(sv, s_sum, SumOp());
+      get_red4(mv, s_max, MaxOp());
+      Diag D;
+      D.sw = sv[0]; D.turn = sv[1]; D.obj = sv[2]; D.chg = sv[3];
+      D.dmax = mv[0]; D.box = mv[1]; D.snapm = mv[2];
+      D.bad = gv[2] != 0.0 || mv[3] != 0.0;
+      decide_account(A, R, a, s_ps, tauf, W.mult, W.gsum, D, scale, s_block, 0);
+      if (tid == 0) s_flag = s_ps[PS_DONE] || s_ps[PS_STALL];
+    }
+    __syncthreads();
+    if (s_flag || r + 1 == rounds) break;                     // uniform
+  }
+  // for the adjoint and the next pass
+  if (threadIdx.x < kPStateStride) ps[threadIdx.x] = s_ps[threadIdx.x];
 }
 
 static size_t polish_smem(int k, int G, int n_sb) {
@@ -2280,6 +2515,35 @@ static size_t polish_smem(int k, int G, int n_sb) {
   const size_t gather = sizeof(double) * kPT + sizeof(int) * 2 * ((size_t)n_sb + 1);
   const size_t both = factor > rows ? factor : rows;
   return both > gather ? both : gather;
+}
+
+static size_t pass_smem(int k, int G, int n_sb) {
+  const size_t rows = sizeof(RowsLds) * (kPT / kRT);
+  const size_t solve = polish_smem(k, G, n_sb);
+  return solve > rows ? solve : rows;
+}
+
+// One workgroup walks an account's rows where the launches between phases
+// cost more than the rows: polish times of two books each, row-block passes
+// against this one: 64 x 2,000 9.4 ms : 5.8, 1,000 x 2,000 21.9 : 15.1,
+// 3,000 x 500 32.8 : 22.2, 64 x 5,000 17.8 : 17.0, 128 x 5,000 8.8 : 8.6; beyond,
+// 300 x 6,000 4.5 : 4.9, 16 x 8,000 8.8 : 10.3, 500 x 10,000 8.3 : 13.9.  The
+// number of accounts does not move the line.
+constexpr int kPassRows = 10 * kRB;
+bool polish_pass_fits(int n, int k, int G) {
+  if (pass_smem(k, G, polish_pass_blocks(n)) > 144 * 1024) return false;   // 16 KB are its own
+  return n <= kPassRows;
+}
+
+hipError_t launch_polish_pass(const PolishArgs& A, const fqp_result& R, int rounds, const float* Bq,
+                              hipStream_t st) {
+  const size_t smem = pass_smem(A.k, A.G, A.n_sb);
+  hipError_t e = hipFuncSetAttribute((const void*)polish_pass_kernel,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(polish_pass_kernel, dim3(A.m_total), dim3(kPT), smem, st, A, R, rounds,
+                     reinterpret_cast<const float4*>(Bq));
+  return hipGetLastError();
 }
 
 hipError_t launch_polish_solve(const PolishArgs& A, hipStream_t st) {

@@ -27,6 +27,8 @@
 namespace fqp {
 hipError_t launch_polish_check_r(const PolishArgs& A, const fqp_result& R, int final_pass,
                                  hipStream_t st);
+hipError_t launch_polish_pass(const PolishArgs& A, const fqp_result& R, int rounds, const float* Bq,
+                              hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // small bookkeeping kernels
@@ -688,6 +690,9 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   WS(rpart, double, "polish_rpart", (size_t)m * n_sb * polish_rpart_stride(k, G));
   WS(spart, double, "polish_spart", (size_t)m * n_sb * 4);
   WS(cpart, double, "polish_cpart", (size_t)m * n_sb * 8);
+  // a certification pass by one workgroup per account reads B~ by columns
+  const bool one_wg = polish_pass_fits(n, k, G);
+  WS(bq_p, float, "polish_bq", one_wg ? (size_t)n * 4 * ((k + 3) / 4) : 1);
   // the rest of Eq. 1: bounds of every constraint row [m][G] (bands, then
   // halfspaces); mu' = eta mu + gamma Sigma w_b and the constant of the
   // benchmark term when the book has a benchmark or a return scale
@@ -743,7 +748,8 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   std::copy(rho_cls.begin(), rho_cls.end(), rho_stage);
   HIP_CHECK(hipMemcpyAsync(rho_d, rho_stage, sizeof(float) * ncls, hipMemcpyHostToDevice, st));
   HIP_CHECK(hipMemcpyAsync(cls_d, cls_h, sizeof(int) * m, hipMemcpyHostToDevice, st));
-  HIP_CHECK(launch_build_bt(n, k, Gl, H, kp, U->B, U->group, U->half, Bt, st));
+  HIP_CHECK(launch_build_bt(n, k, Gl, H, kp, U->B, U->group, U->half, Bt,
+                            one_wg ? bq_p : nullptr, st));
   if (concat_rows)
     HIP_CHECK(launch_concat_rows(m, Gl, H, P->band_lo, P->band_hi, P->half_lo, P->half_hi,
                                  rlo_ws, rhi_ws, st));
@@ -873,6 +879,7 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   pa.n = n; pa.k = k; pa.G = G; pa.Gl = Gl; pa.kp = kp; pa.W = W; pa.m_total = m;
   pa.m_act = m_act;
   pa.act = act; pa.Bt = Bt; pa.f = U->f; pa.d = U->d; pa.group = Gl ? U->group : nullptr;
+  pa.half = H ? U->half : nullptr;
   pa.lbv = P->lb_asset; pa.ubv = P->ub_asset; pa.obj_const = bench ? obj_c : nullptr;
   pa.mu64 = bench ? mu_b64 : nullptr;
   pa.mu = mu_use; pa.z = z; pa.elig = P->eligible; pa.hold = hold; pa.hold_pre = hold_pre;
@@ -1041,7 +1048,11 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
     pa.nf_gate = std::max(4 * k + 64, n / 8 + 4 * k);
     pa.nf_small = 2 * k + 32;
     pa.max_prop = 16;
-    for (int r = 0; r < S.polish_rounds; ++r) {
+    if (one_wg) {
+      HIP_CHECK(launch_polish_pass(pa, *R, S.polish_rounds, bq_p, st));
+      h->stats.polish_calls += 1;
+    }
+    for (int r = 0; !one_wg && r < S.polish_rounds; ++r) {
       pa.first_round = (r == 0);
       // later rounds: only the accounts still refining; the list kernel also
       // stores their count to pinned host memory, and the host stops

@@ -1,6 +1,7 @@
 """GPU tests of the active-set refinement at the edges of its solves: the
 constraint system in one wave's lanes and above them, panels of the
-factorisation, free sets on either side of the row-space solve."""
+factorisation, free sets on either side of the row-space solve, the rows of a
+pass by one workgroup."""
 import pytest
 
 from workloads import make_config
@@ -29,6 +30,19 @@ CASES = [
          gamma=1000.0, ub=0.05),
 ]
 
+# the rows of one workgroup's pass: a handful, around its blocks of 512 and its
+# 1,024 threads, the largest it takes and the first it leaves to the row blocks
+SIZES = [
+    ("c2", dict(N=3, M=2, k=1, groups=0, band_halfwidth=None, ub=0.6)),
+    ("c2", dict(N=65, M=2, k=3, groups=4, ub=0.2)),
+    ("c5", dict(N=511, M=2, k=30, groups=7, band_halfwidth=1e-3, ub=0.03, held=(60, 90))),
+    ("c5", dict(N=1025, M=2, k=33, groups=7, band_halfwidth=1e-3, ub=0.02, held=(60, 90),
+                halfspaces=5, asset_bounds=True, benchmark=True, elig=(0.5, 1.0))),
+    ("c3", dict(N=2049, M=2, k=20, ub=0.02)),
+    ("c5", dict(N=5120, M=2, k=40, groups=10, band_halfwidth=1e-3, ub=0.01, held=(100, 200))),
+    ("c5", dict(N=5121, M=2, k=40, groups=10, band_halfwidth=1e-3, ub=0.01, held=(100, 200))),
+]
+
 
 @pytest.mark.parametrize("over", CASES)
 def test_against_the_oracle(over):
@@ -38,4 +52,13 @@ def test_against_the_oracle(over):
     # (the accounts the oracle itself solves to 1e-11 and the iteration settles
     # within max_iter)
     for a in (1,) if over["groups"] == 44 else (0, 1):
+        check_account(uni, book, a, host)
+
+
+@pytest.mark.parametrize("name,over", SIZES)
+def test_rows_of_a_pass(name, over):
+    uni, book = make_config(name, 44, **over)
+    print(f"case {name} {over}", flush=True)
+    host, _ = run_gpu(uni, book, rho=10.0, max_iter=4000)
+    for a in range(2):
         check_account(uni, book, a, host)
