@@ -170,10 +170,12 @@ hipError_t launch_resident(const ResArgs& A, int KQ, int m_total, int count, hip
 
 // ---- fused pass of wide books (fqp_wide.hip) -----------------------------------
 struct WideArgs {
-  int n, W, kp, m_total;
+  int n, W, k, kp, m_total;
+  int kc, Gl, one;           // columns of B~ in Bp (wide_cols), bands, the column of ones
+  const int32_t* group;      // [n] labels (with bands)
   const int* m_act;
   const int* act;
-  const float* Bp;           // [rows padded to whole 128-row chunks][kp], columns permuted
+  const float* Bp;           // the columns in memory, by 128-row chunks (wide_perm_kernel)
   const float* d;
   const float* mu;
   const float* lbv;          // [m][n] per-asset bounds or null
@@ -190,7 +192,9 @@ struct WideArgs {
   float* part;               // [row tiles][m][kp]
 };
 bool wide_fits(int n, int kp, int m, int ncap, bool split);
-hipError_t launch_wide_setup(int n, int kp, const float* Bt, float* Bp, hipStream_t st);
+int wide_columns(int k, int kp, int H);
+hipError_t launch_wide_setup(int n, int k, int kp, int H, const float* Bt, float* Bp,
+                             hipStream_t st);
 // one launch of an iteration block over nblk row tiles: do_x applies the last
 // factor-space solve, do_p takes the prox step and contracts (else v and z
 // are written)

@@ -798,7 +798,7 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   const int KQ = resident ? resident_kq(kg + 1) : 0;
   const int ntile = (n + 63) / 64, npr = 64 * ntile;
   WS(Bq, float4, "Bq", resident ? (size_t)ntile * KQ * 64 : 1);
-  WS(Bp, float, "Bp", wide ? (size_t)npad_r * kp : 1);
+  WS(Bp, float, "Bp", wide ? (size_t)npad_r * wide_columns(k, kp, H) : 1);
   WS(rows, float4, "res_rows", resident ? (size_t)m * npr : 1);
   WS(lot, int32_t, "res_lot", resident && lots ? (size_t)m * npr : 1);
   HIP_CHECK(launch_pack_rec(pk, hold_rec, n_held, st));
@@ -819,7 +819,9 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
     ra.cvec = cvec; ra.qvec = qvec; ra.sig1 = sig1; ra.mbg = mbg; ra.zb = zb; ra.vb = vb;
     ra.blo = rlo; ra.bhi = rhi; ra.iters = iters;
   } else if (wide) {
-    HIP_CHECK(launch_wide_setup(n, kp, Bt, Bp, st));
+    HIP_CHECK(launch_wide_setup(n, k, kp, H, Bt, Bp, st));
+    wa.k = k; wa.kc = wide_columns(k, kp, H); wa.Gl = Gl; wa.one = k + G;
+    wa.group = Gl ? U->group : nullptr;
     wa.n = n; wa.W = W; wa.kp = kp; wa.m_total = m; wa.m_act = m_act; wa.act = act; wa.Bp = Bp;
     wa.d = U->d; wa.mu = mu_use; wa.lbv = P->lb_asset; wa.ubv = P->ub_asset;
     wa.elig = P->eligible; wa.hold = hold; wa.hold_pre = hold_pre; wa.hold_ptr = hold_ptr;

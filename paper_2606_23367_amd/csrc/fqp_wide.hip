@@ -19,14 +19,17 @@
 // 512 threads: wave w takes rows 16 w .. 16 w + 15 of a chunk through the
 // back-projection and the prox step, then strip w / 2 (32 rows) and half
 // w % 2 of the columns through the contraction.  The next chunk is loaded into
-// registers while the current one is worked on (80 KB in flight a compute
+// registers while the current one is worked on (50 to 80 KB in flight a compute
 // unit).  Columns are stored permuted within groups of 16 (column 4 i + j at
 // 4 j + i), so that four k-steps of the back-projection's operand are one
 // 16-byte LDS read; rows are kp + 4 words apart (those reads are free of bank
 // conflicts).
 //
-// Bound by the HBM stream of B~: 246 MB at 384,800 x 160, 47 us at the rate of
-// a large copy.
+// Bound by the phases of a chunk, one workgroup a compute unit: of 5.7 us at
+// 8 x 384,800 x 160 the back-projection is 2.1 (1.1 of it the matrix pipe), the
+// prox step 1.2, the contraction 0.7, the chunk's way into LDS 0.5 and the three
+// barriers 1.2; no wave waits for memory.  84 us a launch with every column
+// streamed and the rows' own data loaded after the back-projection, 77 now.
 #include "fqp_common.h"
 #include "fqp_kernels.h"
 #include "../../include/fqp.h"
@@ -43,12 +46,35 @@ __host__ __device__ __forceinline__ int wide_pos(int col) {
   return (col & ~15) + 4 * (col & 3) + ((col >> 2) & 3);
 }
 
-__global__ __launch_bounds__(256) void wide_perm_kernel(int n, int npad, int kp, const float* Bt,
-                                                        float* Bp) {
-  const size_t total = (size_t)npad * kp;
+// Columns of B~ kept in memory: without halfspace rows the factor columns (in
+// fours), as the one-hot band columns follow from the labels and the last
+// column is 1; else all of them.  That is 154 MB instead of 246 at 384,800 x (100
+// factors + 50 bands): a third less to stream, and it stays in the 256 MB
+// last-level cache from one iteration to the next.
+__host__ __device__ __forceinline__ int wide_cols(int k, int kp, int H) {
+  return H > 0 ? kp : (k + 3) & ~3;
+}
+
+// Bp, per 128-row chunk: [whole groups of 16 columns][128 rows][16, permuted],
+// then [fours of columns left][128 rows][4]
+__global__ __launch_bounds__(256) void wide_perm_kernel(int n, int npad, int kp, int kc,
+                                                        const float* Bt, float* Bp) {
+  const size_t total = (size_t)npad * kc;
+  const int per = kRowsPerChunk * kc, full = (kc >> 4) * kRowsPerChunk * 16;
   for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (size_t)gridDim.x * 256) {
-    const int row = (int)(e / kp), p = (int)(e % kp);
-    const int col = (p & ~15) + 4 * (p & 3) + ((p >> 2) & 3);   // the permutation is its own inverse
+    const int ch = (int)(e / per), x = (int)(e % per);
+    int rr, col;
+    if (x < full) {
+      const int p = x & 15;
+      rr = (x >> 4) % kRowsPerChunk;
+      // (the permutation is its own inverse)
+      col = (x >> 4) / kRowsPerChunk * 16 + 4 * (p & 3) + (p >> 2);
+    } else {
+      const int y = x - full;
+      rr = (y >> 2) % kRowsPerChunk;
+      col = (kc & ~15) + (y >> 2) / kRowsPerChunk * 4 + (y & 3);
+    }
+    const int row = ch * kRowsPerChunk + rr;
     Bp[e] = row < n ? Bt[(size_t)row * kp + col] : 0.f;
   }
 }
@@ -56,7 +82,6 @@ __global__ __launch_bounds__(256) void wide_perm_kernel(int n, int npad, int kp,
 template <int NT>                         // kp = 16 NT
 __global__ __launch_bounds__(kWdT) void wide_kernel(WideArgs A, int do_x, int do_p) {
   constexpr int kp = 16 * NT, S = kp + 4, NH = NT / 2;
-  constexpr int F4 = kRowsPerChunk * kp / 4 / kWdT;             // float4 loads a thread and chunk
   extern __shared__ float smem[];
   float* Bs = smem;                                             // [128][S]
   float* Rs = Bs + kRowsPerChunk * S;                           // [128][16] R'
@@ -70,7 +95,11 @@ __global__ __launch_bounds__(kWdT) void wide_kernel(WideArgs A, int do_x, int do
   const int l16 = lane & 15, q4 = lane >> 4;
   const int n = A.n;
   if (tid < kWdAcc) {
-    const int a = tid < m_act ? A.act[tid] : -1;
+    // MFMA row 4 q + r takes the list's account 4 r + q: a lane's four rows are
+    // filled one after another over all lanes, so that few accounts take few
+    // rounds of the prox step (1.75 us a chunk for four rounds, of 5.8)
+    const int j = 4 * (tid & 3) + (tid >> 2);
+    const int a = j < m_act ? A.act[j] : -1;
     Aid[tid] = a;
     Hp[tid] = a >= 0 ? A.hold_ptr[a] : 0;
     float4 c0 = make_float4(1.f, 1.f, 0.f, 0.f), c1 = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -84,7 +113,8 @@ __global__ __launch_bounds__(kWdT) void wide_kernel(WideArgs A, int do_x, int do
     Acc[2 * tid + 1] = c1;
   }
   __syncthreads();
-  // p of account l16, columns 4 s + q4
+  const int rounds = (m_act + 3) >> 2;                          // of the lanes' accounts (uniform)
+  // p of MFMA row l16, columns 4 s + q4
   float p[kp / 4];
   {
     const int a = Aid[l16];
@@ -100,41 +130,79 @@ __global__ __launch_bounds__(kWdT) void wide_kernel(WideArgs A, int do_x, int do
   const float* src = do_x ? A.zs : A.v;
   // the row tile's chunks; the first one's loads
   const int c_end = min(tm.chunks, (n - tm.row_begin + kRowsPerChunk - 1) / kRowsPerChunk);
-  floatx4 buf[F4];
+  // a chunk: a float4 a thread of each whole group of 16 columns (row tid / 4),
+  // one of a four of columns left (row tid % 128), the label of row tid
+  static_assert(4 * kRowsPerChunk == kWdT, "a group of 16 columns is a float4 a thread");
+  const int kc = A.kc, fg = kc >> 4, pq = (kc & 15) >> 2;       // uniform
+  const int pr = tid & (kRowsPerChunk - 1), pi = tid >> 7;      // row and four of the columns left
+  floatx4 buf[NT], left;
+  int label = -1;
+  // the wave's rows 16 w + l16 of the chunk, accounts 4 q4 + r
+  float d_n = 1.f, sv_n[4] = {}, mu_n[4] = {};
+  uint32_t ew_n[4] = {}, hw_n[4] = {};
+  int hp_n[4] = {};
   auto fetch = [&](int ch) {
-    const floatx4* g = reinterpret_cast<const floatx4*>(A.Bp) +
-                      (size_t)(tm.row_begin + ch * kRowsPerChunk) * (kp / 4);
+    const int row0 = tm.row_begin + ch * kRowsPerChunk;
+    const floatx4* g = reinterpret_cast<const floatx4*>(A.Bp) + (size_t)row0 * (kc >> 2);
 #pragma unroll
-    for (int u = 0; u < F4; ++u) buf[u] = g[u * kWdT + tid];
+    for (int u = 0; u < NT; ++u)
+      if (u < fg) buf[u] = g[u * kWdT + tid];
+    // (threads without one read the first: no branch around a load in flight)
+    left = g[pi < pq ? fg * kWdT + tid : 0];
+    if (A.group) label = A.group[min(row0 + pr, n - 1)];         // uniform
+    const int rc = min(row0 + 16 * w + l16, n - 1);
+    d_n = A.d[rc];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (r >= rounds) break;                                   // uniform
+      const int a = max(Aid[4 * q4 + r], 0);                    // (an empty slot reads account 0)
+      const size_t off = (size_t)a * n + rc, wi = (size_t)a * A.W + (rc >> 5);
+      sv_n[r] = src[off];
+      mu_n[r] = A.mu[off];
+      ew_n[r] = A.elig ? A.elig[wi] : 0xffffffffu;
+      hw_n[r] = A.hold[wi];
+      hp_n[r] = A.hold_pre[wi];
+    }
   };
+  // the columns not in memory: bands from the labels as chunks pass, the column
+  // of ones (rows past n have R' = 0 and no output)
+  if (kc < kp)
+    for (int e = tid; e < kRowsPerChunk * (kp - kc); e += kWdT) {
+      const int col = kc + e % (kp - kc);
+      Bs[e / (kp - kc) * S + wide_pos(col)] = col == A.one ? 1.f : 0.f;
+    }
+  int hot = -1;                             // row tid's one, from the last chunk
   if (c_end > 0) fetch(0);
   for (int ch = 0; ch < c_end; ++ch) {
     const int r0 = tm.row_begin + ch * kRowsPerChunk;
     __syncthreads();                                            // the last chunk's reads are done
 #pragma unroll
-    for (int u = 0; u < F4; ++u) {
-      const int e = u * kWdT + tid, rr = e / (kp / 4), c4 = e % (kp / 4);
-      *reinterpret_cast<floatx4*>(Bs + rr * S + 4 * c4) = buf[u];
+    for (int u = 0; u < NT; ++u)
+      if (u < fg) *reinterpret_cast<floatx4*>(Bs + (tid >> 2) * S + 16 * u + 4 * (tid & 3)) = buf[u];
+    if (pi < pq) {
+      float* b = Bs + pr * S + 16 * fg + pi;
+      b[0] = left.x; b[4] = left.y; b[8] = left.z; b[12] = left.w;
+    }
+    if (kc < kp && tid < kRowsPerChunk) {
+      float* b = Bs + tid * S;
+      if (hot >= 0) b[hot] = 0.f;
+      const int col = A.k + label;
+      hot = label >= 0 && label < A.Gl && col >= kc ? wide_pos(col) : -1;
+      if (hot >= 0) b[hot] = 1.f;
     }
     __syncthreads();
-    if (ch + 1 < c_end) fetch(ch + 1);
     // ---- back-projection and prox step: rows 16 w + l16, accounts 4 q4 + r
-    const int row = r0 + 16 * w + l16, rc = min(row, n - 1);
+    const int row = r0 + 16 * w + l16;
     const bool row_ok = row < n;
-    const float d_i = row_ok ? A.d[row] : 1.f;
+    const float d_i = row_ok ? d_n : 1.f;
     float sv[4], mu[4];
     uint32_t ew[4], hw[4];
     int hp[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int a = max(Aid[4 * q4 + r], 0);                    // (an empty slot reads account 0)
-      const size_t off = (size_t)a * n + rc, wi = (size_t)a * A.W + (rc >> 5);
-      sv[r] = src[off];
-      mu[r] = A.mu[off];
-      ew[r] = A.elig ? A.elig[wi] : 0xffffffffu;
-      hw[r] = A.hold[wi];
-      hp[r] = A.hold_pre[wi];
+      sv[r] = sv_n[r]; mu[r] = mu_n[r]; ew[r] = ew_n[r]; hw[r] = hw_n[r]; hp[r] = hp_n[r];
     }
+    if (ch + 1 < c_end) fetch(ch + 1);
     floatx4 X;
 #pragma unroll
     for (int r = 0; r < 4; ++r) X[r] = 0.f;
@@ -154,7 +222,7 @@ __global__ __launch_bounds__(kWdT) void wide_kernel(WideArgs A, int do_x, int do
     for (int r = 0; r < 4; ++r) {
       const int m = 4 * q4 + r, a = Aid[m];
       Rp[r] = 0.f;
-      if (a >= 0 && row_ok) {
+      if (r < rounds && a >= 0 && row_ok) {
         const float4 c0 = Acc[2 * m], c1 = Acc[2 * m + 1];
         const float rho = c0.x, gam = c0.z, alpha = c1.w;
         float v = sv[r];
@@ -209,6 +277,8 @@ __global__ __launch_bounds__(kWdT) void wide_kernel(WideArgs A, int do_x, int do
   }
 }
 
+int wide_columns(int k, int kp, int H) { return wide_cols(k, kp, H); }
+
 // Which books: no account has a turnover cap (its search needs every row
 // between the two products), the accounts fit one MFMA tile, and the
 // contractions are the float32 ones (the bf16-split passes sum in another
@@ -241,11 +311,13 @@ hipError_t launch_wide(const WideArgs& A, int nblk, int do_x, int do_p, hipStrea
   }
 }
 
-hipError_t launch_wide_setup(int n, int kp, const float* Bt, float* Bp, hipStream_t st) {
+hipError_t launch_wide_setup(int n, int k, int kp, int H, const float* Bt, float* Bp,
+                             hipStream_t st) {
   const int npad = ((n + kRowsPerChunk - 1) / kRowsPerChunk) * kRowsPerChunk;
-  const size_t total = (size_t)npad * kp;
+  const int kc = wide_cols(k, kp, H);
+  const size_t total = (size_t)npad * kc;
   const unsigned blocks = (unsigned)((total + 255) / 256 < 8192 ? (total + 255) / 256 : 8192);
-  hipLaunchKernelGGL(wide_perm_kernel, dim3(blocks), dim3(256), 0, st, n, npad, kp, Bt, Bp);
+  hipLaunchKernelGGL(wide_perm_kernel, dim3(blocks), dim3(256), 0, st, n, npad, kp, kc, Bt, Bp);
   return hipGetLastError();
 }
 
