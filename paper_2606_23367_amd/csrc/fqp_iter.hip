@@ -35,6 +35,7 @@
 // in factor space (nu, p); PROJECT streams w and applies the back-projection
 // B~ p (MFMA), writing the new v.
 #include <algorithm>
+#include <type_traits>
 
 #include <hip/hip_ext.h>
 
@@ -77,6 +78,8 @@ __global__ __launch_bounds__(256) void gram_partial_kernel(
   const int nk = kg + 1;
   const int ne = nk * nk;
   const int e0 = blockIdx.y * 8192;
+  const int nc = (min(ne - e0, 8192) + 255) / 256;     // entries a thread
+  __shared__ double s_id[64];                           // 1 / Delta of the staged rows
   const int r_begin = blockIdx.x * rows_per_blk;
   const int r_end = min(n, r_begin + rows_per_blk);
   double acc[32];
@@ -93,13 +96,20 @@ __global__ __launch_bounds__(256) void gram_partial_kernel(
     int rows = min(64, r_end - r0);
     for (int e = threadIdx.x; e < rows * kp; e += blockDim.x)
       sB[e] = Bt[(size_t)r0 * kp + e];
+    if (threadIdx.x < rows) s_id[threadIdx.x] = 1.0 / (gamma * (double)d[r0 + threadIdx.x] + rho);
     __syncthreads();
     for (int rr = 0; rr < rows; ++rr) {
-      const double idl = 1.0 / (gamma * (double)d[r0 + rr] + rho);
+      const double idl = s_id[rr];
       const float* row = sB + rr * kp;
+      // (entries past the tile's last are skipped four at a time: on 6 x 6
+      // all but the first were the 29 us of this kernel)
 #pragma unroll
-      for (int c = 0; c < 32; ++c)
-        acc[c] += (double)row[jj[c]] * (double)row[ll[c]] * idl;
+      for (int c4 = 0; c4 < 32; c4 += 4) {
+        if (c4 >= nc) break;                         // uniform
+#pragma unroll
+        for (int c = c4; c < c4 + 4; ++c)
+          acc[c] += (double)row[jj[c]] * (double)row[ll[c]] * idl;
+      }
     }
   }
 #pragma unroll
@@ -126,6 +136,24 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(int ne, int nparts, co
   }
   for (; p < nparts; ++p) s += part[(size_t)p * ne + e];
   Gm[e] = s;
+}
+
+// The sum over a wave (every lane gets it), in the order of a butterfly from 32
+// down to 1: the last four exchanges stay within rows of 16 lanes and go by DPP
+// (rotations by 8 and 4 equal the exchanges, as the sums repeat by then; quad
+// swaps), two instead of six trips through the LDS crossbar.
+__device__ __forceinline__ float wave_sum_f(float x) {
+  x += __shfl_xor(x, 32, 64);
+  x += __shfl_xor(x, 16, 64);
+  auto dpp = [](float y, auto ctrl) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, y),
+                                                                 decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  x += dpp(x, std::integral_constant<int, 0x128>());
+  x += dpp(x, std::integral_constant<int, 0x124>());
+  x += dpp(x, std::integral_constant<int, 0x4E>());
+  x += dpp(x, std::integral_constant<int, 0xB1>());
+  return x;
 }
 
 // add F~^-1 to the Gram matrix, invert, border vectors.  One workgroup of
@@ -938,11 +966,8 @@ __global__ __launch_bounds__(kCapT, 8) void prox_kernel(IterArgs A, int zmode) {
       g += fabsf(z - ri.w0);
       nf += kink ? 0.f : 1.f;
     }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      g += __shfl_xor(g, o, 64);
-      nf += __shfl_xor(nf, o, 64);
-    }
+    g = wave_sum_f(g);
+    nf = wave_sum_f(nf);
     const int buf = it & 1;
     if ((tid & 63) == 0) { s_g[buf][wv] = g; s_n[buf][wv] = nf; }
     __syncthreads();
@@ -1060,11 +1085,8 @@ __global__ __launch_bounds__(kCapT) void prox_stream_kernel(IterArgs A, int zmod
         }
       }
     }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      g += __shfl_xor(g, o, 64);
-      nf += __shfl_xor(nf, o, 64);
-    }
+    g = wave_sum_f(g);
+    nf = wave_sum_f(nf);
     if ((tid & 63) == 0) { s_g[0][wv] = g; s_n[0][wv] = nf; }
     __syncthreads();
     if (tid == 0) {

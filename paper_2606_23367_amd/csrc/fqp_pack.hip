@@ -26,51 +26,82 @@ __device__ __forceinline__ bool is_elig(const uint32_t* elig, int W, int a, int 
   return elig == nullptr || ((elig[(size_t)a * W + (i >> 5)] >> (i & 31)) & 1u);
 }
 
-template <typename T>
-__device__ T block_reduce_sum(T v, T* sh) {
-  sh[threadIdx.x] = v;
+// Sums of NI ints and ND doubles over 256 threads (for thread 0), the doubles by
+// halves: 128, 64, 32, ... 1 apart.  One barrier for all of them (a tree of
+// eight barriers per quantity was most of the kernel on a small book).
+template <int NI, int ND>
+__device__ __forceinline__ void block_sums(int (&iv)[NI], double (&dv)[ND]) {
+  __shared__ double sd[ND][256];
+  __shared__ int si[NI];
+  const int tid = threadIdx.x;
+  if (tid < NI) si[tid] = 0;
   __syncthreads();
-  for (int o = blockDim.x / 2; o >= 1; o >>= 1) {
-    if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-    __syncthreads();
+#pragma unroll
+  for (int q = 0; q < ND; ++q) sd[q][tid] = dv[q];
+#pragma unroll
+  for (int q = 0; q < NI; ++q)
+    if (iv[q]) atomicAdd(&si[q], iv[q]);
+  __syncthreads();
+  if (tid < 64) {
+#pragma unroll
+    for (int q = 0; q < ND; ++q) {
+      double v = (sd[q][tid] + sd[q][tid + 128]) + (sd[q][tid + 64] + sd[q][tid + 192]);
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+      dv[q] = v;
+    }
   }
-  T r = sh[0];
+#pragma unroll
+  for (int q = 0; q < NI; ++q) iv[q] = si[q];
+}
+
+// inclusive sum over the 256 threads' values (s_w: 4 ints; ends synchronised)
+__device__ __forceinline__ int block_scan(int v, int* s_w) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(v, o, 64);
+    v += lane >= o ? u : 0;
+  }
+  if (lane == 63) s_w[wv] = v;
   __syncthreads();
-  return r;
+  for (int q = 0; q < wv; ++q) v += s_w[q];
+  __syncthreads();
+  return v;
 }
 
 __global__ __launch_bounds__(256) void pack_count_kernel(PackArgs A) {
-  __shared__ double shd[256];
-  __shared__ int shi[256];
   const int a = blockIdx.x;
   const int n = A.n, W = A.W;
   const float lb = A.lb[a], ub = A.ub[a];
   int held = 0, bad = 0, bad_box = 0;
   double sum_clip = 0.0, dist = 0.0, sum_lb = 0.0, sum_ub = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) {
-    const size_t off = (size_t)a * n + i;
-    const float mu = A.mu[off];
-    const float w0 = A.w0[off];
-    if (!isfinite(mu) || !isfinite(w0)) bad = 1;
-    if (w0 != 0.f) ++held;
-    const bool el = is_elig(A.elig, W, a, i);
-    float lf, uf;
-    asset_box(A, off, el, lb, ub, lf, uf);
-    if (!(lf <= uf) || !isfinite(lf) || !isfinite(uf)) bad_box = 1;
-    const double l = lf, u = uf;
-    sum_lb += l;
-    sum_ub += u;
-    const double c = fmin(fmax((double)w0, l), u);
-    sum_clip += c;
-    dist += fabs((double)w0 - c);
+  // four rows' loads in flight a thread
+  for (int i0 = threadIdx.x; i0 < n; i0 += 4 * 256) {
+    float mu[4], w4[4], lf[4], uf[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = min(i0 + 256 * u, n - 1);
+      const size_t off = (size_t)a * n + i;
+      mu[u] = A.mu[off];
+      w4[u] = A.w0[off];
+      asset_box(A, off, is_elig(A.elig, W, a, i), lb, ub, lf[u], uf[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (i0 + 256 * u >= n) break;
+      const float w0 = w4[u];
+      if (!isfinite(mu[u]) || !isfinite(w0)) bad = 1;
+      if (w0 != 0.f) ++held;
+      if (!(lf[u] <= uf[u]) || !isfinite(lf[u]) || !isfinite(uf[u])) bad_box = 1;
+      const double l = lf[u], uu = uf[u];
+      sum_lb += l;
+      sum_ub += uu;
+      const double c = fmin(fmax((double)w0, l), uu);
+      sum_clip += c;
+      dist += fabs((double)w0 - c);
+    }
   }
-  held = block_reduce_sum<int>(held, shi);
-  bad = block_reduce_sum<int>(bad, shi);
-  bad_box = block_reduce_sum<int>(bad_box, shi);
-  sum_clip = block_reduce_sum<double>(sum_clip, shd);
-  dist = block_reduce_sum<double>(dist, shd);
-  sum_lb = block_reduce_sum<double>(sum_lb, shd);
-  sum_ub = block_reduce_sum<double>(sum_ub, shd);
 
   // lot data of this account
   int bad_tax = 0;
@@ -89,7 +120,6 @@ __global__ __launch_bounds__(256) void pack_count_kernel(PackArgs A) {
       if (!(s0 >= 0.f && s1 >= s0 && s2 >= s1 && s3 >= s2 && isfinite(s3))) bad_tax = 1;
     }
   }
-  bad_tax = block_reduce_sum<int>(bad_tax, shi);
   int bad_band = 0;
   if (A.blo) {
     for (int g = threadIdx.x; g < A.G; g += 256) {
@@ -98,7 +128,11 @@ __global__ __launch_bounds__(256) void pack_count_kernel(PackArgs A) {
       if (g < A.Gl && (!isfinite(lo) || !isfinite(hi))) bad_band = 1;
     }
   }
-  bad_band = block_reduce_sum<int>(bad_band, shi);
+  int iv[5] = {held, bad, bad_box, bad_tax, bad_band};
+  double dv[4] = {sum_clip, dist, sum_lb, sum_ub};
+  block_sums(iv, dv);
+  held = iv[0]; bad = iv[1]; bad_box = iv[2]; bad_tax = iv[3]; bad_band = iv[4];
+  sum_clip = dv[0]; dist = dv[1]; sum_lb = dv[2]; sum_ub = dv[3];
 
   if (threadIdx.x == 0) {
     A.hold_cnt[a] = held;
@@ -124,7 +158,7 @@ __global__ void pack_scan_kernel(PackArgs A) {
   // exclusive scan of hold_cnt into hold_ptr (single workgroup); the total
   // goes to hold_ptr[m], the largest count of one account to hold_ptr[m + 1]
   __shared__ int carry, most, caps;
-  __shared__ int sh[256];
+  __shared__ int sh[4];
   if (threadIdx.x == 0) {
     carry = 0;
     most = 0;
@@ -137,17 +171,10 @@ __global__ void pack_scan_kernel(PackArgs A) {
     const int v = (i < A.m) ? A.hold_cnt[i] : 0;
     mx = max(mx, v);
     nc += (i < A.m && isfinite(A.tau[i])) ? 1 : 0;
-    sh[threadIdx.x] = v;
+    const int sum = block_scan(v, sh);
+    if (i < A.m) A.hold_ptr[i] = carry + sum - v;
     __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-      int t = (threadIdx.x >= o) ? sh[threadIdx.x - o] : 0;
-      __syncthreads();
-      sh[threadIdx.x] += t;
-      __syncthreads();
-    }
-    if (i < A.m) A.hold_ptr[i] = carry + sh[threadIdx.x] - v;
-    __syncthreads();
-    if (threadIdx.x == 255) carry += sh[255];
+    if (threadIdx.x == 255) carry += sum;
     __syncthreads();
   }
   atomicMax(&most, mx);
@@ -165,7 +192,7 @@ __global__ void pack_scan_kernel(PackArgs A) {
 }
 
 __global__ __launch_bounds__(256) void pack_fill_kernel(PackArgs A) {
-  __shared__ int sh[256];
+  __shared__ int sh[4];
   __shared__ int carry;
   __shared__ uint32_t s_bits[256];
   const int a = blockIdx.x;
@@ -194,15 +221,8 @@ __global__ __launch_bounds__(256) void pack_fill_kernel(PackArgs A) {
     const int wd = wb + threadIdx.x;
     const uint32_t bits = (wd < W) ? s_bits[threadIdx.x] : 0u;
     const int pc = __popc(bits);
-    sh[threadIdx.x] = pc;
-    __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-      int t = (threadIdx.x >= o) ? sh[threadIdx.x - o] : 0;
-      __syncthreads();
-      sh[threadIdx.x] += t;
-      __syncthreads();
-    }
-    const int pre = carry + sh[threadIdx.x] - pc;
+    const int sum = block_scan(pc, sh);
+    const int pre = carry + sum - pc;
     if (wd < W) {
       A.hold[(size_t)a * W + wd] = bits;
       A.hold_pre[(size_t)a * W + wd] = pre;
@@ -217,7 +237,7 @@ __global__ __launch_bounds__(256) void pack_fill_kernel(PackArgs A) {
       }
     }
     __syncthreads();
-    if (threadIdx.x == 255) carry += sh[255];
+    if (threadIdx.x == 255) carry += sum;
     __syncthreads();
   }
   // every lot entry points its name's record at itself: the record index is

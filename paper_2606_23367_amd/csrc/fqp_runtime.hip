@@ -102,25 +102,21 @@ __global__ void sanitize_state_kernel(size_t count, float* v) {
 // (host_count: pinned host memory that also receives the count, or null)
 __global__ void compact_kernel(int m, const int32_t* status, int* act, int* m_act,
                                int* host_count) {
-  __shared__ int sh[256];
-  __shared__ int carry;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  for (int base = 0; base < m; base += 256) {
+  __shared__ int s_w[2][4];                // the waves' counts, in turns
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  int carry = 0;
+  for (int base = 0, t = 0; base < m; base += 256, t ^= 1) {
     const int a = base + threadIdx.x;
-    const int v = (a < m && status[a] == -1) ? 1 : 0;
-    sh[threadIdx.x] = v;
+    const bool v = a < m && status[a] == -1;
+    const unsigned long long mk = __ballot(v);
+    if (lane == 0) s_w[t][wv] = __popcll(mk);
     __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-      int t = (threadIdx.x >= o) ? sh[threadIdx.x - o] : 0;
-      __syncthreads();
-      sh[threadIdx.x] += t;
-      __syncthreads();
+    int pos = carry + __popcll(mk & (lane ? ~0ull >> (64 - lane) : 0ull));
+    for (int q = 0; q < 4; ++q) {
+      pos += q < wv ? s_w[t][q] : 0;
+      carry += s_w[t][q];
     }
-    if (v) act[carry + sh[threadIdx.x] - 1] = a;
-    __syncthreads();
-    if (threadIdx.x == 255) carry += sh[255];
-    __syncthreads();
+    if (v) act[pos] = a;
   }
   if (threadIdx.x == 0) {
     *m_act = carry;
