@@ -162,6 +162,9 @@ __device__ __forceinline__ float wave_sum_f(float x) {
 // rows, its lanes two columns each); wider blocks are factored (Cholesky)
 // and inverted by triangular sweeps in the global scratch Kw
 constexpr int kKfLds = 96;
+// (A step is bound by instruction issue: the pivot row by a branch of its wave,
+// columns past 64 only where there are any; 106 -> 88 us at 81 columns, 68 -> 53
+// at 50 against selects on every entry.  Four waves of 24 rows took 268.)
 constexpr int kKfRows = kKfLds / 16;     // rows per wave of the in-register inversion (16 waves)
 
 __global__ __launch_bounds__(1024) void kfactor_kernel(int k, int G, int kp, int nparts,
@@ -180,8 +183,8 @@ __global__ __launch_bounds__(1024) void kfactor_kernel(int k, int G, int kp, int
   // border column c with its last entry (c_kg = 1^T Delta^-1 1), then q
   double* cv = in_lds ? kf_smem + kg * kg + 4 * kg : kf_smem;   // [kg + 1]
   double* qs = cv + kg + 1;                                     // [kg]
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int nw = (int)(blockDim.x >> 6);
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int nw = 16;
   // (Gm holds the sum of the row-block partials: gram_reduce_kernel)
   (void)part;
   (void)nparts;
@@ -206,6 +209,7 @@ __global__ __launch_bounds__(1024) void kfactor_kernel(int k, int G, int kp, int
     // matrix, out-of-range entries set to zero afterwards)
     const int c0 = min(lane, kg - 1), c1 = min(lane + 64, kg - 1);
     const double fd0 = c0 < k ? (double)f[c0] : 1.0, fd1 = c1 < k ? (double)f[c1] : 1.0;
+    const bool two = kg > 64;                          // uniform
     double x0[kKfRows], x1[kKfRows];
 #pragma unroll
     for (int t = 0; t < kKfRows; ++t) {
@@ -226,14 +230,18 @@ __global__ __launch_bounds__(1024) void kfactor_kernel(int k, int G, int kp, int
       double* cb = cbuf + (p & 1) * kg;
       const int pl = p & 63;
       const bool phi = p >= 64;
+      if (wv == (p & (nw - 1))) {                      // uniform: the wave of row p
 #pragma unroll
-      for (int t = 0; t < kKfRows; ++t) {
-        const int i = wv + nw * t;
-        if (i == p) {
-          if (lane < kg) rb[lane] = x0[t];
-          if (lane + 64 < kg) rb[lane + 64] = x1[t];
-        }
-        if (i < kg && lane == pl) cb[i] = phi ? x1[t] : x0[t];
+        for (int t = 0; t < kKfRows; ++t)
+          if (wv + nw * t == p) {
+            if (lane < kg) rb[lane] = x0[t];
+            if (lane + 64 < kg) rb[lane + 64] = x1[t];
+          }
+      }
+      if (lane == pl) {
+#pragma unroll
+        for (int t = 0; t < kKfRows; ++t)
+          if (wv + nw * t < kg) cb[wv + nw * t] = phi ? x1[t] : x0[t];
       }
       __syncthreads();
       // all of this step's LDS reads at once (clamped indices)
@@ -244,12 +252,18 @@ __global__ __launch_bounds__(1024) void kfactor_kernel(int k, int G, int kp, int
       const double ip = 1.0 / piv;
       const double r0 = lane < kg ? (lane == p ? 1.0 : a0) * ip : 0.0;
       const double r1 = lane + 64 < kg ? (lane + 64 == p ? 1.0 : a1) * ip : 0.0;
+      // (rows past the last hold zeros and meet cr of the last row: they stay
+      // finite and are never stored)
+      const bool h0 = lane == p, h1 = lane + 64 == p;
 #pragma unroll
       for (int t = 0; t < kKfRows; ++t) {
-        const int i = wv + nw * t;
-        const double c = (i < kg && i != p) ? cr[t] : 0.0;
-        x0[t] = (i == p) ? r0 : ((lane == p) ? 0.0 : x0[t]) - c * r0;
-        x1[t] = (i == p) ? r1 : ((lane + 64 == p) ? 0.0 : x1[t]) - c * r1;
+        x0[t] = (h0 ? 0.0 : x0[t]) - cr[t] * r0;
+        if (two) x1[t] = (h1 ? 0.0 : x1[t]) - cr[t] * r1;
+      }
+      if (wv == (p & (nw - 1))) {                      // uniform: the wave of row p
+#pragma unroll
+        for (int t = 0; t < kKfRows; ++t)
+          if (wv + nw * t == p) { x0[t] = r0; x1[t] = r1; }
       }
     }
 #pragma unroll

@@ -40,9 +40,11 @@ __global__ void init_accounts_kernel(int m, int G, const int* cls, const float* 
                                      const float* blo, const float* bhi, int* iters,
                                      int32_t* pstate, int npstate, int warm,
                                      const float* wz, const float* wv, const float* wl,
-                                     const int32_t* st_in, int32_t* st_out) {
+                                     const int32_t* st_in, int32_t* st_out,
+                                     int32_t* pcount) {
   const int a = blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= m) return;
+  if (a < 1) pcount[0] = pcount[1] = 0;
   // statuses of the validation pass reach the caller's array only here,
   // after every workspace request of the call has succeeded
   st_out[a] = st_in[a];
@@ -613,28 +615,7 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   float* rho_stage = h->hstage + m;
   int* cls_h = reinterpret_cast<int*>(h->hstage + 2 * (size_t)m);
   HIP_CHECK(hipMemcpyAsync(h->hstage, P->gamma, sizeof(float) * m, hipMemcpyDeviceToHost, st));
-  HIP_CHECK(hipStreamSynchronize(st));
-  std::vector<float> cls_gamma;
-  {
-    std::map<float, int> seen;
-    for (int a = 0; a < m; ++a) {
-      float g = gam_h[a];
-      if (!(g > 0.f) || !std::isfinite(g)) g = 1.f;   // invalid: flagged by pack
-      auto it = seen.find(g);
-      if (it == seen.end()) {
-        int id = (int)cls_gamma.size();
-        seen[g] = id;
-        cls_gamma.push_back(g);
-        cls_h[a] = id;
-      } else {
-        cls_h[a] = it->second;
-      }
-    }
-  }
-  const int ncls = (int)cls_gamma.size();
-  const float rho = auto_rho(&S);
-  const float rho_b = S.rho_band > 0.f ? S.rho_band : rho;
-  std::vector<float> rho_cls(ncls, rho);
+  HIP_CHECK(hipEventRecord(h->ev_r[0], st));         // the class values are in hstage
 
   // ---- workspace ----------------------------------------------------------
   // Every request comes before the first write to the caller's outputs: a
@@ -643,15 +624,6 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   const int gram_rows = 32;          // row blocks of the Gram partials: 313 at n = 10,000
   const int nparts = (n + gram_rows - 1) / gram_rows;
   WS(gpart, double, "gram_part", (size_t)nparts * (kg + 1) * (kg + 1));
-  const size_t kw_stride = (size_t)(kg + 1) * (kg + 1) + 2 * (size_t)kg * kg + kg + 16;
-  WS(Kw, double, "kwork", kw_stride * ncls);
-  WS(Kinv, float, "Kinv", (size_t)ncls * kp * kp);
-  WS(cvec, float, "cvec", (size_t)ncls * kp);
-  WS(qvec, float, "qvec", (size_t)ncls * kp);
-  WS(sig1, float, "sig1", (size_t)ncls);
-  WS(mbg, float, "mbg", (size_t)ncls * kp * (G > 0 ? G : 1));
-  WS(rho_d, float, "rho_cls", (size_t)ncls);
-  WS(cls_d, int, "cls", (size_t)m);
   WS(v, float, "v", (size_t)m * n);
   WS(z, float, "z", (size_t)m * n);
   WS(hold, uint32_t, "hold", (size_t)m * W);
@@ -741,9 +713,6 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   WS(btt_lo, uint16_t, "btt_lo", nbf);
 
   // ---- universe ------------------------------------------------------------
-  std::copy(rho_cls.begin(), rho_cls.end(), rho_stage);
-  HIP_CHECK(hipMemcpyAsync(rho_d, rho_stage, sizeof(float) * ncls, hipMemcpyHostToDevice, st));
-  HIP_CHECK(hipMemcpyAsync(cls_d, cls_h, sizeof(int) * m, hipMemcpyHostToDevice, st));
   HIP_CHECK(launch_build_bt(n, k, Gl, H, kp, U->B, U->group, U->half, Bt,
                             one_wg ? bq_p : nullptr, st));
   if (concat_rows)
@@ -772,6 +741,44 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   // by the most held names of any account: both counts come back to pinned
   // memory while the factor-space set-up below runs
   HIP_CHECK(hipEventRecord(h->ev_pack, st));
+
+  // ---- classes (the host waited for the values while the device works on the
+  // launches above) --------------------------------------------------------
+  HIP_CHECK(hipEventSynchronize(h->ev_r[0]));
+  std::vector<float> cls_gamma;
+  {
+    std::map<float, int> seen;
+    for (int a = 0; a < m; ++a) {
+      float g = gam_h[a];
+      if (!(g > 0.f) || !std::isfinite(g)) g = 1.f;   // invalid: flagged by pack
+      auto it = seen.find(g);
+      if (it == seen.end()) {
+        int id = (int)cls_gamma.size();
+        seen[g] = id;
+        cls_gamma.push_back(g);
+        cls_h[a] = id;
+      } else {
+        cls_h[a] = it->second;
+      }
+    }
+  }
+  const int ncls = (int)cls_gamma.size();
+  const float rho = auto_rho(&S);
+  const float rho_b = S.rho_band > 0.f ? S.rho_band : rho;
+  std::vector<float> rho_cls(ncls, rho);
+  const size_t kw_stride = (size_t)(kg + 1) * (kg + 1) + 2 * (size_t)kg * kg + kg + 16;
+  WS(Kw, double, "kwork", kw_stride * ncls);
+  WS(Kinv, float, "Kinv", (size_t)ncls * kp * kp);
+  WS(cvec, float, "cvec", (size_t)ncls * kp);
+  WS(qvec, float, "qvec", (size_t)ncls * kp);
+  WS(sig1, float, "sig1", (size_t)ncls);
+  WS(mbg, float, "mbg", (size_t)ncls * kp * (G > 0 ? G : 1));
+  // the classes' rho [m at most], then every account's class: one copy
+  WS(rho_d, float, "cls", 2 * (size_t)m);
+  const int* cls_d = reinterpret_cast<const int*>(rho_d + m);
+  std::copy(rho_cls.begin(), rho_cls.end(), rho_stage);
+  HIP_CHECK(hipMemcpyAsync(rho_d, rho_stage, 2 * sizeof(float) * (size_t)m, hipMemcpyHostToDevice,
+                           st));
 
   // ---- universe: the factor-space blocks per class
   for (int c = 0; c < ncls; ++c) {
@@ -837,7 +844,7 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
                      rho_d, P->gamma, P->kappa, P->lb, P->ub, P->tau, P->tax_ptr, S.alpha, rho_b,
                      par, zb, vb, rlo, rhi, iters, pstate, kPStateStride,
                      warm ? 1 : 0, G ? ws_z : nullptr, G ? ws_vb : nullptr, ws_l, st_in,
-                     R->status);
+                     R->status, pcount);
   HIP_CHECK(hipGetLastError());
   if (warm) {
     if (warm_given)
@@ -889,7 +896,6 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   pa.n_rb = n_rb; pa.gpart = gpart_p;
   pa.n_sb = n_sb; pa.fseg = fseg; pa.rpart = rpart; pa.spart = spart; pa.cpart = cpart;
   pa.hold_rec = hold_rec;
-  HIP_CHECK(hipMemsetAsync(pcount, 0, 2 * sizeof(int32_t), st));
   pa.eps_prim = S.eps_prim; pa.eps_dual = S.eps_dual; pa.eps_comp = S.eps_comp;
   HIP_CHECK(hipEventRecord(h->ev_t[1], st));         // end of setup
 
