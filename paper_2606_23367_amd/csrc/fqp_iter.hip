@@ -65,7 +65,7 @@ __global__ void build_bt_kernel(int n, int k, int G, int H, int kp, const float*
   else if (j == k + G + H) v = 1.f;
   Bt[e] = v;
   // the first k columns by fours, rows consecutive within a group of four
-  if (Bq && j < ((k + 3) & ~3)) Bq[((size_t)(j >> 2) * n + i) * 4 + (j & 3)] = v;
+  if (j < ((k + 3) & ~3)) Bq[((size_t)(j >> 2) * n + i) * 4 + (j & 3)] = v;
 }
 
 // partial Gram  sum_i B~_ij B~_il / Delta_i  over a chunk of rows, for

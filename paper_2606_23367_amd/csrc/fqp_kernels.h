@@ -107,7 +107,7 @@ bool cap_resident_fits(int n, int max_held);
 hipError_t launch_prox(const IterArgs& A, int m_total, bool resident, int zmode,
                        hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 hipError_t launch_ksolve(const KArgs& A, int m_total, hipStream_t st);
-// Bq (or null): [ceil(k / 4)][n] float4, the first k columns by fours
+// Bq: [ceil(k / 4)][n] float4, the first k columns by fours
 hipError_t launch_build_bt(int n, int k, int G, int H, int kp, const float* B,
                            const int32_t* group, const float* half, float* Bt, float* Bq,
                            hipStream_t st);
@@ -259,6 +259,7 @@ struct PolishArgs {
   const float* f;            // [k]
   const float* d;            // [n]
   const int32_t* group;      // [n] or null
+  const float4* Bq;          // [ceil(k / 4)][n] the factor columns by fours
   const float* half;         // [G - Gl][n] halfspace rows or null
   const float* mu;           // [m][n]
   const float* z;            // [m][n]  ADMM iterate

@@ -1377,9 +1377,12 @@ constexpr int kGbRows = 256;              // rows per gbase workgroup (one per t
 constexpr int kGbAcc = 16;                // accounts per gbase workgroup
 
 // g_i = gamma (d_i w_i + b_i . y) - mu_i for kGbRows rows x kGbAcc accounts:
-// each thread streams its row of B once (four columns at a time) against
-// the accounts' y vectors (LDS broadcasts), so the universe block is read
-// once per 16 accounts; per-(account, row block) maxima / sums go to gpart
+// each thread streams its row of B once (four columns at a time, from the copy
+// that keeps them consecutive over rows: a wave's load of 64 rows of B~ was
+// 64 lines, which did not survive in the L1 until their next four columns: 92 us a round
+// at 8 x 384,800, 33 now)
+// against the accounts' y vectors (LDS broadcasts), so the universe block is
+// read once per 16 accounts; per-(account, row block) maxima / sums go to gpart
 __global__ __launch_bounds__(256) void polish_gbase_kernel(PolishArgs A, int final_pass) {
   __shared__ double s_y[kGbAcc][kMaxK + 4];
   __shared__ int s_a[kGbAcc];
@@ -1432,10 +1435,9 @@ __global__ __launch_bounds__(256) void polish_gbase_kernel(PolishArgs A, int fin
 #pragma unroll
   for (int q = 0; q < kGbAcc; ++q) sig[q] = 0.0;
   if (row_ok) {
-    const float4* brow = reinterpret_cast<const float4*>(A.Bt + (size_t)i * A.kp);
 #pragma unroll 4
     for (int j4 = 0; j4 < k4 / 4; ++j4) {
-      const float4 b = brow[j4];
+      const float4 b = A.Bq[(size_t)j4 * n + i];
       const double b0 = b.x, b1 = b.y, b2 = b.z, b3 = b.w;
 #pragma unroll
       for (int q = 0; q < kGbAcc; ++q) {
@@ -2224,8 +2226,7 @@ __global__ __launch_bounds__(64) void polish_decide_kernel(PolishArgs A, fqp_res
 // Same arithmetic in the same order as the row-block passes (their sums over
 // rows differ in rounding only).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kPT) void polish_pass_kernel(PolishArgs A, fqp_result R, int rounds,
-                                                          const float4* Bq) {
+__global__ __launch_bounds__(kPT) void polish_pass_kernel(PolishArgs A, fqp_result R, int rounds) {
   extern __shared__ double smem_d[];
   __shared__ AcctLds W;
   __shared__ StepRows SR;
@@ -2273,7 +2274,7 @@ __global__ __launch_bounds__(kPT) void polish_pass_kernel(PolishArgs A, fqp_resu
       double sig = 0.0;
 #pragma unroll 4
       for (int j = 0; j < k4; ++j) {
-        const float4 b = Bq[(size_t)j * n + i];
+        const float4 b = A.Bq[(size_t)j * n + i];
         const double* y = W.yF + 4 * j;
         sig += (double)b.x * y[0] + (double)b.y * y[1] + (double)b.z * y[2] + (double)b.w * y[3];
       }
@@ -2367,14 +2368,13 @@ bool polish_pass_fits(int n, int k, int G) {
   return n <= kPassRows;
 }
 
-hipError_t launch_polish_pass(const PolishArgs& A, const fqp_result& R, int rounds, const float* Bq,
+hipError_t launch_polish_pass(const PolishArgs& A, const fqp_result& R, int rounds,
                               hipStream_t st) {
   const size_t smem = pass_smem(A.k, A.G, A.n_sb);
   hipError_t e = hipFuncSetAttribute((const void*)polish_pass_kernel,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(polish_pass_kernel, dim3(A.m_total), dim3(kPT), smem, st, A, R, rounds,
-                     reinterpret_cast<const float4*>(Bq));
+  hipLaunchKernelGGL(polish_pass_kernel, dim3(A.m_total), dim3(kPT), smem, st, A, R, rounds);
   return hipGetLastError();
 }
 

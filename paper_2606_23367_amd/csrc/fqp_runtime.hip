@@ -27,7 +27,7 @@
 namespace fqp {
 hipError_t launch_polish_check_r(const PolishArgs& A, const fqp_result& R, int final_pass,
                                  hipStream_t st);
-hipError_t launch_polish_pass(const PolishArgs& A, const fqp_result& R, int rounds, const float* Bq,
+hipError_t launch_polish_pass(const PolishArgs& A, const fqp_result& R, int rounds,
                               hipStream_t st);
 
 // ---------------------------------------------------------------------------
@@ -658,9 +658,9 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   WS(rpart, double, "polish_rpart", (size_t)m * n_sb * polish_rpart_stride(k, G));
   WS(spart, double, "polish_spart", (size_t)m * n_sb * 4);
   WS(cpart, double, "polish_cpart", (size_t)m * n_sb * 8);
-  // a certification pass by one workgroup per account reads B~ by columns
-  const bool one_wg = polish_pass_fits(n, k, G);
-  WS(bq_p, float, "polish_bq", one_wg ? (size_t)n * 4 * ((k + 3) / 4) : 1);
+  // the gradient base reads B~ by columns
+  WS(bq_p, float4, "polish_bq", (size_t)n * ((k + 3) / 4));
+  const bool one_wg = polish_pass_fits(n, k, G);        // a pass by one workgroup per account
   // the rest of Eq. 1: bounds of every constraint row [m][G] (bands, then
   // halfspaces); mu' = eta mu + gamma Sigma w_b and the constant of the
   // benchmark term when the book has a benchmark or a return scale
@@ -714,7 +714,7 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
 
   // ---- universe ------------------------------------------------------------
   HIP_CHECK(launch_build_bt(n, k, Gl, H, kp, U->B, U->group, U->half, Bt,
-                            one_wg ? bq_p : nullptr, st));
+                            reinterpret_cast<float*>(bq_p), st));
   if (concat_rows)
     HIP_CHECK(launch_concat_rows(m, Gl, H, P->band_lo, P->band_hi, P->half_lo, P->half_hi,
                                  rlo_ws, rhi_ws, st));
@@ -885,6 +885,7 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   pa.m_act = m_act;
   pa.act = act; pa.Bt = Bt; pa.f = U->f; pa.d = U->d; pa.group = Gl ? U->group : nullptr;
   pa.half = H ? U->half : nullptr;
+  pa.Bq = bq_p;
   pa.lbv = P->lb_asset; pa.ubv = P->ub_asset; pa.obj_const = bench ? obj_c : nullptr;
   pa.mu64 = bench ? mu_b64 : nullptr;
   pa.mu = mu_use; pa.z = z; pa.elig = P->eligible; pa.hold = hold; pa.hold_pre = hold_pre;
@@ -1053,7 +1054,7 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
     pa.nf_small = 2 * k + 32;
     pa.max_prop = 16;
     if (one_wg) {
-      HIP_CHECK(launch_polish_pass(pa, *R, S.polish_rounds, bq_p, st));
+      HIP_CHECK(launch_polish_pass(pa, *R, S.polish_rounds, st));
       h->stats.polish_calls += 1;
     }
     for (int r = 0; !one_wg && r < S.polish_rounds; ++r) {
