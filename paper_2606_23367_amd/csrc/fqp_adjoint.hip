@@ -388,7 +388,8 @@ hipError_t launch_adjoint(const AdjArgs& A, hipStream_t st) {
   const size_t schur = (size_t)kSchurW * (2 * kSchurW + 1), sums = 2 * (kPT / 64) * (size_t)A.k;
   const size_t smem = sizeof(double) * std::max(factor, std::max(schur, sums));
   hipError_t e = hipFuncSetAttribute((const void*)adjoint_solve_kernel,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     153 * 1024);   // at k = 128 and the most rows
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(adjoint_solve_kernel, dim3(A.m), dim3(kPT), smem, st, A);
   e = hipGetLastError();

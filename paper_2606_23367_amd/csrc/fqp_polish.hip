@@ -816,13 +816,31 @@ __device__ __forceinline__ int schur_solve(int nc, int ncol, const double* Sv, c
   return nd;
 }
 
+// doubles of LDS the solve's matrices take
+__host__ __device__ __forceinline__ int solve_doubles(int k, int G) {
+  // factor-space path: Kf and the staged rows (then the list sums' per-wave
+  // partials over Kf: 16 (k + G))
+  int d = k * kf_ld(k) + stage_rows(k, G) * stage_stride(k, G + 3);
+  const int lists = (kPT / 64) * (k + G);
+  d = lists > d ? lists : d;
+  // row-space path: H, V, X, f, F yX, b.F yX, 1 / L_jj, the free rows of B~
+  // (floats)
+  const int rows = kSmallF * kHld + 2 * kSmallF * (G + 3) + 2 * k + 2 * kSmallF +
+                   (kSmallF / 2) * (k + G);
+  return rows > d ? rows : d;
+}
+constexpr int kSolveVecs = 3 * kSchurW + kSmallF + kMaxK;   // the vectors behind them
+
+// row blocks up to which the columns of their partials are summed in shares
+// (the offsets of longer accounts' lists need the space)
+constexpr int kGatherParts = 16384;
+
 // what the per-account phases of a refinement round hand on in LDS
 struct AcctLds {
   double mult[2 + kMaxG];      // in: of the previous pattern, out: of this one
   double fy[kMaxK];            // F B_X^T w_X (fixed rows)
-  double gfix[kMaxG];          // the fixed rows' constraint-row sums
+  double gsum[kMaxG];          // constraint-row sums: of the fixed rows, then of the polished w
   double yF[kMaxK + 16];       // F B^T w of the polished w
-  double gsum[kMaxG];          // its constraint-row sums
   double sh[2 * kPW];
 };
 
@@ -904,7 +922,9 @@ __device__ __forceinline__ PatternSums gather_pattern(const PolishArgs& A, int a
   const double* rp = A.rpart + (size_t)a * S * rps;
   const int32_t* fseg = A.fseg + (size_t)a * n;
   double* s_part = smem_d;                      // [parts][kg + 2] column sums of a share of the blocks
-  int* s_of = reinterpret_cast<int*>(smem_d + kPT);   // [S + 1] free-list offsets (Kf not built yet)
+  const bool shares = S <= kGatherParts;
+  // [S + 1] free-list offsets (Kf not built yet)
+  int* s_of = reinterpret_cast<int*>(smem_d + (shares ? kPT : 0));
   int* s_ox = s_of + (S + 1);                   // [S + 1] nonzero-list offsets
   __shared__ double s_sx[2];
   __shared__ unsigned s_sig;
@@ -922,8 +942,9 @@ __device__ __forceinline__ PatternSums gather_pattern(const PolishArgs& A, int a
   // columns of the partials: a share of the blocks per part, sixteen blocks'
   // loads in flight a thread (past the share's end its last block's, dropped)
   const int cols = kg + 2;
-  const int parts = max(1, min(kPT / cols, (S + 15) / 16));
+  const int parts = shares ? max(1, min(kPT / cols, (S + 15) / 16)) : 1;
   const int share = (S + parts - 1) / parts;
+  double col_sum = 0.0;
   if (tid < parts * cols) {
     const int j = tid % cols, b0 = (tid / cols) * share, b1 = min(S, b0 + share);
     double v = 0.0;
@@ -934,7 +955,8 @@ __device__ __forceinline__ PatternSums gather_pattern(const PolishArgs& A, int a
 #pragma unroll
       for (int u = 0; u < 16; ++u) v += bb + u < b1 ? x[u] : 0.0;
     }
-    s_part[tid] = v;
+    col_sum = v;
+    if (shares) s_part[tid] = v;
   }
   // block offsets of the two lists: prefix sums (a wave scan when the
   // account has at most 64 row blocks)
@@ -970,7 +992,7 @@ __device__ __forceinline__ PatternSums gather_pattern(const PolishArgs& A, int a
   X.yx = 0.0;
   X.f = 0.0;
   if (tid < cols) {
-    double v = s_part[tid];
+    double v = col_sum;                     // (this thread's share is the column's first)
     for (int q = 1; q < parts; ++q) v += s_part[q * cols + tid];
     if (tid < k) {
       const double fj = (double)A.f[tid];
@@ -978,7 +1000,7 @@ __device__ __forceinline__ PatternSums gather_pattern(const PolishArgs& A, int a
       X.yx = v;
       X.f = fj;
     }
-    else if (tid < kg) W.gfix[tid - k] = v;
+    else if (tid < kg) W.gsum[tid - k] = v;
     else s_sx[tid - kg] = v;
   }
   const int nF = s_of[S], nX = s_ox[S];
@@ -1010,11 +1032,13 @@ __device__ __forceinline__ PatternSums gather_pattern(const PolishArgs& A, int a
 
 // the solve of one account's pattern by a workgroup of kPT threads; smem_d:
 // dynamic LDS of polish_smem bytes; ps: its bookkeeping (global or LDS).
+// vec: kSolveVecs doubles of LDS (behind the matrices in polish_solve, where
+// a very long account's list offsets take all of it before).
 // Leaves the free rows' weights in wout, W.mult, W.yF, W.gsum (not
 // synchronised) and returns the turnover of the polished weights.
 __device__ __forceinline__ double solve_pattern(const PolishArgs& A, int a, int tid, const float* par,
                                                 int* ps, const PatternSums& X, double* smem_d,
-                                                AcctLds& W) {
+                                                double* vec, AcctLds& W) {
   const int k = A.k, G = A.G, n = A.n;
   const float lbf = par[P_LB], ubf = par[P_UB], kap = par[P_KAPPA], tauf = par[P_TAU];
   const double gam = par[P_GAMMA];
@@ -1025,10 +1049,11 @@ __device__ __forceinline__ double solve_pattern(const PolishArgs& A, int a, int 
   double* w = A.wout + (size_t)a * n;
   double* Kf = smem_d;                      // [k][kf_ld]
   double* const shd = W.sh;
-  // the constraint system's vectors when it is solved in LDS
-  __shared__ double s_h[kSchurW], s_e0[kSchurW], s_eta[kSchurW];
-  __shared__ double s_wf[kSmallF];         // small free sets: the free weights
-  __shared__ double s_inv[kMaxK];          // 1 / L_jj of Kf
+  // the constraint system's vectors when it is solved in LDS, a small free
+  // set's weights, 1 / L_jj of its factor or Kf's
+  double* const s_h = vec;
+  double *const s_e0 = s_h + kSchurW, *const s_eta = s_e0 + kSchurW, *const s_wf = s_eta + kSchurW;
+  double* const s_inv = s_wf + kSmallF;
   const int cap_on = ps[PS_CAP], nF = X.nF, kg = k + G;
 
   // active constraint columns: 0 budget, bands (active order), cap
@@ -1048,7 +1073,7 @@ __device__ __forceinline__ double solve_pattern(const PolishArgs& A, int a, int 
   double* Sd = sl ? smem_d : wk.S;              // where H or Kf was, once they are done with
   if (tid < G && band_active(ps, tid)) {
     const double bnd = band_upper(ps, tid) ? A.bhi[(size_t)a * G + tid] : A.blo[(size_t)a * G + tid];
-    hd[col_of(tid)] = bnd - W.gfix[tid];
+    hd[col_of(tid)] = bnd - W.gsum[tid];
   }
   if (tid == 0) {
     hd[0] = 1.0 - X.sx;
@@ -1331,13 +1356,13 @@ __device__ __forceinline__ double solve_pattern(const PolishArgs& A, int a, int 
       double s = 0.0;
       for (int r = 0; r < nF; ++r) s += (double)L.Bs[r * kg + tid] * s_wf[r];
       if (tid < k) W.yF[tid] = (X.yx + s) * X.f;
-      else W.gsum[tid - k] = W.gfix[tid - k] + s;
+      else W.gsum[tid - k] += s;
     }
   } else {
     double ys = 0.0, gs = 0.0;
     list_sums(A, tid, flist, n, nF, 0, w, Kf, ys, gs);     // the solve is done with Kf
     if (tid < k) W.yF[tid] = (X.yx + ys) * X.f;
-    if (tid < G) W.gsum[tid] = W.gfix[tid] + gs;
+    if (tid < G) W.gsum[tid] += gs;
   }
   return X.sturn + turn_f;
 }
@@ -1358,7 +1383,8 @@ __global__ __launch_bounds__(kPT) void polish_solve_kernel(PolishArgs A) {
     for (int e = tid; e < 2 + G; e += kPT) W.mult[e] = mult[e];
   const PatternSums X = gather_pattern(A, a, tid, A.first_round, smem_d, W);
   if (gated(A, A.first_round, ps, X, &s_same)) return;
-  const double turn = solve_pattern(A, a, tid, par, ps, X, smem_d, W);
+  const double turn = solve_pattern(A, a, tid, par, ps, X, smem_d, smem_d + solve_doubles(k, G),
+                                    W);
   // for the passes after it (a thread's own entries of yF and gsum)
   const Wk wk = wk_of(A, a);
   if (tid < k) wk.yF[tid] = W.yF[tid];
@@ -2230,7 +2256,7 @@ __global__ __launch_bounds__(kPT) void polish_pass_kernel(PolishArgs A, fqp_resu
   extern __shared__ double smem_d[];
   __shared__ AcctLds W;
   __shared__ StepRows SR;
-  __shared__ double s_red[3 * kPW];
+  __shared__ double s_red[3 * kPW], s_vec[kSolveVecs];
   __shared__ double4 s_sum4[kPT / 16], s_max4[kPT / 16];
   double *const s_sum = &s_sum4[0].x, *const s_max = &s_max4[0].x;
   __shared__ int s_ps[kPStateStride], s_same, s_block, s_key[2], s_flag;
@@ -2264,7 +2290,7 @@ __global__ __launch_bounds__(kPT) void polish_pass_kernel(PolishArgs A, fqp_resu
     }
     const PatternSums X = gather_pattern(A, a, tid, first, smem_d, W);
     if (gated(A, first, s_ps, X, &s_same)) break;             // uniform
-    const double turn0 = solve_pattern(A, a, tid, par, s_ps, X, smem_d, W);
+    const double turn0 = solve_pattern(A, a, tid, par, s_ps, X, smem_d, s_vec, W);
     if (tid < 4 * k4 - k) W.yF[k + tid] = 0.0;
     __syncthreads();
     // ---- gradient base: a row a thread, B~ by columns of four (coalesced)
@@ -2332,23 +2358,16 @@ __global__ __launch_bounds__(kPT) void polish_pass_kernel(PolishArgs A, fqp_resu
 }
 
 static size_t polish_smem(int k, int G, int n_sb) {
-  // factor-space path: Kf and the staged rows (then the list sums' per-wave
-  // partials over Kf: 16 (k + G) doubles)
-  const size_t stage = sizeof(double) * (size_t)stage_rows(k, G) * stage_stride(k, G + 3);
-  const size_t lists = sizeof(double) * (kPT / 64) * (size_t)(k + G);
-  size_t factor = sizeof(double) * (size_t)k * kf_ld(k) + stage;
-  if (lists > factor) factor = lists;
-  // row-space path: H, V, X, f, F yX, b.F yX, 1 / L_jj (doubles), the free
-  // rows of B~ (floats)
-  const size_t ncol = (size_t)G + 3;
-  const size_t rows = sizeof(double) * (kSmallF * kHld + 2 * kSmallF * ncol + 2 * (size_t)k +
-                                        2 * kSmallF) +
-                      sizeof(float) * kSmallF * (size_t)(k + G);
-  // the gather: a double a thread, then the row blocks' list offsets
-  const size_t gather = sizeof(double) * kPT + sizeof(int) * 2 * ((size_t)n_sb + 1);
-  const size_t both = factor > rows ? factor : rows;
-  return both > gather ? both : gather;
+  const size_t solve = sizeof(double) * ((size_t)solve_doubles(k, G) + kSolveVecs);
+  // the gather: a double a thread (long accounts: none), the list offsets
+  const size_t gather = (n_sb > kGatherParts ? 0 : sizeof(double) * kPT) +
+                        sizeof(int) * 2 * ((size_t)n_sb + 1);
+  return solve > gather ? solve : gather;
 }
+
+// dynamic LDS: of the solve at k = 128 and the most constraint rows; of a pass,
+// whose own variables take 12 KB
+constexpr size_t kSolveLds = 156 * 1024, kPassLds = 144 * 1024;
 
 static size_t pass_smem(int k, int G, int n_sb) {
   const size_t rows = sizeof(RowsLds) * (kPT / kRT);
@@ -2364,7 +2383,7 @@ static size_t pass_smem(int k, int G, int n_sb) {
 // number of accounts does not move the line.
 constexpr int kPassRows = 10 * kRB;
 bool polish_pass_fits(int n, int k, int G) {
-  if (pass_smem(k, G, polish_pass_blocks(n)) > 144 * 1024) return false;   // 16 KB are its own
+  if (pass_smem(k, G, polish_pass_blocks(n)) > kPassLds) return false;
   return n <= kPassRows;
 }
 
@@ -2372,7 +2391,7 @@ hipError_t launch_polish_pass(const PolishArgs& A, const fqp_result& R, int roun
                               hipStream_t st) {
   const size_t smem = pass_smem(A.k, A.G, A.n_sb);
   hipError_t e = hipFuncSetAttribute((const void*)polish_pass_kernel,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kPassLds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(polish_pass_kernel, dim3(A.m_total), dim3(kPT), smem, st, A, R, rounds);
   return hipGetLastError();
@@ -2383,8 +2402,11 @@ hipError_t launch_polish_solve(const PolishArgs& A, hipStream_t st) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t smem = polish_smem(A.k, A.G, A.n_sb);
+  // (the attribute belongs to the process: at least what any book of the
+  // library's limits takes, so that calls of several threads agree)
   e = hipFuncSetAttribute((const void*)polish_solve_kernel,
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                          hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)(smem > kSolveLds ? smem : kSolveLds));
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(polish_solve_kernel, dim3(A.m_total), dim3(kPT), smem, st, A);
   return hipGetLastError();

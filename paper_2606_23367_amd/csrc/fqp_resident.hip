@@ -492,7 +492,7 @@ template <int KQ, int NTHR>
 static hipError_t launch_resident_t(const ResArgs& A, int m_total, int count, hipStream_t st) {
   const size_t smem = resident_smem(A);
   hipError_t e = hipFuncSetAttribute((const void*)resident_kernel<KQ, NTHR>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, 140 * 1024);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((resident_kernel<KQ, NTHR>), dim3(m_total), dim3(NTHR), smem, st, A, count);
   return hipGetLastError();
