@@ -5,11 +5,12 @@
 //   pack   universe block B~, per-account validation and held-asset records
 //   setup  one factor-space Cholesky/inverse per distinct (gamma, rho) class
 //   init   z = u = 0, contraction of mu for the first x-step
-//   loop   blocks of `check_every` iterations [prox, contract, k-solve,
-//          project] (captured
-//          once in a hipGraph and replayed), then float64 polish and
-//          certification rounds on every active account, then compaction
-//          of the active list; the host reads the number still active
+//   loop   blocks of `check_every` iterations: one account-resident kernel, the
+//          fused wide pass and k-solve, or [prox, contract, k-solve, project]
+//          (captured once in a hipGraph and replayed), then float64 polish
+//          and certification rounds on every active account (one kernel up to
+//          5,120 rows, else launches per round), then compaction of the
+//          active list; the host reads the number still active
 //   final  one last polish + diagnostics pass for accounts not certified
 #include <chrono>
 #include <cmath>
