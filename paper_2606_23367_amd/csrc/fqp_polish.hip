@@ -2257,8 +2257,10 @@ __global__ __launch_bounds__(kPT) void polish_pass_kernel(PolishArgs A, fqp_resu
   __shared__ AcctLds W;
   __shared__ StepRows SR;
   __shared__ double s_red[3 * kPW], s_vec[kSolveVecs];
-  __shared__ double4 s_sum4[kPT / 16], s_max4[kPT / 16];
-  double *const s_sum = &s_sum4[0].x, *const s_max = &s_max4[0].x;
+  // (the gradient scale has partials of its own: wave 0 may still read them
+  // when the first wave is through its rows and stores its diagnostics)
+  __shared__ double4 s_sum4[kPT / 16], s_max4[kPT / 16], s_grad4[kPT / 16];
+  double *const s_sum = &s_sum4[0].x, *const s_max = &s_max4[0].x, *const s_grad = &s_grad4[0].x;
   __shared__ int s_ps[kPStateStride], s_same, s_block, s_key[2], s_flag;
   const int n = A.n, k = A.k, G = A.G;
   const int slot = blockIdx.x;
@@ -2315,9 +2317,9 @@ __global__ __launch_bounds__(kPT) void polish_pass_kernel(PolishArgs A, fqp_resu
     step_bounds(A, a, W.gsum, SR);
     if (tid == 0) s_block = -1;
     double gv[4] = {gmax, mumax, bad, 0.0};   // (of use to the first wave only)
-    put_red4(gv, s_sum, MaxOp());
+    put_red4(gv, s_grad, MaxOp());
     __syncthreads();                          // (also publishes SR)
-    if (tid < 64) get_red4(gv, s_sum, MaxOp());
+    if (tid < 64) get_red4(gv, s_grad, MaxOp());
     const double scale = fmax(fmax(gv[0], gv[1]), 1e-12);
     const int nd = s_ps[PS_ND];
     const double thr = 0.01 * A.eps_comp * scale;
@@ -2366,7 +2368,7 @@ static size_t polish_smem(int k, int G, int n_sb) {
 }
 
 // dynamic LDS: of the solve at k = 128 and the most constraint rows; of a pass,
-// whose own variables take 12 KB
+// whose own variables take 14 KB
 constexpr size_t kSolveLds = 156 * 1024, kPassLds = 144 * 1024;
 
 static size_t pass_smem(int k, int G, int n_sb) {

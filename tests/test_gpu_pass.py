@@ -1,0 +1,46 @@
+"""GPU tests of the certification pass that one workgroup runs per account
+(n <= 5,120): the order of its phases, seen where most of its 16 waves have no
+rows and run ahead of the first."""
+import numpy as np
+import pytest
+
+from oracle.kkt import residuals
+from oracle.problem import account, n_rows
+from workloads import make_config
+from _gpu_helpers import check_reported_diagnostics
+
+pytestmark = pytest.mark.gpu
+
+
+def _solve(uni, book, repeats=1, **settings):
+    import torch
+    from paper_2606_23367_amd.solver import Solver, to_device
+    P, s, runs = to_device(uni, book), Solver(0), []
+    for _ in range(repeats):
+        out = s.solve(P, **settings)
+        torch.cuda.synchronize()
+        runs.append({k: v.cpu().numpy() for k, v in out.items()})
+    return runs, s.stats()
+
+
+def _check_diagnostics(uni, book, host):
+    for a in range(book.m):
+        P = account(uni, book, a)
+        r = residuals(P, host["w"][a], host["nu"][a], host["lam_band"][a] if n_rows(P) else None,
+                      host["lam_cap"][a])
+        check_reported_diagnostics(host, a, r)
+
+
+# 256 accounts whose free rows pin every multiplier (no null direction, so no
+# sweep with its barriers between the gradient scale and the diagnostics): the
+# first wave reads the scale's partials while the others store the diagnostics'
+@pytest.mark.parametrize("n", [20, 40, 200])
+def test_gradient_scale_survives_the_diagnostics(n):
+    print(f"case n {n}", flush=True)
+    uni, book = make_config("c1", 51, N=n, M=256, k=5, ub=0.2)
+    runs, _ = _solve(uni, book, repeats=12, rho=0.05)
+    assert np.all(runs[0]["status"] == 0)
+    for other in runs[1:]:
+        for key in ("w", "obj", "r_prim", "r_dual", "r_comp", "status"):
+            assert np.array_equal(runs[0][key], other[key]), key
+    _check_diagnostics(uni, book, runs[0])
