@@ -2355,7 +2355,9 @@ __global__ __launch_bounds__(kPT) void polish_pass_kernel(PolishArgs A, fqp_resu
     __syncthreads();
     if (s_flag || r + 1 == rounds) break;                     // uniform
   }
-  // for the adjoint and the next pass
+  // for the adjoint and the next pass (a gated account leaves the rounds right
+  // behind the stores of its flags)
+  __syncthreads();
   if (threadIdx.x < kPStateStride) ps[threadIdx.x] = s_ps[threadIdx.x];
 }
 

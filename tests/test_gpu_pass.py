@@ -44,3 +44,18 @@ def test_gradient_scale_survives_the_diagnostics(n):
         for key in ("w", "obj", "r_prim", "r_dual", "r_comp", "status"):
             assert np.array_equal(runs[0][key], other[key]), key
     _check_diagnostics(uni, book, runs[0])
+
+
+# free sets too large for the first passes (no trade cost, loose boxes): the gate
+# sends the accounts back to the iterations until their pattern repeats, so
+# every gated pass hands its bookkeeping to the next one
+def test_gated_accounts_resume():
+    print("case gated", flush=True)
+    uni, book = make_config("c2", 52, N=600, M=24, k=8, groups=3, kappa=0.0, gamma=1000.0, ub=0.05)
+    runs, st = _solve(uni, book, repeats=4, rho=1.0, check_every=20, max_iter=4000)
+    assert st["polish_gated"] > 0 and st["iterations"] > 20
+    assert np.all(runs[0]["status"] == 0)
+    for other in runs[1:]:
+        for key in ("w", "obj", "r_dual", "iters"):
+            assert np.array_equal(runs[0][key], other[key]), key
+    _check_diagnostics(uni, book, runs[0])
