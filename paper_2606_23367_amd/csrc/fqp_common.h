@@ -187,11 +187,17 @@ __device__ inline void chol_factor(double* L, int k, int ld, double* inv) {
 // lower (k <= 128, leading dimension ld), inv its inverse diagonal.  Columns
 // are independent: wave q solves columns q, q + nwaves, ... with lane i holding
 // rows i and i + 64; a solved entry passes by readlane, and the entries of L
-// of eight steps are loaded before the first is used.  Ends with a barrier.
+// of eight steps are loaded before the first is used.  A pattern without free
+// rows leaves nothing to solve (k = 0: L and inv have no entry to read).  Ends
+// with a barrier.
 __device__ inline void chol_solve_cols(const double* L, int k, int ld, const double* inv, double* Y,
                                        int ncol) {
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = (int)(blockDim.x >> 6);
+  if (k <= 0) {                                               // uniform
+    __syncthreads();
+    return;
+  }
   const int l0 = min(lane, k - 1), l1 = min(lane + 64, k - 1);
   const bool two = k > 64;                                    // uniform
   // the lane's own pivots and their reciprocals: each step's quotient is formed

@@ -7,7 +7,7 @@ import pytest
 from oracle.kkt import residuals
 from oracle.problem import account, n_rows
 from workloads import make_config
-from _gpu_helpers import check_reported_diagnostics
+from _gpu_helpers import check_account, check_reported_diagnostics
 
 pytestmark = pytest.mark.gpu
 
@@ -59,3 +59,32 @@ def test_gated_accounts_resume():
         for key in ("w", "obj", "r_dual", "iters"):
             assert np.array_equal(runs[0][key], other[key]), key
     _check_diagnostics(uni, book, runs[0])
+
+
+# optima at a vertex of the box (64 names at ub = 1 / 64, the rest at 0): no free
+# row, so every system over the free rows is empty; by one workgroup and by the
+# row blocks, and the gradient there (the weights do not move: zero)
+@pytest.mark.parametrize("n,m", [(64, 3), (200, 8), (6000, 2)])
+def test_patterns_without_free_rows(n, m):
+    import torch
+    from paper_2606_23367_amd.solver import Solver, to_device
+    print(f"case vertex n {n}", flush=True)
+    uni, book = make_config("c1", 53, N=n, M=m, k=3, ub=1.0 / 64, w0="zero")
+    # 64 names clear of the rest (returns stay float32 values)
+    book.mu[:, :64] = (book.mu[:, :64] + 0.25).astype(np.float32)
+    book.eligible[:, 200:] = False
+    s = Solver(0)
+    out = s.solve(to_device(uni, book), rho=10.0)
+    host = {k: v.cpu().numpy() for k, v in out.items()}
+    assert np.all(host["status"] == 0)
+    _check_diagnostics(uni, book, host)
+    # (an account may end one pattern short, a free row held at its bound by the budget)
+    want = np.where(np.arange(n) < 64, 1.0 / 64, 0.0)
+    at = [a for a in range(m) if np.array_equal(host["w"][a], want)]
+    assert at, "no account ends without free rows"
+    for a in range(min(m, 3)):
+        check_account(uni, book, a, host)
+    g = torch.ones((m, n), dtype=torch.float64, device="cuda:0")
+    dmu, dB = s.adjoint(g)
+    assert np.all(dmu.cpu().numpy()[at] == 0.0)
+    assert np.all(np.isfinite(dB.cpu().numpy()))
