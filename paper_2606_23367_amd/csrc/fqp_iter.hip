@@ -1489,12 +1489,17 @@ hipError_t launch_prox(const IterArgs& A, int m_total, bool resident, int zmode,
   return hipGetLastError();
 }
 
+// dynamic LDS of ksolve at the most columns and constraint rows
+constexpr int kKsLds = 4 * kMaxKp * kMaxG;
+
 template <int KB, int PB>
 static hipError_t launch_ksolve_t(const KArgs& A, int m_total, hipStream_t st) {
   const size_t smem = sizeof(float) * (size_t)(A.k + A.G + 1) * A.G;
   if (smem > 32 * 1024) {
+    // (the attribute belongs to the process: one value for every book, so that
+    // calls of several threads agree)
     hipError_t e = hipFuncSetAttribute((const void*)ksolve_kernel<KB, PB>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kKsLds);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((ksolve_kernel<KB, PB>), dim3(m_total), dim3(kKsT), smem, st, A);
