@@ -169,7 +169,7 @@ __global__ __launch_bounds__(kPT) void adjoint_solve_kernel(AdjArgs A) {
             const int j = 4 * tj + q, l = 4 * tl + s;
             if (j < k && l <= j) {
               double v = acc[q * 4 + s];
-              if (j == l) v += 1.0 / (double)A.f[j];
+              if (j == l) v += factor_weight(A.f[j]);
               Kf[j * ld + l] = v;
             }
           }

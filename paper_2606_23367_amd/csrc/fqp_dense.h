@@ -44,6 +44,12 @@ __device__ __forceinline__ double push_d(double x, int to) {
 struct SumOp { __device__ double operator()(double a, double b) const { return a + b; } };
 struct MaxOp { __device__ double operator()(double a, double b) const { return fmax(a, b); } };
 
+// 1 / f_j on the diagonal of K_F.  A factor of no variance (f_j = 0) drops out of
+// the solves by its diagonal's weight; an infinite one would meet its own
+// reciprocal 0 in div_by (inf * 0).  The reciprocal of every other float32 is
+// below the bound.
+__device__ __forceinline__ double factor_weight(float f) { return fmin(1.0 / (double)f, 1e300); }
+
 // S eta = C H^-1 rhs - h, S positive semidefinite (nc x ncol, the rhs column
 // last), by one wave (nc <= kSchurW), lane i its row i: a pivoted Cholesky
 // finds the rank, the components it does not reach keep their value in e0, and

@@ -1208,7 +1208,7 @@ __device__ __forceinline__ double solve_pattern(const PolishArgs& A, int a, int 
             const int j = 4 * tj + q, l = 4 * tl + s;
             if (j < k && l <= j) {
               double v = acc[q * 4 + s];
-              if (j == l) v += 1.0 / (double)A.f[j];
+              if (j == l) v += factor_weight(A.f[j]);
               Kf[j * ld + l] = v;
             }
           }

@@ -2,6 +2,7 @@
 constraint system in one wave's lanes and above them, panels of the
 factorisation, free sets on either side of the row-space solve, the rows of a
 pass by one workgroup."""
+import numpy as np
 import pytest
 
 from workloads import make_config
@@ -62,3 +63,42 @@ def test_rows_of_a_pass(name, over):
     host, _ = run_gpu(uni, book, rho=10.0, max_iter=4000)
     for a in range(2):
         check_account(uni, book, a, host)
+
+
+# a factor of no variance: the book is the one without its column (free sets in
+# row space, in factor space, and the row blocks), and so are its gradients
+DEAD_FACTOR = [("c2", dict(N=500, M=2, k=9, groups=4, ub=0.05), 1.0),
+               ("c5", dict(N=600, M=2, k=40, groups=5, tax=False, kappa=0.0, gamma=1000.0, ub=0.05,
+                           held=(60, 90)), 10.0),
+               ("c5", dict(N=6000, M=2, k=70, groups=5, tax=False, kappa=0.0, gamma=1000.0, ub=0.05,
+                           held=(60, 90)), 10.0)]
+
+
+@pytest.mark.parametrize("name,over,rho", DEAD_FACTOR)
+def test_factor_without_variance(name, over, rho):
+    import oracle
+    from dataclasses import replace
+    from oracle.adjoint import gradients
+    from oracle.problem import account
+    from test_gpu_adjoint import _gpu_adjoint
+    print(f"case dead factor {over}", flush=True)
+    uni, book = make_config(name, 45, **over)
+    dead = over["k"] // 2
+    keep = np.arange(uni.k) != dead
+    uni.f[dead] = 0.0
+    short = replace(uni, B=np.ascontiguousarray(uni.B[:, keep]), f=uni.f[keep])
+    C = np.random.default_rng(45).normal(size=(book.m, uni.n))
+    host, dmu, dB = _gpu_adjoint(uni, book, C, rho=rho, eps_prim=1e-9, eps_dual=1e-9, eps_comp=1e-9)
+    assert np.all(dB[:, dead] == 0.0)
+    ref, bound = np.zeros((uni.n, uni.k - 1)), 0.0
+    for a in range(book.m):
+        check_account(short, book, a, host)
+        P = account(short, book, a)
+        orc = oracle.solve_account(P)
+        g_mu, g_B = gradients(P, orc["w"], orc["lam_band"], orc["lam_cap"], C[a])
+        # (the scale of the other gradient tests: a vertex has a zero gradient)
+        scale = max(np.abs(g_mu).max(), np.abs(C[a]).max() / (P.gamma * short.d.max()))
+        assert np.max(np.abs(dmu[a] - g_mu)) <= 1e-6 * scale, a
+        ref += g_B
+        bound += scale * np.abs(P.gamma * short.f * (short.B.T @ orc["w"])).max()
+    assert np.max(np.abs(dB[:, keep] - ref)) <= 1e-6 * max(np.abs(ref).max(), bound)
