@@ -1506,13 +1506,25 @@ static hipError_t launch_ksolve_t(const KArgs& A, int m_total, hipStream_t st) {
   return hipGetLastError();
 }
 
-// K^-1 entries a thread takes: kp / (512 / kp) = 16 at kp <= 64 (and spare),
-// 20 at 96, 32 at 128, 54 at 160, 96 at 192
+// K^-1 entries a thread takes: kp / (512 / kp) = 2 at kp = 32, 8 at 64, 20 at 96,
+// 32 at 128, 54 at 160, 96 at 192; partials in flight: four where no thread
+// can have more.  Entries and partials past a thread's last are loaded all the
+// same, and with thousands of accounts on few rows the cost is that of the loads: at
+// 4,000 x 60 an iteration is 85 us with 103 factors and 41 with 5, with 16 to 32
+// entries and partials of which two to 26 count it was 132 and 49.
+template <int KB, int PB>
+static hipError_t launch_ksolve_p(const KArgs& A, int m_total, hipStream_t st) {
+  const int chunks = (A.n + kRowsPerChunk - 1) / kRowsPerChunk;
+  const int row_tiles = std::min(chunks, std::max(A.nblk, 1));      // at most, at any m_act
+  return row_tiles <= 4 * (kKsT / A.kp) ? launch_ksolve_t<KB, 4>(A, m_total, st)
+                                        : launch_ksolve_t<KB, PB>(A, m_total, st);
+}
 hipError_t launch_ksolve(const KArgs& A, int m_total, hipStream_t st) {
-  if (A.kp <= 64) return launch_ksolve_t<16, 16>(A, m_total, st);
-  if (A.kp <= 96) return launch_ksolve_t<20, 16>(A, m_total, st);
-  if (A.kp <= 128) return launch_ksolve_t<32, 32>(A, m_total, st);
-  return launch_ksolve_t<54, 32>(A, m_total, st);
+  if (A.kp <= 32) return launch_ksolve_p<2, 16>(A, m_total, st);
+  if (A.kp <= 64) return launch_ksolve_p<8, 16>(A, m_total, st);
+  if (A.kp <= 96) return launch_ksolve_p<20, 16>(A, m_total, st);
+  if (A.kp <= 128) return launch_ksolve_p<32, 32>(A, m_total, st);
+  return launch_ksolve_p<54, 32>(A, m_total, st);
 }
 
 hipError_t launch_split_bt(int n, int npad, int kp, const float* Bt, uint16_t* bh, uint16_t* bl,
