@@ -162,8 +162,11 @@ struct ResArgs {
 // quarter of the padded factor width the resident kernel is compiled for
 int resident_kq(int kw);
 // whether a book of m accounts runs its blocks account-resident: kw = used
-// columns of B~, ncap = accounts with a turnover cap
-bool resident_fits(int n, int kw, int G, bool lots, int m, int ncap, int n_cu);
+// columns of B~, ncap = accounts with a turnover cap, max_held = the most names
+// one account holds, asset_box: per-asset bounds, split: the passes' contractions
+// are the bf16-split ones
+bool resident_fits(int n, int kw, int G, bool lots, int m, int ncap, int max_held, bool asset_box,
+                   bool split, int n_cu);
 hipError_t launch_resident_setup(const ResRowArgs& A, int kp, int KQ, const float* Bt, float4* Bq,
                                  hipStream_t st);
 hipError_t launch_resident(const ResArgs& A, int KQ, int m_total, int count, hipStream_t st);

@@ -462,25 +462,37 @@ int resident_kq(int kw) {
 
 // Which books: the resident block wins while one compute unit streams the
 // account's share of B~ faster than four launches drain.  Both sides in us
-// an iteration, fitted to measurements over n = 100 .. 16,000, 6 .. 91
-// columns and 1 .. 500 accounts (resident / four passes):
+// an iteration, fitted to measurements over n = 64 .. 16,384, 6 .. 96 columns, 1 ..
+// 4,096 accounts, 100 held names an account and all of them (resident / four
+// passes):
 //   no cap:  100 x 6, 1 account 1.5 / 13.2;  481 x 21, 128 accounts 2.4 / 18;
 //            2,000 x 51, 128: 7.5 / 26;  5,000 x 71, 128: 17 / 37;
-//            5,000 x 91, 500: 45 / 58;  10,000 x 81, 1: 32 / 26, 128: 36 / 46
+//            128 x 6, 4,096: 23 / 60;  10,000 x 81, 1: 32 / 26, 128: 36 / 46
+//            8,192 x 56, 1,024: 88 / 68 with 100 held names, / 133 with all
 //   caps:    481 x 21, 128: 6.3 / 22;  2,000 x 51, 128: 19 / 29;
 //            4,000 x 41, 1: 25 / 21, 128: 26 / 29;  10,000 x 81: 76 / 29
-// A capped account streams B~ twice and searches its rows; more accounts
-// than compute units take further rounds of workgroups.
-bool resident_fits(int n, int kw, int G, bool lots, int m, int ncap, int n_cu) {
+//            2,048 x 6, 512: 48 / 39 with lots on every name (24 without)
+// A capped account streams B~ twice and searches its rows, their lots from
+// memory past the first few hundred; more accounts than compute units take
+// further rounds of workgroups.  The four passes cost by the launches and the
+// workgroups an account takes, and by the entries: four times as much an entry
+// where PROX cannot hold the held names in LDS or walks per-asset bounds, or with
+// float32 contractions (at one price for all, books of few held names took blocks
+// up to 1.46 times as long).
+bool resident_fits(int n, int kw, int G, bool lots, int m, int ncap, int max_held, bool asset_box,
+                   bool split, int n_cu) {
   if (kw > 96) return false;
   const int tiles = (n + 63) / 64;
   const size_t smem = sizeof(float) * ((size_t)tiles * 64 * (lots ? 2 : 1) + (size_t)kw * G);
   if (smem > 140 * 1024) return false;
   const double stream = 0.011 * tiles * resident_kq(kw);
   const double rounds = n_cu > 0 ? (double)((m + n_cu - 1) / n_cu) : 1.0;
-  const double res = rounds * (ncap > 0 ? 3.5 + 2.0 * stream + 0.0022 * n : 1.6 + stream);
+  const double far_lots = lots && max_held > 512 ? 0.004 * (max_held - 512) : 0.0;
+  const double res = rounds * (ncap > 0 ? 3.5 + 2.0 * stream + 0.0022 * n + far_lots
+                                        : 1.6 + stream * (lots ? 1.05 : 1.0));
+  const double entry = max_held > 1024 || asset_box || !split ? 1.2e-5 : 3e-6;
   const double four = 13.0 + 0.1 * kw + (m > 8 ? 4.0 : 0.0) + 6e-4 * n +
-                      (ncap > 0 ? 7e-6 : 1.2e-5) * (double)n * m;
+                      (ncap > 0 ? 7e-6 * (double)n * m : entry * (double)n * m + 0.01 * m);
   return res < 0.95 * four;
 }
 

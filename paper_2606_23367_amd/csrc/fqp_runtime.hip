@@ -797,7 +797,8 @@ extern "C" fqp_error fqp_solve_batch(fqp_handle* h, const fqp_universe* U, const
   // when their launches are to be timed)
   const bool lots = P->tax_ptr != nullptr;
   const bool resident =
-      !S.profile && resident_fits(n, kg + 1, G, lots, m, h->hcount[8], h->n_cu);
+      !S.profile && resident_fits(n, kg + 1, G, lots, m, h->hcount[8], max_held,
+                                  P->lb_asset != nullptr, split, h->n_cu);
   const bool wide = !S.profile && !resident && wide_fits(n, kp, m, h->hcount[8], split);
   const int KQ = resident ? resident_kq(kg + 1) : 0;
   const int ntile = (n + 63) / 64, npr = 64 * ntile;
