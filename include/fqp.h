@@ -134,8 +134,11 @@ typedef struct fqp_book {
   const float *eta;          /* [m] return scale eta >= 0; NULL = 1          */
 } fqp_book;
 
-/* Arithmetic of the factor contractions inside the ADMM iterations (the
- * polish and the certificate are float64 either way). */
+/* Arithmetic of the factor contractions inside the ADMM iterations, where a
+ * block of them runs as the four passes PROX, CONTRACT, factor-space solve and
+ * PROJECT (the polish and the certificate are float64 either way).  A block that
+ * one workgroup runs for its account (small books) contracts in float32 whatever
+ * is set. */
 typedef enum {
   FQP_PREC_FP32 = 0,    /* float32 MFMA (32x32x2)                           */
   FQP_PREC_BF16X3 = 1   /* bf16 MFMA on hi/lo splits of each float32 operand:
@@ -161,7 +164,11 @@ typedef struct fqp_settings {
   int32_t profile;       /* bit 0: time every PROJECT-pass launch, bit 1:
                             every CONTRACT-pass launch, bit 2: every PROX-
                             pass launch, with events that the kernel's own
-                            start and end stamp (no graphs)                */
+                            start and end stamp (no graphs).  A call with
+                            any bit set runs the four passes, also on books
+                            whose blocks take another form otherwise: it
+                            times those launches, not that form, and on
+                            small books the iterates round differently      */
   double time_limit_ms;  /* wall-clock limit of the call (<= 0: none)     */
   int32_t precision;     /* fqp_precision of the ADMM contractions        */
   int32_t first_check;   /* iteration of the first polish / certification
@@ -182,7 +189,9 @@ typedef struct fqp_settings {
                             untouched.  0 in production                    */
   int32_t tile_rows;     /* rows of one iteration-pass workgroup, in 128-row
                             chunks (0: sized from the occupancy so that a
-                            full batch runs in one round of workgroups)    */
+                            full batch runs in one round of workgroups);
+                            without effect where one workgroup runs an
+                            account's block                                */
 } fqp_settings;
 
 /* Outputs (device pointers, caller-owned).  Any may be NULL except w and
@@ -217,8 +226,12 @@ static inline size_t fqp_state_floats(int32_t m, int32_t n, int32_t n_groups) {
 /* Host-side counters of the last fqp_solve_batch call. */
 typedef struct fqp_stats {
   int32_t iterations;       /* ADMM iterations run (max over accounts)      */
-  int32_t iter_launches;    /* fused iteration kernel launches              */
-  int32_t polish_calls;     /* polish / certification kernel launches       */
+  int32_t iter_launches;    /* ADMM iterations launched (a block counts each
+                               of its iterations, whatever form it takes)   */
+  int32_t polish_calls;     /* polish / certification launches: one a pass
+                               where one workgroup runs all rounds of its
+                               account's pass (up to 5,120 assets), else
+                               one a refinement round                       */
   int32_t n_solved;         /* accounts with status SOLVED                  */
   double iter_kernel_ms;    /* summed execution time of the PROJECT-pass
                                launches (settings.profile bit 0, else 0)   */
