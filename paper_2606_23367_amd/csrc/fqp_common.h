@@ -105,16 +105,20 @@ __device__ __forceinline__ double lane_d(double x, int l) {
   return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
 }
 
-// a / b from the correctly rounded reciprocal ib of b: the quotient with one
-// correction (Markstein), correctly rounded like the division it replaces
-// for finite operands in range, at three operations in a chain of them
+// a / b from a reciprocal ib of b that is right to the last place: the quotient
+// with one correction (Markstein's step), three operations in a chain of them.
+// Correctly rounded where ib is; root_recip's ib is a rounded Newton step, which
+// is that in all but rare cases, but not proven to be: the bound is one unit in the
+// last place, for finite a, b and quotient (b or a * ib infinite gives no number,
+// where a division gave 0 or infinity)
 __device__ __forceinline__ double div_by(double a, double b, double ib) {
   const double q = a * ib;
   return fma(fma(-b, q, a), ib, q);
 }
 
-// sqrt(a) and its reciprocal (a normal, positive) from one estimate, refined
-// to the last place: a third of the chain of a root and a division
+// sqrt(a) and its reciprocal (a normal, positive, finite) from one estimate,
+// each within a unit in the last place: a third of the chain of a root and a
+// division
 __device__ __forceinline__ void root_recip(double a, double& d, double& id) {
   double y = __builtin_amdgcn_rsq(a);
   y = fma(0.5 * y, fma(-a * y, y, 1.0), y);

@@ -411,14 +411,6 @@ __device__ __forceinline__ double row_coef(const Args& A, int i, int g) {
   return g < A.Gl ? (A.group[i] == g ? 1.0 : 0.0) : (double)A.Bt[(size_t)i * A.kp + A.k + g];
 }
 
-// sum_g (row g at asset i) x[g] over every constraint row
-template <typename Args>
-__device__ __forceinline__ double rows_dot(const Args& A, int i, const double* x) {
-  double s = A.Gl ? x[A.group[i]] : 0.0;
-  for (int g = A.Gl; g < A.G; ++g) s += (double)A.Bt[(size_t)i * A.kp + A.k + g] * x[g];
-  return s;
-}
-
 // mu' = eta mu + gamma Sigma w_b and (gamma/2) w_b^T Sigma w_b per account
 // (the benchmark term of Eq. 1 expanded)
 hipError_t launch_benchmark_prep(int m, int n, int k, const float* B, const float* f,

@@ -342,8 +342,8 @@ __device__ __forceinline__ double bsum(double v, double* sh) {
   return sv[0];
 }
 
-// row_coef / rows_dot with the row's label already loaded (grp, unused
-// without band rows)
+// row_coef with the row's label already loaded (grp, unused without band rows),
+// and the sum of all constraint rows' coefficients at row i times x
 __device__ __forceinline__ double row_coef_g(const PolishArgs& A, int i, int grp, int g) {
   return g < A.Gl ? (grp == g ? 1.0 : 0.0) : (double)A.half[(size_t)(g - A.Gl) * A.n + i];
 }
@@ -1531,11 +1531,12 @@ __global__ __launch_bounds__(256) void polish_gbase_kernel(PolishArgs A, int fin
 
 // ---------------------------------------------------------------------------
 // polish_check: external diagnostics in float64 and refinement, after the
-// gradient base, in four launches: the null-direction sweep rows (row
-// blocks; the common case of one open direction), polish_pre (per account:
-// the gradient scale and the sweep decisions), the diagnostic rows (row
-// blocks: residual partials and refinement proposals) and polish_decide
-// (per account: the certificate and the refinement decisions)
+// gradient base: the null-direction sweep rows (row blocks; the common case
+// of one open direction), polish_pre (per account: the gradient scale and the
+// sweep decisions), for accounts of many row blocks polish_dir (a launch for each
+// of several open directions), the diagnostic rows (row blocks: residual
+// partials and refinement proposals) and polish_decide (per account: the
+// certificate and the refinement decisions)
 // ---------------------------------------------------------------------------
 
 // Along a stored null direction v of the free-row equations the free rows
@@ -1866,10 +1867,10 @@ __device__ __forceinline__ void sweep_one(const PolishArgs& A, int a, int tid, c
 
 // per account: the gradient scale (from polish_gbase's blocks), then the
 // multipliers the free rows leave open (one direction: from the sweep
-// blocks; more: swept here, twice, as the directions interact); stores the
-// multipliers, the row to release and the scale for the passes after it
+// blocks; more: swept here one after another, from kSplitDir row blocks on by
+// polish_dir instead); stores the multipliers, the row to release and the scale
+// for the passes after it
 __global__ __launch_bounds__(kPTC) void polish_pre_kernel(PolishArgs A, int final_pass) {
-  __shared__ double shd[kPW];
   __shared__ double s_red6[6 * kPW];
   __shared__ StepRows R;
   __shared__ double mult[2 + kMaxG];
