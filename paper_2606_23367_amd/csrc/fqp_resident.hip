@@ -471,7 +471,7 @@ int resident_kq(int kw) {
 //            8,192 x 56, 1,024: 88 / 68 with 100 held names, / 133 with all
 //   caps:    481 x 21, 128: 6.3 / 22;  2,000 x 51, 128: 19 / 29;
 //            4,000 x 41, 1: 25 / 21, 128: 26 / 29;  10,000 x 81: 76 / 29
-//            2,048 x 6, 512: 48 / 39 with lots on every name (24 without)
+//            2,048 x 6, 512: 48 / 39 with lots on every name, 27 / 34 without
 // A capped account streams B~ twice and searches its rows, their lots from
 // memory past the first few hundred; more accounts than compute units take
 // further rounds of workgroups.  The four passes cost by the launches and the
